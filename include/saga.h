@@ -140,6 +140,13 @@ typedef struct saga_timings {
  */
 saga_status saga_create(saga_ctx** out, int device, void* hip_stream, size_t hbm_budget_bytes);
 saga_status saga_destroy(saga_ctx* ctx);
+/*
+ * Enqueue later calls on hip_stream (NULL: the default stream of the context's device). With ordered = 1 they run after
+ * everything the context has enqueued so far: its workspaces are shared by all its calls. With ordered = 0 the caller sees
+ * to that, or records into a graph what it enqueues there. Nothing happens if the context is on that stream already. The
+ * stream must exist as long as the context is on it.
+ */
+saga_status saga_set_stream(saga_ctx* ctx, void* hip_stream, int32_t ordered);
 
 /*
  * Ingest a CSC graph (Section 3.1). col_ptr is int64 [n_vertices + 1], row_idx

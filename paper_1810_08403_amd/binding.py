@@ -7,6 +7,7 @@ library is missing: there is no CPU fallback.
 from __future__ import annotations
 
 import atexit
+import contextlib
 import ctypes
 import os
 import sys
@@ -27,7 +28,7 @@ EDGE_OP = {"copy": 0, "mul_weight": 1, "gated": 2, "pool": 3}
 MEM_DEVICE, MEM_HOST = 0, 1
 
 # every entry point include/saga.h declares
-EXPORTS = ["saga_create", "saga_destroy", "saga_graph_create_csc", "saga_graph_destroy",
+EXPORTS = ["saga_create", "saga_destroy", "saga_set_stream", "saga_graph_create_csc", "saga_graph_destroy",
            "saga_graph_set_edge_data", "saga_layer_forward", "saga_layer_forward_noalloc", "saga_layer_backward", "saga_set_profiling", "saga_reset_timings",
            "saga_get_timings", "saga_set_option", "saga_peak_device_bytes", "saga_last_error",
            "saga_graph_info", "saga_plan_work_list", "saga_plan_reencoding", "saga_copy_bytes", "saga_version"]
@@ -110,6 +111,8 @@ def declare_signatures(L: ctypes.CDLL) -> ctypes.CDLL:
     L.saga_create.argtypes = [ctypes.POINTER(P), ctypes.c_int, P, SZ]
     L.saga_destroy.restype = I32
     L.saga_destroy.argtypes = [P]
+    L.saga_set_stream.restype = I32
+    L.saga_set_stream.argtypes = [P, P, I32]
     L.saga_graph_create_csc.restype = I32
     L.saga_graph_create_csc.argtypes = [P, I64, I64, P, P, I32, ctypes.POINTER(P)]
     L.saga_graph_destroy.restype = I32
@@ -181,9 +184,8 @@ class Graph:
     def set_edge_data(self, w: torch.Tensor):
         assert w.dtype == torch.float32 and w.is_contiguous() and w.numel() == self.nnz
         assert w.is_cuda == self.on_device
-        if w.is_cuda:
-            self.ctx.stream.wait_stream(torch.cuda.current_stream(self.ctx.device))
-        self.ctx._check(self.ctx.lib.saga_graph_set_edge_data(self._h, w.data_ptr()))
+        with self.ctx._on_stream():
+            self.ctx._check(self.ctx.lib.saga_graph_set_edge_data(self._h, w.data_ptr()))
 
     def info(self):
         a, b, c = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
@@ -207,10 +209,12 @@ class Graph:
 class Context:
     """saga_ctx on one GPU.
 
-    The library enqueues on `stream`, a torch.cuda.Stream of default priority
-    (a fresh one unless given). layer_forward orders that stream after torch's
-    current stream and torch's current stream after it, so tensors produced or
-    consumed by torch ops need no extra synchronisation.
+    Calls are ordered like torch ops on torch's current stream, so tensors produced or consumed by torch ops need no
+    extra synchronisation. Where that is the device's default stream and no stream was given, the library enqueues on it.
+    Otherwise it enqueues on `stream`, a torch.cuda.Stream of default priority (a fresh one unless given), ordered after
+    the current stream and the current stream after it: two events a call, 29 of the 59 us of a GCN layer over 4,096
+    vertices and 13 us of its time on the GPU (17 us a call without them). The default stream is followed and no other,
+    because it is the one stream that cannot be destroyed behind the context.
     """
 
     def __init__(self, device: int = 0, stream: Optional["torch.cuda.Stream"] = None, hbm_budget_bytes: int = 0):
@@ -224,11 +228,52 @@ class Context:
             raise SagaError(st, "saga_create failed")
         self._h = h
         self.device = device
+        self._follow = stream is None
+        self._on_default = False  # the library enqueues on the default stream, not on `stream`
         self._graphs = weakref.WeakSet()
         _live_contexts.add(self)
 
     def synchronize(self):
         self.stream.synchronize()
+        if self._on_default:
+            torch.cuda.default_stream(self.device).synchronize()
+
+    def _switch(self, to_default: bool, ordered: bool):
+        self._check(self.lib.saga_set_stream(self._h, None if to_default else self.stream.cuda_stream, 1 if ordered else 0))
+        self._on_default = to_default
+
+    def _enter(self):
+        """Before a library call: the stream to join afterwards (None: nothing to join), and whether to go back to the
+        default stream then."""
+        cur = torch.cuda.current_stream(self.device)
+        if self._follow and cur.cuda_stream == 0:
+            if not self._on_default:
+                self._switch(True, ordered=True)
+            return None, False
+        back = False
+        if self._on_default:
+            # What is being captured runs when the graph is launched, behind whatever its stream is behind then; an event
+            # from outside the capture must not enter it.
+            back = torch.cuda.is_current_stream_capturing()
+            self._switch(False, ordered=not back)
+        if cur == self.stream:
+            return None, back
+        self.stream.wait_stream(cur)
+        return cur, back
+
+    def _leave(self, cur, back):
+        if cur is not None:
+            cur.wait_stream(self.stream)
+        if back:
+            self._switch(True, ordered=False)
+
+    @contextlib.contextmanager
+    def _on_stream(self):
+        state = self._enter()
+        try:
+            yield
+        finally:
+            self._leave(*state)
 
     def _check(self, st: int):
         if st != SAGA_OK:
@@ -243,10 +288,9 @@ class Context:
         assert col_ptr.is_cuda == row_idx.is_cuda
         g = ctypes.c_void_p()
         where = MEM_DEVICE if col_ptr.is_cuda else MEM_HOST
-        if col_ptr.is_cuda:
-            self.stream.wait_stream(torch.cuda.current_stream(self.device))
-        self._check(self.lib.saga_graph_create_csc(self._h, n, row_idx.numel(), col_ptr.data_ptr(),
-                                                   row_idx.data_ptr(), where, ctypes.byref(g)))
+        with self._on_stream():
+            self._check(self.lib.saga_graph_create_csc(self._h, n, row_idx.numel(), col_ptr.data_ptr(),
+                                                       row_idx.data_ptr(), where, ctypes.byref(g)))
         graph = Graph(self, g.value, n, row_idx.numel(), col_ptr.is_cuda)
         self._graphs.add(graph)
         return graph
@@ -272,13 +316,12 @@ class Context:
         vp = VertexParams(ctypes.pointer(tw) if tw is not None else None,
                           ctypes.pointer(tb) if tb is not None else None, ACT[act], 0,
                           ctypes.pointer(tws) if tws is not None else None)
-        cur = torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            self.stream.wait_stream(cur)
         entry = self.lib.saga_layer_forward_noalloc if no_alloc else self.lib.saga_layer_forward
-        self._check(entry(self._h, g._h, ctypes.byref(tx), ctypes.byref(ep), AGG[agg], ctypes.byref(vp), ctypes.byref(ty), _ref(tacc)))
-        if cur != self.stream:
-            cur.wait_stream(self.stream)
+        state = self._enter()
+        try:
+            self._check(entry(self._h, g._h, ctypes.byref(tx), ctypes.byref(ep), AGG[agg], ctypes.byref(vp), ctypes.byref(ty), _ref(tacc)))
+        finally:
+            self._leave(*state)
         return Y
 
     def layer_backward(self, g: Graph, A: torch.Tensor, dY: torch.Tensor, W: torch.Tensor, dW: torch.Tensor,
@@ -302,23 +345,20 @@ class Context:
                         ptr(twg), ptr(tbg), ptr(twm), ptr(twp), ptr(tbp))
         vp = VertexParams(ptr(tw), ptr(tb), ACT[act], 0, ptr(tws))
         grads = LayerGrads(ptr(tdx), ptr(tdw), ptr(tdb), ptr(tdws), ptr(tdwg), ptr(tdbg), ptr(tdwm), ptr(tdwp), ptr(tdbp))
-        cur = torch.cuda.current_stream(self.device)
-        if cur != self.stream:
-            self.stream.wait_stream(cur)
-        self._check(self.lib.saga_layer_backward(self._h, g._h, _ref(tx), _ref(ta), _ref(ty), _ref(tdy), ctypes.byref(ep),
-                                                 AGG[agg], ctypes.byref(vp), ctypes.byref(grads)))
-        if cur != self.stream:
-            cur.wait_stream(self.stream)
+        state = self._enter()
+        try:
+            self._check(self.lib.saga_layer_backward(self._h, g._h, _ref(tx), _ref(ta), _ref(ty), _ref(tdy), ctypes.byref(ep),
+                                                     AGG[agg], ctypes.byref(vp), ctypes.byref(grads)))
+        finally:
+            self._leave(*state)
         return dW
 
     def copy_bytes(self, dst: torch.Tensor, src: torch.Tensor):
         """Plain copy kernel on the library's stream (counter calibration)."""
         nbytes = src.numel() * src.element_size()
         assert dst.numel() * dst.element_size() == nbytes and dst.is_cuda and src.is_cuda
-        cur = torch.cuda.current_stream(self.device)
-        self.stream.wait_stream(cur)
-        self._check(self.lib.saga_copy_bytes(self._h, dst.data_ptr(), src.data_ptr(), nbytes))
-        cur.wait_stream(self.stream)
+        with self._on_stream():
+            self._check(self.lib.saga_copy_bytes(self._h, dst.data_ptr(), src.data_ptr(), nbytes))
 
     def set_profiling(self, on: bool):
         self._check(self.lib.saga_set_profiling(self._h, 1 if on else 0))

@@ -1217,13 +1217,13 @@ saga_status saga_create(saga_ctx** out, int device, void* hip_stream, size_t hbm
             delete c;
             return SAGA_ERR_HIP;
         }
-        c->own_stream = true;
+        c->made_stream = c->stream;
     }
     // the static scratch array has its own copy, at its own address, on every GPU: ask for this device's, with this device current
     void* sp = nullptr;
     if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp) {
         (void)hipGetLastError();
-        if (c->own_stream) (void)hipStreamDestroy(c->stream);
+        if (c->made_stream) (void)hipStreamDestroy(c->made_stream);
         delete c;
         return SAGA_ERR_HIP;
     }
@@ -1251,8 +1251,25 @@ saga_status saga_destroy(saga_ctx* ctx)
         for (auto& e : es.ev) (void)hipEventDestroy(e);
         (void)hipEventDestroy(es.ev_dense);
     }
-    if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
+    if (ctx->ev_switch) (void)hipEventDestroy(ctx->ev_switch);
+    if (ctx->made_stream) (void)hipStreamDestroy(ctx->made_stream);
     delete ctx;
+    return SAGA_OK;
+}
+
+saga_status saga_set_stream(saga_ctx* ctx, void* hip_stream, int32_t ordered)
+{
+    if (!ctx) return SAGA_ERR_INVALID_ARG;
+    if (ordered != 0 && ordered != 1) return ctx->fail(SAGA_ERR_INVALID_ARG, "ordered must be 0 or 1");
+    const hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (s == ctx->stream) return SAGA_OK;
+    DeviceGuard guard(ctx->device);
+    if (ordered) {
+        if (!ctx->ev_switch) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->ev_switch, hipEventDisableTiming));
+        HIP_TRY(ctx, hipEventRecord(ctx->ev_switch, ctx->stream));
+        HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_switch, 0));
+    }
+    ctx->stream = s;
     return SAGA_OK;
 }
 

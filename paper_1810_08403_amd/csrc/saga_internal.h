@@ -179,7 +179,8 @@ struct DevBuf {
 struct saga_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
-    bool own_stream = false;
+    hipStream_t made_stream = nullptr;  // the one saga_create made, if the caller gave none
+    hipEvent_t ev_switch = nullptr;     // orders a new stream after the one before it (saga_set_stream)
     size_t budget = 0;
     size_t cur_bytes = 0, peak_bytes = 0;
     std::string err;

@@ -1,0 +1,51 @@
+"""Calls follow torch's current stream: the library runs on the default stream itself, and on a stream of its own, joined by
+events, under any other. Its workspaces are shared by all calls of a context, so switching must keep calls in order."""
+import pytest
+import torch
+
+import saga_inputs as si
+from helpers import new_context
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("given", [False, True])   # the library's own choice of stream, a stream given at creation
+def test_alternating_streams_without_host_waits(given):
+    import paper_1810_08403_amd as saga
+    wl = si.workload(2, scale=13, f_in=96, f_out=40)
+    n = wl.graph.n
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    ctx = saga.Context(0, stream=other) if given else saga.Context(0)
+    h = ctx.graph_create_csc(n, wl.graph.col_ptr.cuda(), wl.graph.row_idx.cuda())
+    w, W = wl.edge_weight.cuda(), wl.W.cuda()
+    layer = lambda x, y: ctx.layer_forward(h, x, y, edge_op="mul_weight", edge_weight=w, W=W, act="relu")
+    X = [torch.randn(n, 96, device="cuda") for _ in range(12)]
+    want = []
+    for x in X:
+        want.append(torch.empty(n, 40, device="cuda"))
+        layer(x, want[-1])
+        torch.cuda.synchronize()
+    got = [torch.full((n, 40), float("nan"), device="cuda") for _ in X]
+    graphs = []
+    main = torch.cuda.current_stream()
+    for i, (x, y) in enumerate(zip(X, got)):
+        if i % 3 == 0:                                # default stream, input made just before
+            layer(x + 0.0, y)
+        elif i % 3 == 1:                              # a side stream that does not wait for the call before
+            with torch.cuda.stream(side):
+                layer(x, y)
+        else:                                         # recorded in between: runs at its replay
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                layer(x, y)
+            graphs.append(g)
+    main.wait_stream(side)
+    for k in range(3):
+        for g in graphs:
+            g.replay()
+        layer(X[0], got[0])
+    ctx.synchronize()
+    torch.cuda.synchronize()
+    for i in range(len(X)):
+        assert torch.equal(got[i], want[i]), f"call {i} differs"
+    ctx.destroy()
