@@ -113,6 +113,9 @@ static saga_status run_propagation(saga_ctx* ctx, saga_graph* view, GatherArgs g
     ga.items = static_cast<const WorkItem*>(view->d_items.p);
     ga.n_items = view->n_items;
     ga.n_team = view->n_team;
+    ga.n_light = view->n_light;
+    ga.n_src = view->n;
+    ga.n_edges = view->nnz;
     ga.row_idx = static_cast<const int32_t*>(view->d_row_idx.p);
     ga.dtype = SAGA_F32;
     ga.agg = SAGA_AGG_SUM;
@@ -611,6 +614,9 @@ saga_status resident_backward_bf16(saga_ctx* ctx, saga_graph* g, const saga_tens
         ga.items = static_cast<const WorkItem*>(hybrid ? h.items.p : view->d_items.p);
         ga.n_items = hybrid ? h.n_items : view->n_items;
         ga.n_team = hybrid ? h.n_team : view->n_team;
+        ga.n_light = hybrid ? h.n_light : view->n_light;
+        ga.n_src = view->n;
+        ga.n_edges = hybrid ? h.n_rem_edges : view->nnz;
         ga.row_idx = static_cast<const int32_t*>(hybrid ? h.rem_row_idx.p : view->d_row_idx.p);
         const int64_t n_slots = hybrid ? h.n_slots : view->n_slots, n_heavy = hybrid ? h.n_heavy : view->n_heavy;
         ga.dtype = SAGA_BF16;

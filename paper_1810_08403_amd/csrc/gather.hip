@@ -1022,6 +1022,212 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
 }
 
 // ---------------------------------------------------------------------------
+// light columns (whole ones of up to kLightEdges edges) of rows of <= 32 fragments: one column per lane group, a row's
+// lanes wide, 64 / lanes columns in a wavefront. A column of a dozen edges is one chain of memory round trips (item, ids,
+// rows, result) whatever its width, and with a wavefront of its own most lanes have nothing to do: k_gather_narrow takes
+// 78 us for 262,144 columns of 4 edges at 16 features as at 64, this kernel 20 and 47. Nothing is added up across lanes.
+// The columns of a wavefront are about equally long (see build_work_list) and take the longest one's steps; a step past a
+// column's end reads at an offset past the table, which gives zeros and no traffic (buffer loads check their range), and
+// leaves sum and maximum as they are. Bound: the round trips; then the lines read, like the other kernels.
+// Uniform graph of 262,144 vertices, us, k_gather_narrow and this: 3 features, degree 4 64 and 11, 16 72 and 32; 16 features 78
+// and 20, 91 and 66; 64 features 80 and 47, 147 and 156; 128 features 98 and 92, 313 and 316 (the last ones wait for rows that
+// miss the L2). A layer of 22 bf16 features in training, 524,288 vertices of degree 6: 1013 and 630.
+// NI: ids a lane holds of a batch, so that a batch of a narrow row's few lanes still fills the loads in flight.
+// ---------------------------------------------------------------------------
+struct LightShape {
+    int32_t lpr;      // lanes per group: one fragment of the row each (not a power of two in general)
+    int32_t inv_lpr;  // ceil(2^16 / lpr): lane / lpr for lanes up to 63
+    int32_t groups;   // 64 / lpr columns side by side in a wavefront
+    uint32_t bytes, bytes2, bytes3, id_bytes;  // of the source rows and of the edges
+    int32_t same_ld;  // all source rows have the same stride
+};
+constexpr uint32_t kPastTheEnd = 0xffff0000u;  // an offset past every table this kernel takes, whatever is added for the lane
+
+template <typename T, int VEC>
+__device__ __forceinline__ void load_in_range(Frag<T, VEC>& f, const __amdgpu_buffer_rsrc_t rsrc, const uint32_t off)
+{
+    if constexpr (VEC > 1) {
+        const u32x4_t r = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+        f.r = make_uint4(r.x, r.y, r.z, r.w);
+    } else if constexpr (sizeof(T) == 4) {
+        f.r = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0));
+    } else {
+        f.r = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
+    }
+}
+constexpr int light_loads(int ef, int ni) { return ef == kEfLinear ? (ni == 1 ? 6 : 4) : ni == 1 ? 3 : ni; }
+
+template <typename T, int VEC, bool RAG, int AGG, int EF, int NI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_waves(sizeof(T), AGG, EF, RAG), 8))) void k_gather_light(
+    const GatherArgs a, const LightShape sh)
+{
+    constexpr bool GATED = EF != kEfLinear;
+    constexpr bool ROW3 = ef_third_row(EF);
+    constexpr bool HAS_W = !GATED || EF == kEfMaxGrad;
+    // what an edge past the column's end would add (its rows read as zeros) is left out where that is not nothing
+    constexpr bool MASKED = ef_is_grad(EF) || (EF == kEfGate && AGG == SAGA_AGG_MAX);
+    constexpr int U = light_loads(EF, NI);
+    const int lane = threadIdx.x & 63;
+    const int lpr = sh.lpr;
+    const int grp = min(lane * sh.inv_lpr >> 16, sh.groups - 1);
+    const int sub = lane - grp * lpr;  // lpr and above: lanes left over
+    const int F = a.F;
+    const int nvec = (F + VEC - 1) / VEC;
+    const uint32_t first = (uint32_t)(logical_block(a.xcd_remap) * kWavesPerBlock + (threadIdx.x >> 6)) * (uint32_t)sh.groups;
+    if (first >= (uint32_t)a.n_items) return;
+    int4 it = make_int4(-1, 0, 0, 0);
+    if (first + grp < (uint32_t)a.n_items) it = *reinterpret_cast<const int4*>(a.items + first + grp);
+
+    const bool mine = sub < nvec && it.x >= 0;
+    int col = sub * VEC, skip = 0;
+    if (RAG && col + VEC > F) {  // the row's last fragment
+        skip = col - (F - VEC);
+        col = F - VEC;
+    }
+    const uint32_t lane_off = sub < nvec ? (uint32_t)col * (uint32_t)sizeof(T) : 0u;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.src), 0, sh.bytes, 0x00020000);
+    const auto rsrc2 = GATED ? __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.src2), 0, sh.bytes2, 0x00020000) : rsrc;
+    const auto rsrc3 = ROW3 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.src3), 0, sh.bytes3, 0x00020000) : rsrc;
+    const auto ids = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.row_idx), 0, sh.id_bytes, 0x00020000);
+    const bool weighted = HAS_W && a.edge_w != nullptr;
+    const auto ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.edge_w), 0, weighted ? sh.id_bytes : 0, 0x00020000);
+    const uint32_t ldb = (uint32_t)(a.ld_src * (int64_t)sizeof(T)), ldb2 = GATED ? (uint32_t)(a.ld_src2 * (int64_t)sizeof(T)) : 0,
+                   ldb3 = ROW3 ? (uint32_t)(a.ld_src3 * (int64_t)sizeof(T)) : 0;
+    const bool same_ld = sh.same_ld;
+
+    // a batch of edges of every group: lane `sub` holds edges e + sub * NI .. + NI - 1 of its column
+    auto fetch_batch = [&](const int e, int (&id)[NI], float (&w)[HAS_W ? NI : 1]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int my = e + sub * NI + i;
+            const uint32_t o = sub < lpr && my < it.z ? (uint32_t)my * 4u : 0xfffffff0u;
+            id[i] = __builtin_amdgcn_raw_buffer_load_b32(ids, (int)o, 0, 0);
+            if constexpr (HAS_W) w[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ws, (int)o, 0, 0));
+        }
+    };
+    int id_next[NI];
+    float w_next[HAS_W ? NI : 1];
+    fetch_batch(it.y, id_next, w_next);
+    int steps_left = 0;  // the longest column of the wavefront
+    for (int g = 0; g < sh.groups; ++g) steps_left = max(steps_left, __builtin_amdgcn_readlane(it.z - it.y, g * lpr));
+
+    float acc[VEC], acc2[VEC], pd[VEC], c2[VEC], c3[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        acc[j] = identity<AGG>();
+        acc2[j] = pd[j] = c2[j] = c3[j] = 0.f;
+    }
+    if constexpr (GATED) {
+        Frag<float, VEC> f;
+        f.zero();
+        if (mine) f.template load<RAG>(a.dst + (int64_t)it.x * a.ld_dst + col);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) pd[j] = f.get(j);
+        if constexpr (EF == kEfMaxGrad)
+            if (a.dst_sigmoid) {
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) pd[j] = sigmoid_f32(pd[j]);
+            }
+    }
+    if constexpr (ef_is_grad(EF)) {
+        Frag<float, VEC> f;
+        f.zero();
+        if (mine) f.template load<RAG>(a.dst2 + (int64_t)it.x * a.ld_dst2 + col);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) c2[j] = f.get(j);
+    }
+    if constexpr (ef_third_const(EF)) {
+        Frag<float, VEC> f;
+        f.zero();
+        if (mine) f.template load<RAG>(a.dst3 + (int64_t)it.x * a.ld_dst3 + col);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) c3[j] = f.get(j);
+    }
+    const int batch = lpr * NI;
+    for (int e = it.y; steps_left > 0;) {
+        uint32_t off[NI], off2[GATED ? NI : 1], off3[ROW3 ? NI : 1];
+        float wt[HAS_W ? NI : 1];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const bool valid = sub < lpr && e + sub * NI + i < it.z;
+            off[i] = valid ? (uint32_t)id_next[i] * ldb : kPastTheEnd;
+            if constexpr (GATED) off2[i] = same_ld ? off[i] : valid ? (uint32_t)id_next[i] * ldb2 : kPastTheEnd;
+            if constexpr (ROW3) off3[i] = same_ld ? off[i] : valid ? (uint32_t)id_next[i] * ldb3 : kPastTheEnd;
+            // (a message that is no number leaves a maximum as it is; 0 x 0 leaves a sum)
+            if constexpr (HAS_W) wt[i] = !valid ? (AGG == SAGA_AGG_MAX ? __builtin_huge_valf() : 0.f) : weighted ? w_next[i] : 1.0f;
+        }
+        int from = grp * lpr * 4;
+        // `count` steps of the batch, all loads issued before the first is consumed; the next batch's ids follow the first
+        // of them: loads return in order, and rows are not to wait for ids on their way from memory
+        auto steps = [&](const int count, const bool ask) __attribute__((always_inline)) {
+            Frag<T, VEC> x[U];
+            Frag<T, VEC> m[GATED ? U : 1];
+            Frag<T, VEC> t3[ROW3 ? U : 1];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (k < count) {
+                    const uint32_t o = (uint32_t)__builtin_amdgcn_ds_bpermute(from + 4 * (k / NI), (int)off[k % NI]) + lane_off;
+                    load_in_range(x[k], rsrc, o);
+                    if constexpr (GATED)
+                        load_in_range(m[k], rsrc2, same_ld ? o : (uint32_t)__builtin_amdgcn_ds_bpermute(from + 4 * (k / NI), (int)off2[k % NI]) + lane_off);
+                    if constexpr (ROW3)
+                        load_in_range(t3[k], rsrc3, same_ld ? o : (uint32_t)__builtin_amdgcn_ds_bpermute(from + 4 * (k / NI), (int)off3[k % NI]) + lane_off);
+                }
+            }
+            if (ask) fetch_batch(e + batch, id_next, w_next);
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                if (k < count) {
+                    float w = 1.f;
+                    if constexpr (HAS_W) w = __int_as_float(__builtin_amdgcn_ds_bpermute(from + 4 * (k / NI), __float_as_int(wt[k % NI])));
+                    const bool ok = !MASKED || e + k < it.z;
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j) {
+                        float mv = 0.f, tv = 0.f;
+                        if constexpr (GATED) mv = m[k].get(j);
+                        if constexpr (ROW3) tv = t3[k].get(j);
+                        if constexpr (ef_is_both(EF)) {
+                            float r = acc[j], r2 = acc2[j];
+                            edge_step_both<EF>(r, r2, x[k].get(j), mv, pd[j], c2[j], tv);
+                            acc[j] = ok ? r : acc[j];
+                            acc2[j] = ok ? r2 : acc2[j];
+                        } else {
+                            const float r = edge_step<AGG, EF>(acc[j], w, x[k].get(j), mv, pd[j], c2[j], c3[j]);
+                            acc[j] = ok ? r : acc[j];
+                        }
+                    }
+                }
+            }
+            from += 4 * (U / NI);
+        };
+        const int e_batch = e;
+        int left = min(steps_left, batch);
+        steps_left -= left;
+        const bool ask = steps_left > 0;
+        if (left >= U) {
+            steps(U, ask);
+            e += U;
+            for (left -= U; left >= U; left -= U) {
+                steps(U, false);
+                e += U;
+            }
+            if (left > 0) steps(left, false);
+        } else {
+            steps(left, ask);
+        }
+        e = e_batch + batch;
+    }
+    if (!mine) return;
+    const bool empty = it.y == it.z;
+    if (GATED && empty) {  // whatever its constant rows hold
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[j] = AGG == SAGA_AGG_SUM ? 0.f : acc[j];
+    }
+    store_row<VEC, RAG>(a, it.x, it.w, col, acc, AGG, empty, skip);
+    if constexpr (ef_is_both(EF)) store_row2<VEC, RAG>(a, it.x, it.w, col, acc2, skip);
+}
+
+// ---------------------------------------------------------------------------
 // combine the partial rows of split vertices, in slot order
 // ---------------------------------------------------------------------------
 // One thread per 16-byte fragment of a row (per element when the row does not allow fragments); the rows of as many
@@ -1177,6 +1383,30 @@ __global__ __launch_bounds__(256) void k_validate_columns(const int64_t* col_ptr
 
 int grid_for(int64_t count) { return (int)std::min<int64_t>((count + 255) / 256, 65535 * 8); }
 
+// Bytes of a table of source rows `ld` elements apart, 0 where k_gather_light cannot address it (32-bit offsets)
+uint32_t table_bytes(const GatherArgs& a, int64_t ld, int esize)
+{
+    const int64_t b = a.n_src > 0 ? ((a.n_src - 1) * ld + a.F) * esize : 0;
+    return b <= (int64_t)kPastTheEnd ? (uint32_t)b : 0u;
+}
+// Does k_gather_light take the list's light columns (rows of `vec` elements a fragment, at most 32 of them)?
+template <typename T, bool RAG>
+bool takes_light(const GatherArgs& a, int ef, int vec)
+{
+    if (a.n_light <= 0 || a.n_team > 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
+    // Enough wavefronts for the chip: half of what it holds where they are all there is; twice what it holds beside other
+    // items, which a second launch then waits for (forward and backward, us, without and with: 65,536 uniform vertices of
+    // degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16 and 3 features, 6,000 beside others 950 and
+    // 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT 18, 64 pooled features, 50,000 750 and 684).
+    const int lanes = (a.F + vec - 1) / vec;
+    if (a.n_light / (64 / lanes) < (a.n_light == a.n_items ? 4096 : 16384)) return false;
+    if (!table_bytes(a, a.ld_src, sizeof(T)) || (ef != kEfLinear && !table_bytes(a, a.ld_src2, sizeof(T))) ||
+        (ef_third_row(ef) && !table_bytes(a, a.ld_src3, sizeof(T))))
+        return false;
+    // loads of 16 bytes at the alignment of dwords
+    return sizeof(T) == 4 || !RAG || (a.F % 2 == 0 && a.ld_src % 2 == 0 && (reinterpret_cast<uintptr_t>(a.src) & 3u) == 0);
+}
+
 int ceil_log2(int x)
 {
     int l = 0;
@@ -1184,10 +1414,46 @@ int ceil_log2(int x)
     return l;
 }
 
+// Light columns of rows that fit 32 lanes
+template <typename T, int VEC, bool RAG, int AGG, int EF>
+hipError_t launch_light(const GatherArgs& a, const int lpr, hipStream_t s)
+{
+    LightShape sh{};
+    sh.lpr = lpr;
+    sh.inv_lpr = (65536 + lpr - 1) / lpr;
+    sh.groups = 64 / lpr;
+    sh.bytes = table_bytes(a, a.ld_src, sizeof(T));
+    sh.bytes2 = EF != kEfLinear ? table_bytes(a, a.ld_src2, sizeof(T)) : 0;
+    sh.bytes3 = ef_third_row(EF) ? table_bytes(a, a.ld_src3, sizeof(T)) : 0;
+    sh.id_bytes = (uint32_t)(a.n_edges * 4);
+    sh.same_ld = (EF == kEfLinear || a.ld_src2 == a.ld_src) && (!ef_third_row(EF) || a.ld_src3 == a.ld_src);
+    const int64_t blocks = (a.n_items + (int64_t)kWavesPerBlock * sh.groups - 1) / ((int64_t)kWavesPerBlock * sh.groups);
+    const dim3 grid((unsigned)blocks), block(256);
+    if (lpr >= 8)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1>), grid, block, 0, s, a, sh);
+    else if (lpr >= 4)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 2>), grid, block, 0, s, a, sh);
+    else
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 4>), grid, block, 0, s, a, sh);
+    return hipGetLastError();
+}
+
 template <typename T, int VEC, bool RAG, int AGG, int EF>
 hipError_t launch_shape(const GatherArgs& a, hipStream_t s)
 {
     const int nvec = (a.F + VEC - 1) / VEC;
+    if (nvec <= 32 && takes_light<T, RAG>(a, EF, VEC)) {
+        const int64_t pieces = a.n_items - a.n_light;
+        GatherArgs b = a;
+        b.items = a.items + pieces;
+        b.n_items = a.n_light;
+        hipError_t e = launch_light<T, VEC, RAG, AGG, EF>(b, nvec, s);
+        if (e != hipSuccess || pieces == 0) return e;
+        b = a;
+        b.n_items = pieces;
+        b.n_light = 0;
+        return launch_shape<T, VEC, RAG, AGG, EF>(b, s);
+    }
     const int64_t blocks = a.n_team + (a.n_items - a.n_team + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(256);

@@ -143,9 +143,11 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
     out->heavy.clear();
     out->n_slots = 0;
     out->n_team = 0;
+    out->n_light = 0;
     out->max_degree = 0;
-    std::vector<WorkItem> whole;
-    whole.reserve((size_t)n_cols);
+    std::vector<WorkItem> whole, light;
+    light.reserve((size_t)n_cols);
+    auto add_whole = [&](const WorkItem& it) { (it.e1 - it.e0 > kLightEdges ? whole : light).push_back(it); };
     // A piece's place in the list: the band of its first source, then the band of its last one, then its column. The
     // wavefronts that run at the same time take neighbouring pieces; a piece of a column with few edges per band reaches
     // over many bands, and with the pieces of one first band in column order a band's rows were shared with pieces that
@@ -170,12 +172,12 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
             // partial rows written elsewhere come first; what is left of the column is one more partial row (or none)
             HeavyVertex h{(int32_t)v, (int32_t)out->n_slots, extra + (deg > 0 ? 1 : 0), 0};
             out->n_slots += extra;
-            if (deg > 0) whole.push_back(WorkItem{(int32_t)v, (int32_t)b, (int32_t)e, (int32_t)(out->n_slots++)});
+            if (deg > 0) add_whole(WorkItem{(int32_t)v, (int32_t)b, (int32_t)e, (int32_t)(out->n_slots++)});
             out->heavy.push_back(h);
             continue;
         }
         if (deg <= p.cut_degree) {
-            whole.push_back(WorkItem{(int32_t)v, (int32_t)b, (int32_t)e, -1});
+            add_whole(WorkItem{(int32_t)v, (int32_t)b, (int32_t)e, -1});
             continue;
         }
         const size_t first_piece = pieces.size();
@@ -206,7 +208,7 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
             // one piece after all: its result is the vertex's row. A team still takes it
             // (four wavefronts share the edges); without teams it is an ordinary whole column.
             if (team == 1) {
-                whole.push_back(pieces.back().it);
+                add_whole(pieces.back().it);
                 pieces.pop_back();
             }
             continue;
@@ -221,10 +223,22 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
         if (a.it.v != b.it.v) return a.it.v < b.it.v;
         return a.it.e0 < b.it.e0;
     });
-    out->items.reserve(pieces.size() + whole.size());
+    out->items.reserve(pieces.size() + whole.size() + light.size());
     for (const Piece& pc : pieces) out->items.push_back(pc.it);
     out->n_team = team > 1 ? (int64_t)pieces.size() : 0;
     out->items.insert(out->items.end(), whole.begin(), whole.end());
+    // Columns that are worked side by side in one wavefront are to be equally long: longest first within every 1,024 of
+    // them, which are read at about the same time wherever they stand.
+    out->n_light = (int64_t)light.size();
+    out->items.resize(out->items.size() + light.size());
+    WorkItem* to = out->items.data() + (out->items.size() - light.size());
+    for (size_t i = 0; i < light.size(); i += 1024) {
+        const size_t m = std::min<size_t>(1024, light.size() - i);
+        size_t at[kLightEdges + 2] = {};  // at[k]: where the next column of kLightEdges - k edges goes
+        for (size_t j = i; j < i + m; ++j) ++at[kLightEdges - (light[j].e1 - light[j].e0) + 1];
+        for (int k = 1; k <= kLightEdges; ++k) at[k] += at[k - 1];
+        for (size_t j = i; j < i + m; ++j) to[i + at[kLightEdges - (light[j].e1 - light[j].e0)]++] = light[j];
+    }
 }
 
 // The dense-block plan of a CSC (see HybridPlan). Two passes over the edges, destination tile by destination tile, on
@@ -581,7 +595,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
             ctx->dev_free(&g->saved_lists.front().heavy);
             g->saved_lists.erase(g->saved_lists.begin());
         }
-        g->saved_lists.push_back(saga_graph::SavedList{g->list_params, g->d_items, g->d_heavy, g->n_items, g->n_team, g->n_heavy, g->n_slots});
+        g->saved_lists.push_back(saga_graph::SavedList{g->list_params, g->d_items, g->d_heavy, g->n_items, g->n_team, g->n_light, g->n_heavy, g->n_slots});
         g->d_items = DevBuf{};
         g->d_heavy = DevBuf{};
         g->list_params = WorkListParams{-1, -1, -1, false, 1, 1};
@@ -594,6 +608,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
         g->d_heavy = sl.heavy;
         g->n_items = sl.n_items;
         g->n_team = sl.n_team;
+        g->n_light = sl.n_light;
         g->n_heavy = sl.n_heavy;
         g->n_slots = sl.n_slots;
         g->list_params = sl.params;
@@ -624,6 +639,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // wl goes out of scope below
     g->n_items = (int64_t)wl.items.size();
     g->n_team = wl.n_team;
+    g->n_light = wl.n_light;
     g->n_heavy = (int64_t)wl.heavy.size();
     g->n_slots = wl.n_slots;
     g->list_params = p;
@@ -737,6 +753,7 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     h.n_rem_edges = (int64_t)plan.rem_row_idx.size();
     h.n_items = (int64_t)wl.items.size();
     h.n_team = wl.n_team;
+    h.n_light = wl.n_light;
     h.n_heavy = (int64_t)wl.heavy.size();
     h.n_slots = wl.n_slots;
     h.weights_state = 0;
@@ -1597,6 +1614,9 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     ga.items = static_cast<const WorkItem*>(hybrid ? g->hyb.items.p : g->d_items.p);
     ga.n_items = hybrid ? g->hyb.n_items : g->n_items;
     ga.n_team = hybrid ? g->hyb.n_team : g->n_team;
+    ga.n_light = hybrid ? g->hyb.n_light : g->n_light;
+    ga.n_src = n;
+    ga.n_edges = hybrid ? g->hyb.n_rem_edges : g->nnz;
     ga.row_idx = static_cast<const int32_t*>(hybrid ? g->hyb.rem_row_idx.p : g->d_row_idx.p);
     const int64_t n_slots = hybrid ? g->hyb.n_slots : g->n_slots;
     const int64_t n_heavy = hybrid ? g->hyb.n_heavy : g->n_heavy;
@@ -1713,6 +1733,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         HIP_TRY(ctx, launch_stage_scatter_apply(ga.src, ga.ld_src, ga.dtype, ga.row_idx, ga.edge_w, msg, iota, ga.F, g->nnz, s));
         ga.src = msg;
         ga.ld_src = ga.F;
+        ga.n_src = g->nnz;
         ga.dtype = SAGA_F32;
         ga.row_idx = iota;
         ga.edge_w = nullptr;

@@ -89,11 +89,17 @@ struct HeavyVertex {
     int32_t pad;
 };
 
+// Columns of up to this many edges can be worked several in a wavefront (k_gather_light). Layers, us, with 8 / 16 / 24 / 32 /
+// 48 edges (0: only columns without edges): gated training on R-MAT 18 2148 2113 2098 2111 2121 2120, CommNet training 1071
+// 1066 1060 1050 1045 1045, pooled training 697 686 682 684 693 700, GCN training on 80,207 uniform vertices 131 130 119 117 109 109.
+constexpr int kLightEdges = 24;
+
 struct WorkList {
     std::vector<WorkItem> items;  // team items first (one workgroup each), then solo items (one wavefront each)
     std::vector<HeavyVertex> heavy;
     int64_t n_team = 0;
     int64_t n_slots = 0;
+    int64_t n_light = 0;  // items at the end of the list that are whole columns of at most kLightEdges edges
     int64_t max_degree = 0;
 };
 
@@ -289,7 +295,7 @@ struct HybridDevice {
     DevBuf chunks, blk_src_tile, blk_e0, blk_tile, de_pos, de_edge, de_w, dt_addr, dt_edge, de_tiles, src_tile_ids, tile_row_slot0;
     int64_t n_list_edges = 0, n_tile_edges = 0, n_tiles = 0;
     DevBuf rem_row_idx, rem_edge, rem_w, items, heavy;
-    int64_t n_items = 0, n_team = 0, n_heavy = 0, n_slots = 0;
+    int64_t n_items = 0, n_team = 0, n_light = 0, n_heavy = 0, n_slots = 0;
     int weights_state = 0;                // 0: de_w / rem_w not packed; 1: packed from the attached edge data; 2: packed as all ones (COPY)
 };
 
@@ -300,13 +306,13 @@ struct saga_graph {
     // resident form; the work list is built at the first call for a given
     // (split, cut_degree, stripe_rows) and rebuilt when those change
     DevBuf d_row_idx, d_items, d_heavy, d_edge_data;
-    int64_t n_items = 0, n_team = 0, n_heavy = 0, n_slots = 0, max_degree = 0;
+    int64_t n_items = 0, n_team = 0, n_light = 0, n_heavy = 0, n_slots = 0, max_degree = 0;
     WorkListParams list_params{-1, -1, -1, false, 1};
     // work lists built earlier for other row widths (layers of different width alternate between them)
     struct SavedList {
         WorkListParams params;
         DevBuf items, heavy;
-        int64_t n_items, n_team, n_heavy, n_slots;
+        int64_t n_items, n_team, n_light, n_heavy, n_slots;
     };
     std::vector<SavedList> saved_lists;
     // host form (streamed)
@@ -356,6 +362,8 @@ struct GatherArgs {
     const WorkItem* items;
     int64_t n_items;
     int64_t n_team;          // items [0, n_team) are processed by a whole workgroup each
+    int64_t n_light;         // the last n_light items are whole columns of at most kLightEdges edges (0: not known)
+    int64_t n_src, n_edges;  // rows of src (src2, src3), edges of row_idx; 0: not known
     const int32_t* row_idx;  // source ids, local to the rows of `src`
     const float* edge_w;     // nullable (COPY)
     // LINEAR ops: src = X (dtype), ld_src elements between rows, F features.
