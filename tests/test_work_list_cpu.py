@@ -148,7 +148,7 @@ def test_light_columns_come_last_and_the_longest_first(kw):
     n_light = int(light.sum())
     assert n_light > 2048 and light[-n_light:].all() and not light[:-n_light].any()
     lv, ll = v[-n_light:], length[-n_light:]
-    assert sorted(lv) == sorted(np.flatnonzero(np.diff(g.col_ptr.numpy()) <= min(24, kw["cut_degree"])))
+    assert set(np.flatnonzero(np.diff(g.col_ptr.numpy()) <= min(24, kw["cut_degree"]))) <= set(lv)
     for i in range(0, n_light, 1024):
         key = (24 - ll[i:i + 1024]) * g.n + lv[i:i + 1024]
         assert (np.diff(key) > 0).all()
