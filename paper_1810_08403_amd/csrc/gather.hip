@@ -1393,7 +1393,7 @@ uint32_t table_bytes(const GatherArgs& a, int64_t ld, int esize)
 template <typename T, bool RAG>
 bool takes_light(const GatherArgs& a, int ef, int vec)
 {
-    if (a.n_light <= 0 || a.n_team > 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
+    if (a.n_light <= 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
     // Enough wavefronts for the chip: half of what it holds where they are all there is; twice what it holds beside other
     // items, which a second launch then waits for (forward and backward, us, without and with: 65,536 uniform vertices of
     // degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16 and 3 features, 6,000 beside others 950 and

@@ -224,9 +224,21 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
         return a.it.e0 < b.it.e0;
     });
     out->items.reserve(pieces.size() + whole.size() + light.size());
-    for (const Piece& pc : pieces) out->items.push_back(pc.it);
-    out->n_team = team > 1 ? (int64_t)pieces.size() : 0;
-    out->items.insert(out->items.end(), whole.begin(), whole.end());
+    const bool split_long = team == 1 && p.long_edges > 0;
+    auto is_long = [&](const WorkItem& it) { return it.e1 - it.e0 > p.long_edges; };
+    if (split_long) {
+        for (const Piece& pc : pieces)
+            if (is_long(pc.it)) out->items.push_back(pc.it);
+        for (const WorkItem& it : whole)
+            if (is_long(it)) out->items.push_back(it);
+        out->n_team = (int64_t)out->items.size();
+    } else if (team > 1) {
+        out->n_team = (int64_t)pieces.size();
+    }
+    for (const Piece& pc : pieces)
+        if (!split_long || !is_long(pc.it)) out->items.push_back(pc.it);
+    for (const WorkItem& it : whole)
+        if (!split_long || !is_long(it)) out->items.push_back(it);
     // Columns that are worked side by side in one wavefront are to be equally long: longest first within every 1,024 of
     // them, which are read at about the same time wherever they stand.
     out->n_light = (int64_t)light.size();
@@ -576,15 +588,31 @@ WorkListParams work_list_params(const saga_ctx* ctx, int64_t row_bytes, int32_t 
     return p;
 }
 
+// Items of a resident list that four wavefronts share (WorkListParams::long_edges). Narrow rows fit bands of so many source
+// rows that a hub's column is one piece of thousands of edges, and the launch lasts as long as the one wavefront that works
+// it. Layers, us, with none / items past 128 / 512 / 1,024 edges: two GCN layers in training, 16 and 3 features in the second, 944
+// 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23; wider rows have shorter
+// pieces and gain nothing: CommNet in training, 128 features, 1089 1099 1099 1085.
+static int64_t long_edges(const saga_ctx* ctx, int64_t row_bytes)
+{
+    if (ctx->opt_team || ctx->opt_mma) return 0;  // every piece is shared already; the matrix-unit kernels take no shared items
+    return row_bytes <= 256 ? 128 : 1024;
+}
+
+static bool same_params(const WorkListParams& a, const WorkListParams& b)
+{
+    return a.min_edges == b.min_edges && a.cut_degree == b.cut_degree && a.stripe_rows == b.stripe_rows && a.team == b.team && a.order == b.order &&
+           a.long_edges == b.long_edges;
+}
+
 saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32_t width)
 {
     // source rows that all fit the L2s together (8 x 4 MiB) are not what finer pieces are for: there is no miss to save,
     // only partial rows to add
     const bool table_in_l2 = g->n * std::max<int64_t>(row_bytes, 1) <= (32ll << 20);
-    const WorkListParams p = work_list_params(ctx, row_bytes, table_in_l2 ? 0 : width);
-    auto same = [](const WorkListParams& a, const WorkListParams& b) {
-        return a.min_edges == b.min_edges && a.cut_degree == b.cut_degree && a.stripe_rows == b.stripe_rows && a.team == b.team && a.order == b.order;
-    };
+    WorkListParams p = work_list_params(ctx, row_bytes, table_in_l2 ? 0 : width);
+    p.long_edges = long_edges(ctx, row_bytes);
+    auto same = same_params;
     if (same(p, g->list_params)) return SAGA_OK;
     if (ctx->arena_active)
         return ctx->fail(SAGA_ERR_UNSUPPORTED, "no work list for this row width yet: call saga_layer_forward once with the same shapes first");
@@ -684,10 +712,9 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     const bool wide_rows = row_bytes >= 1024;
     if (!ctx->opt_split_set && wide_rows) p.min_edges = (!ctx->opt_stripe_set && p.stripe_rows > 0) ? 40 : 48;
     if (!ctx->opt_stripe_set && wide_rows && p.stripe_rows > 0) p.stripe_rows *= 2;
+    p.long_edges = long_edges(ctx, row_bytes);
     const HybridParams hp = hybrid_params(ctx);
-    auto same = [](const WorkListParams& a, const WorkListParams& b) {
-        return a.min_edges == b.min_edges && a.cut_degree == b.cut_degree && a.stripe_rows == b.stripe_rows && a.team == b.team && a.order == b.order;
-    };
+    auto same = same_params;
     if (h.built && same(p, h.list_params) && hp.min_block_edges == h.hp.min_block_edges && hp.min_tile_gain == h.hp.min_tile_gain &&
         hp.max_chunk_blocks == h.hp.max_chunk_blocks)
         return SAGA_OK;

@@ -110,6 +110,7 @@ struct WorkListParams {
     bool skip_empty = false;  // leave columns without edges out (streamed chunks: nothing to add)
     int32_t team = 1;         // wavefronts that share one piece of a cut column (1 or 4)
     int32_t order = 1;        // pieces in the list: 0 by first band and column, 1 by first band, last band and column
+    int64_t long_edges = 0;   // team = 1: items of more edges than this are worked by four wavefronts all the same (0: none are)
 };
 // Build the work list of a CSC block whose arrays are on the host
 // (col_ptr[0] = 0; vertex ids and edge offsets are local to the block).
