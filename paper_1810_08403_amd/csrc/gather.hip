@@ -1055,10 +1055,15 @@ __device__ __forceinline__ void load_in_range(Frag<T, VEC>& f, const __amdgpu_bu
         f.r = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
     }
 }
+constexpr int light_min_waves(int elem_bytes, int agg, int ef, bool rag, int ni)
+{
+    const int w = narrow_min_waves(elem_bytes, agg, ef, rag);
+    return ni == 4 && w > 6 ? 6 : elem_bytes == 2 && agg == SAGA_AGG_MAX && ni == 1 ? 5 : w;  // no spills
+}
 constexpr int light_loads(int ef, int ni) { return ef == kEfLinear ? (ni == 1 ? 6 : 4) : ni == 1 ? 3 : ni; }
 
 template <typename T, int VEC, bool RAG, int AGG, int EF, int NI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_waves(sizeof(T), AGG, EF, RAG), 8))) void k_gather_light(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_waves(sizeof(T), AGG, EF, RAG, NI), 8))) void k_gather_light(
     const GatherArgs a, const LightShape sh)
 {
     constexpr bool GATED = EF != kEfLinear;
@@ -1175,6 +1180,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
                 }
             }
             if (ask) fetch_batch(e + batch, id_next, w_next);
+            // Sums by pairs of edges, then by chunk, then all: one chain would round once per edge, where the lane groups of
+            // k_gather_narrow round a handful of times. Error of the result against float64, normal data, here / there: columns
+            // of 2 edges 3.1e-8 / 3.7e-8, of 4 4.1 / 4.6, of 8 4.9 to 5.1 / 4.8 to 5.3, of 16 5.8 to 6.0 / 5.6 to 6.0.
+            constexpr bool TREE = AGG == SAGA_AGG_SUM;
+            float chunk[VEC], chunk2[VEC], pair[VEC], pair2[VEC];
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                chunk[j] = TREE ? 0.f : acc[j];
+                chunk2[j] = 0.f;
+            }
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 if (k < count) {
@@ -1186,17 +1201,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
                         float mv = 0.f, tv = 0.f;
                         if constexpr (GATED) mv = m[k].get(j);
                         if constexpr (ROW3) tv = t3[k].get(j);
-                        if constexpr (ef_is_both(EF)) {
-                            float r = acc[j], r2 = acc2[j];
-                            edge_step_both<EF>(r, r2, x[k].get(j), mv, pd[j], c2[j], tv);
-                            acc[j] = ok ? r : acc[j];
-                            acc2[j] = ok ? r2 : acc2[j];
+                        if constexpr (TREE) {
+                            const bool first = k % 2 == 0;
+                            float r = first ? 0.f : pair[j], r2 = first ? 0.f : pair2[j];
+                            const float was = r, was2 = r2;
+                            if constexpr (ef_is_both(EF))
+                                edge_step_both<EF>(r, r2, x[k].get(j), mv, pd[j], c2[j], tv);
+                            else
+                                r = edge_step<AGG, EF>(r, w, x[k].get(j), mv, pd[j], c2[j], c3[j]);
+                            pair[j] = ok ? r : was;
+                            if constexpr (ef_is_both(EF)) pair2[j] = ok ? r2 : was2;
+                            if (!first || k == count - 1) {
+                                chunk[j] += pair[j];
+                                if constexpr (ef_is_both(EF)) chunk2[j] += pair2[j];
+                            }
                         } else {
-                            const float r = edge_step<AGG, EF>(acc[j], w, x[k].get(j), mv, pd[j], c2[j], c3[j]);
-                            acc[j] = ok ? r : acc[j];
+                            const float r = edge_step<AGG, EF>(chunk[j], w, x[k].get(j), mv, pd[j], c2[j], c3[j]);
+                            chunk[j] = ok ? r : chunk[j];
                         }
                     }
                 }
+            }
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                acc[j] = TREE ? acc[j] + chunk[j] : chunk[j];
+                if constexpr (ef_is_both(EF)) acc2[j] += chunk2[j];
             }
             from += 4 * (U / NI);
         };
@@ -1394,12 +1423,12 @@ template <typename T, bool RAG>
 bool takes_light(const GatherArgs& a, int ef, int vec)
 {
     if (a.n_light <= 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
-    // Enough wavefronts for the chip: half of what it holds where they are all there is; twice what it holds beside other
-    // items, which a second launch then waits for (forward and backward, us, without and with: 65,536 uniform vertices of
+    // Enough wavefronts for the chip: half of what it holds where they are nearly all there is; twice what it holds beside
+    // other items, which a second launch then waits for (forward and backward, us, without and with: 65,536 uniform vertices of
     // degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16 and 3 features, 6,000 beside others 950 and
     // 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT 18, 64 pooled features, 50,000 750 and 684).
     const int lanes = (a.F + vec - 1) / vec;
-    if (a.n_light / (64 / lanes) < (a.n_light == a.n_items ? 4096 : 16384)) return false;
+    if (a.n_light / (64 / lanes) < (16 * (a.n_items - a.n_light) <= a.n_light ? 4096 : 16384)) return false;
     if (!table_bytes(a, a.ld_src, sizeof(T)) || (ef != kEfLinear && !table_bytes(a, a.ld_src2, sizeof(T))) ||
         (ef_third_row(ef) && !table_bytes(a, a.ld_src3, sizeof(T))))
         return false;

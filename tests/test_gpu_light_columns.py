@@ -9,13 +9,13 @@ DEV = "cuda"
 
 
 def _graph(n, heavy, seed):
-    """Degrees 0, 1, 7, 8, 23, 24 in turn (and, with `heavy`, some of 25 and 300, and three at the length from which four
-    wavefronts share an item)."""
+    """Degrees 0 to 16, the edges among them, in turn (and, with `heavy`, some of 17 and 300, and three at the length from
+    which four wavefronts share an item)."""
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
-    deg = torch.tensor([0, 1, 7, 8, 23, 24, 3, 16], device=DEV).repeat((n + 7) // 8)[:n].clone()
+    deg = torch.tensor([0, 1, 7, 8, 15, 16, 3, 13], device=DEV).repeat((n + 7) // 8)[:n].clone()
     if heavy:
-        deg[::97] = 25
+        deg[::97] = 17
         deg[5::4001] = 300
         deg[3], deg[11], deg[19] = 128, 129, 5000
     dst = torch.repeat_interleave(torch.arange(n, device=DEV), deg)

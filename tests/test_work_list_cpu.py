@@ -139,17 +139,17 @@ def test_reencoding_is_deterministic_in_the_seed_and_rejects_bad_tilings():
 
 @pytest.mark.parametrize("kw", [dict(min_edges=64, cut_degree=128, stripe_rows=256), dict(min_edges=16, cut_degree=16, stripe_rows=64)])
 def test_light_columns_come_last_and_the_longest_first(kw):
-    """Whole columns of up to 24 edges end the list, every 1,024 of them in order of length, columns of one length in order."""
+    """Whole columns of up to 16 edges end the list, every 1,024 of them in order of length, columns of one length in order."""
     g = si.workload(2, scale=13).graph
     items, _ = _plan(g, **kw)
     v, e0, e1, slot = items.T.astype(np.int64)
     length = e1 - e0
-    light = (slot < 0) & (length <= 24)
+    light = (slot < 0) & (length <= 16)
     n_light = int(light.sum())
     assert n_light > 2048 and light[-n_light:].all() and not light[:-n_light].any()
     lv, ll = v[-n_light:], length[-n_light:]
-    assert set(np.flatnonzero(np.diff(g.col_ptr.numpy()) <= min(24, kw["cut_degree"]))) <= set(lv)
+    assert set(np.flatnonzero(np.diff(g.col_ptr.numpy()) <= min(16, kw["cut_degree"]))) <= set(lv)
     for i in range(0, n_light, 1024):
-        key = (24 - ll[i:i + 1024]) * g.n + lv[i:i + 1024]
+        key = (16 - ll[i:i + 1024]) * g.n + lv[i:i + 1024]
         assert (np.diff(key) > 0).all()
         assert i == 0 or lv[i:i + 1024].min() > lv[i - 1024:i].max()
