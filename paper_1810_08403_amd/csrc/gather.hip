@@ -18,7 +18,8 @@
 //     are combined in a fixed order, so sums are reproducible.
 //
 // Kernels: k_gather_wide (rows of >= 64 fragments of 16 bytes), k_gather_narrow
-// (fewer: several edges side by side in a wavefront), both templates over the
+// (fewer: several edges side by side in a wavefront), k_gather_light (short
+// columns of such rows: several columns side by side), all templates over the
 // per-edge function; k_gather_wide_mma / k_gather_narrow_mma (optional: bf16
 // sums whose multiply-accumulate runs on the matrix unit); k_combine (partial
 // rows of cut columns); k_stage_scatter / k_stage_apply_edge (the stages one by
@@ -1576,14 +1577,16 @@ hipError_t launch_gather(const GatherArgs& a, hipStream_t s)
     }
     if (a.dtype == SAGA_F32) return launch_rows<float, 4>(a, vec_ok, s);
     if (gated) return hipErrorInvalidValue;
-    if (a.mma && vec_ok && a.agg == SAGA_AGG_SUM && a.n_team == 0 && a.F > 8 * 8 && a.F <= 64 * 8) {
+    if (a.mma && vec_ok && a.agg == SAGA_AGG_SUM && a.F > 8 * 8 && a.F <= 64 * 8) {
         const int64_t blocks = (a.n_items + kWavesPerBlock - 1) / kWavesPerBlock;
         if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+        GatherArgs b = a;
+        b.n_team = 0;  // these kernels share no items: a long one is one wavefront's like any other
         const int nvec = a.F / 8;
         if (nvec > 32)
-            hipLaunchKernelGGL(k_gather_wide_mma, dim3((unsigned)blocks), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(k_gather_wide_mma, dim3((unsigned)blocks), dim3(256), 0, s, b);
         else
-            hipLaunchKernelGGL(k_gather_narrow_mma, dim3((unsigned)blocks), dim3(256), 0, s, a, nvec > 16 ? 5 : 4);
+            hipLaunchKernelGGL(k_gather_narrow_mma, dim3((unsigned)blocks), dim3(256), 0, s, b, nvec > 16 ? 5 : 4);
         return hipGetLastError();
     }
     return launch_rows<uint16_t, 8>(a, vec_ok, s);

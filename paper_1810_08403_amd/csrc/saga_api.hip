@@ -593,10 +593,12 @@ WorkListParams work_list_params(const saga_ctx* ctx, int64_t row_bytes, int32_t 
 // it. Layers, us, with none / items past 128 / 512 / 1,024 edges: two GCN layers in training, 16 and 3 features in the second, 944
 // 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23; wider rows have shorter
 // pieces and gain nothing: CommNet in training, 128 features, 1089 1099 1099 1085.
-static int64_t long_edges(const saga_ctx* ctx, int64_t row_bytes)
+// By the rows per band, which is 4,096 or more at 256 bytes a row and 1 MiB a band, and not by the width itself: widths that
+// share a list go on sharing it.
+static int64_t long_edges(const WorkListParams& p)
 {
-    if (ctx->opt_team || ctx->opt_mma) return 0;  // every piece is shared already; the matrix-unit kernels take no shared items
-    return row_bytes <= 256 ? 128 : 1024;
+    if (p.team > 1) return 0;  // every piece is shared already
+    return p.stripe_rows >= 4096 ? 128 : 1024;
 }
 
 static bool same_params(const WorkListParams& a, const WorkListParams& b)
@@ -611,7 +613,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
     // only partial rows to add
     const bool table_in_l2 = g->n * std::max<int64_t>(row_bytes, 1) <= (32ll << 20);
     WorkListParams p = work_list_params(ctx, row_bytes, table_in_l2 ? 0 : width);
-    p.long_edges = long_edges(ctx, row_bytes);
+    p.long_edges = long_edges(p);
     auto same = same_params;
     if (same(p, g->list_params)) return SAGA_OK;
     if (ctx->arena_active)
@@ -712,7 +714,7 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     const bool wide_rows = row_bytes >= 1024;
     if (!ctx->opt_split_set && wide_rows) p.min_edges = (!ctx->opt_stripe_set && p.stripe_rows > 0) ? 40 : 48;
     if (!ctx->opt_stripe_set && wide_rows && p.stripe_rows > 0) p.stripe_rows *= 2;
-    p.long_edges = long_edges(ctx, row_bytes);
+    p.long_edges = long_edges(p);
     const HybridParams hp = hybrid_params(ctx);
     auto same = same_params;
     if (h.built && same(p, h.list_params) && hp.min_block_edges == h.hp.min_block_edges && hp.min_tile_gain == h.hp.min_tile_gain &&
@@ -1652,7 +1654,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     ga.agg = agg;
     ga.op = pool ? (int32_t)SAGA_EDGE_COPY : ep->op;
     ga.xcd_remap = ctx->opt_xcd_remap;
-    ga.mma = ctx->opt_mma;
+    ga.mma = ctx->opt_mma && !(ctx->opt_team && ga.n_team > 0);
     ga.accumulate = 0;
 
     if (ep->op == SAGA_EDGE_GATED) {

@@ -106,3 +106,34 @@ def test_no_alloc_with_more_packed_weights_than_scratch(op, F, Fm, Fo, with_self
     assert ((Y1.double() - ref).abs() / scale).max().item() <= 1e-5
     h.destroy()
     ctx.destroy()
+
+
+@pytest.mark.parametrize("first,then", [(dict(F=128), dict(F=64)), (dict(F=128), dict(F=128, mma=1))])
+def test_no_alloc_takes_a_list_built_for_another_width_or_without_mma(first, then):
+    """Without bands the work list is the same for every width, and it is the same with and without the matrix unit: the
+    call without allocations takes it (items that four wavefronts share are in it) and gives the ordinary call's bits."""
+    import paper_1810_08403_amd as saga
+    rng = np.random.default_rng(3)
+    n = 6000
+    g = _graph(rng, n, 90000, True)
+    ctx = saga.Context(0)
+    ctx.set_option("stripe_kb", 0)
+    ctx.set_option("cut_degree", 1 << 20)                     # the hub is one long item
+    h = ctx.graph_create_csc(n, g.col_ptr.cuda(), g.row_idx.cuda())
+    X = torch.as_tensor(rng.standard_normal((n, 128)).astype(np.float32)).cuda().bfloat16()
+    out = lambda F: torch.full((n, F), float("nan"), device="cuda")
+    Y = lambda F: torch.empty(n, F, device="cuda", dtype=torch.bfloat16)
+    run = lambda F, A, **kw: ctx.layer_forward(h, X[:, :F].contiguous(), Y(F), edge_op="copy", accum_out=A, **kw)
+    run(first["F"], out(first["F"]))
+    ctx.set_option("mma", then.get("mma", 0))
+    F = then["F"]
+    A0, A1 = out(F), out(F)
+    run(F, A0, no_alloc=True)
+    run(F, A1)
+    torch.cuda.synchronize()
+    assert not torch.isnan(A0).any() and torch.equal(A0, A1)
+    dst, msg = torch.repeat_interleave(torch.arange(n), g.col_ptr.diff()).cuda(), X[g.row_idx.long().cuda(), :F].double()
+    ref, scale = (torch.zeros(n, F, dtype=torch.float64, device="cuda").index_add_(0, dst, v) for v in (msg, msg.abs()))
+    # at most 6,000 additions of exact messages, each off by a unit in the last place at most (the matrix unit truncates)
+    assert ((A0.double() - ref).abs() <= 6000 * 2.0 ** -23 * scale).all()
+    ctx.destroy()
