@@ -1425,9 +1425,10 @@ bool takes_light(const GatherArgs& a, int ef, int vec)
 {
     if (a.n_light <= 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
     // Enough wavefronts for the chip: half of what it holds where they are nearly all there is; twice what it holds beside
-    // other items, which a second launch then waits for (forward and backward, us, without and with: 65,536 uniform vertices of
-    // degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16 and 3 features, 6,000 beside others 950 and
-    // 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT 18, 64 pooled features, 50,000 750 and 684).
+    // other items, which a second launch then waits for (measured with columns of up to 24 edges; forward and backward, us,
+    // without and with: 65,536 uniform vertices of degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16
+    // and 3 features, 6,000 beside others 950 and 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT
+    // 18, 64 pooled features, 50,000 750 and 684).
     const int lanes = (a.F + vec - 1) / vec;
     if (a.n_light / (64 / lanes) < (16 * (a.n_items - a.n_light) <= a.n_light ? 4096 : 16384)) return false;
     if (!table_bytes(a, a.ld_src, sizeof(T)) || (ef != kEfLinear && !table_bytes(a, a.ld_src2, sizeof(T))) ||
