@@ -1034,6 +1034,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
 // and 20, 91 and 66; 64 features 80 and 47, 147 and 156; 128 features 98 and 92, 313 and 316 (the last ones wait for rows that
 // miss the L2). A layer of 22 bf16 features in training, 524,288 vertices of degree 6: 1013 and 630.
 // NI: ids a lane holds of a batch, so that a batch of a narrow row's few lanes still fills the loads in flight.
+// TWO (rows of 17 to 32 fragments, sums): the even and the odd edges of a column in a chain each, added at the end. That is what
+// k_gather_narrow's two lane groups do with such a row, and gives the same bits: which of the two kernels takes a column is a
+// matter of speed alone. (The pairs and chunks of the other form turned bf16 roundings and ReLU decisions of a 256-wide bf16
+// layer in training by their last fp32 bit: 5e-4 of dX and dW. The chains take as long.)
 // ---------------------------------------------------------------------------
 struct LightShape {
     int32_t lpr;      // lanes per group: one fragment of the row each (not a power of two in general)
@@ -1056,23 +1060,27 @@ __device__ __forceinline__ void load_in_range(Frag<T, VEC>& f, const __amdgpu_bu
         f.r = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
     }
 }
-constexpr int light_min_waves(int elem_bytes, int agg, int ef, bool rag, int ni)
+constexpr int light_min_waves(int elem_bytes, int agg, int ef, bool rag, int ni, bool two)
 {
     const int w = narrow_min_waves(elem_bytes, agg, ef, rag);
-    return ni == 4 && w > 6 ? 6 : elem_bytes == 2 && agg == SAGA_AGG_MAX && ni == 1 ? 5 : w;  // no spills
+    return ni == 4 && w > 6 ? 6 : elem_bytes == 2 && two ? 7 : elem_bytes == 2 && agg == SAGA_AGG_MAX && ni == 1 ? 5 : w;  // no spills
 }
-constexpr int light_loads(int ef, int ni) { return ef == kEfLinear ? (ni == 1 ? 6 : 4) : ni == 1 ? 3 : ni; }
+// TWO: an even number, so that a step's place in its chunk says which chain it belongs to (gated training, R-MAT 18 with 128
+// features: 2204 us with 2 as with 3 and one chain, 2215 with 4, which costs wavefronts)
+constexpr int light_loads(int ef, int ni, bool two) { return ef == kEfLinear ? (ni == 1 ? 6 : 4) : two ? 2 : ni == 1 ? 3 : ni; }
 
-template <typename T, int VEC, bool RAG, int AGG, int EF, int NI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_waves(sizeof(T), AGG, EF, RAG, NI), 8))) void k_gather_light(
+template <typename T, int VEC, bool RAG, int AGG, int EF, int NI, bool TWO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_waves(sizeof(T), AGG, EF, RAG, NI, TWO), 8))) void k_gather_light(
     const GatherArgs a, const LightShape sh)
 {
+    constexpr int U = light_loads(EF, NI, TWO);
+    static_assert(!TWO || AGG == SAGA_AGG_SUM, "a maximum does not depend on the order");
+    static_assert(!TWO || (U % 2 == 0 && kLightEdges <= 17), "chunks start at even edges, and one batch of 17 ids holds a column");
     constexpr bool GATED = EF != kEfLinear;
     constexpr bool ROW3 = ef_third_row(EF);
     constexpr bool HAS_W = !GATED || EF == kEfMaxGrad;
     // what an edge past the column's end would add (its rows read as zeros) is left out where that is not nothing
     constexpr bool MASKED = ef_is_grad(EF) || (EF == kEfGate && AGG == SAGA_AGG_MAX);
-    constexpr int U = light_loads(EF, NI);
     const int lane = threadIdx.x & 63;
     const int lpr = sh.lpr;
     const int grp = min(lane * sh.inv_lpr >> 16, sh.groups - 1);
@@ -1117,11 +1125,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
     int steps_left = 0;  // the longest column of the wavefront
     for (int g = 0; g < sh.groups; ++g) steps_left = max(steps_left, __builtin_amdgcn_readlane(it.z - it.y, g * lpr));
 
-    float acc[VEC], acc2[VEC], pd[VEC], c2[VEC], c3[VEC];
+    float acc[VEC], acc2[VEC], odd[VEC], odd2[VEC], pd[VEC], c2[VEC], c3[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
         acc[j] = identity<AGG>();
-        acc2[j] = pd[j] = c2[j] = c3[j] = 0.f;
+        acc2[j] = odd[j] = odd2[j] = pd[j] = c2[j] = c3[j] = 0.f;
     }
     if constexpr (GATED) {
         Frag<float, VEC> f;
@@ -1181,10 +1189,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
                 }
             }
             if (ask) fetch_batch(e + batch, id_next, w_next);
-            // Sums by pairs of edges, then by chunk, then all: one chain would round once per edge, where the lane groups of
-            // k_gather_narrow round a handful of times. Error of the result against float64, normal data, here / there: columns
+            // Without TWO, sums by pairs of edges, then by chunk, then all: one chain would round once per edge, where the lane groups
+            // of k_gather_narrow round a handful of times. Error of the result against float64, normal data, here / there: columns
             // of 2 edges 3.1e-8 / 3.7e-8, of 4 4.1 / 4.6, of 8 4.9 to 5.1 / 4.8 to 5.3, of 16 5.8 to 6.0 / 5.6 to 6.0.
-            constexpr bool TREE = AGG == SAGA_AGG_SUM;
+            constexpr bool TREE = AGG == SAGA_AGG_SUM && !TWO;
             float chunk[VEC], chunk2[VEC], pair[VEC], pair2[VEC];
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
@@ -1202,7 +1210,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
                         float mv = 0.f, tv = 0.f;
                         if constexpr (GATED) mv = m[k].get(j);
                         if constexpr (ROW3) tv = t3[k].get(j);
-                        if constexpr (TREE) {
+                        if constexpr (TWO) {
+                            float& r = k % 2 == 0 ? acc[j] : odd[j];
+                            float& r2 = k % 2 == 0 ? acc2[j] : odd2[j];
+                            const float was = r, was2 = r2;
+                            if constexpr (ef_is_both(EF))
+                                edge_step_both<EF>(r, r2, x[k].get(j), mv, pd[j], c2[j], tv);
+                            else
+                                r = edge_step<AGG, EF>(r, w, x[k].get(j), mv, pd[j], c2[j], c3[j]);
+                            r = ok ? r : was;
+                            if constexpr (ef_is_both(EF)) r2 = ok ? r2 : was2;
+                        } else if constexpr (TREE) {
                             const bool first = k % 2 == 0;
                             float r = first ? 0.f : pair[j], r2 = first ? 0.f : pair2[j];
                             const float was = r, was2 = r2;
@@ -1225,8 +1243,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
             }
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
-                acc[j] = TREE ? acc[j] + chunk[j] : chunk[j];
-                if constexpr (ef_is_both(EF)) acc2[j] += chunk2[j];
+                if constexpr (!TWO) {  // (the chains hold their sums already)
+                    acc[j] = TREE ? acc[j] + chunk[j] : chunk[j];
+                    if constexpr (ef_is_both(EF)) acc2[j] += chunk2[j];
+                }
             }
             from += 4 * (U / NI);
         };
@@ -1248,6 +1268,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
         e = e_batch + batch;
     }
     if (!mine) return;
+    if constexpr (TWO) {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            acc[j] += odd[j];
+            acc2[j] += odd2[j];
+        }
+    }
     const bool empty = it.y == it.z;
     if (GATED && empty) {  // whatever its constant rows hold
 #pragma unroll
@@ -1460,12 +1487,15 @@ hipError_t launch_light(const GatherArgs& a, const int lpr, hipStream_t s)
     sh.same_ld = (EF == kEfLinear || a.ld_src2 == a.ld_src) && (!ef_third_row(EF) || a.ld_src3 == a.ld_src);
     const int64_t blocks = (a.n_items + (int64_t)kWavesPerBlock * sh.groups - 1) / ((int64_t)kWavesPerBlock * sh.groups);
     const dim3 grid((unsigned)blocks), block(256);
-    if (lpr >= 8)
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1>), grid, block, 0, s, a, sh);
+    constexpr bool TWO = AGG == SAGA_AGG_SUM && VEC > 1;
+    if (TWO && lpr > 16)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, TWO>), grid, block, 0, s, a, sh);
+    else if (lpr >= 8)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, false>), grid, block, 0, s, a, sh);
     else if (lpr >= 4)
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 2>), grid, block, 0, s, a, sh);
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 2, false>), grid, block, 0, s, a, sh);
     else
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 4>), grid, block, 0, s, a, sh);
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 4, false>), grid, block, 0, s, a, sh);
     return hipGetLastError();
 }
 

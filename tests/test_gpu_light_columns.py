@@ -129,3 +129,42 @@ def test_gated_and_pooled_layers_both_ways(F, agg):
         for k, v in grads.items():
             assert rel(v, leaf[k[1:]].grad) <= bound, (op, agg, F, k)
     ctx.destroy()
+
+
+@pytest.mark.parametrize("F,dtype", [(68, "f32"), (69, "f32"), (100, "f32"), (127, "f32"), (128, "f32"), (136, "bf16"), (150, "bf16"), (256, "bf16")])
+def test_rows_of_17_to_32_fragments_keep_the_order_of_the_other_kernel(F, dtype):
+    """Such rows lie two side by side in a wavefront of the kernel for columns of any length: one lane group adds up the even
+    edges, the other the odd ones. Several short columns side by side give the same bits, whichever kernel takes them."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    n = 2 * 4 * 4200
+    g = torch.Generator(device=DEV)
+    g.manual_seed(F)
+    # lengths up to the longest such column, and short ones between them: 3.6 edges a column
+    deg = torch.tensor([0, 1, 7, 1, 2, 16, 1, 0, 15, 2, 1, 3, 1, 8, 0, 1, 2, 13, 0, 1, 5, 2, 1, 4], device=DEV).repeat(n // 24)
+    n = deg.numel()
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), deg)
+    key = torch.unique(dst * n + torch.randint(0, n, (dst.numel(),), generator=g, device=DEV))
+    dst = key // n
+    deg = torch.bincount(dst, minlength=n)
+    col_ptr = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    torch.cumsum(deg, 0, out=col_ptr[1:])
+    row_idx = (key - dst * n).int()
+    ctx, h = _ctx(n, col_ptr, row_idx)
+    X = torch.randn(n, F, generator=g, device=DEV).to(tdt)
+    # powers of two: a fused multiply-add rounds like the addition of the product
+    w = 2.0 ** torch.randint(-2, 3, (row_idx.numel(),), generator=g, device=DEV)
+    for weight in (None, w):
+        A = torch.full((n, F), float("nan"), device=DEV)
+        kw = dict(edge_op="mul_weight", edge_weight=weight) if weight is not None else dict(edge_op="copy")
+        if dtype == "f32":
+            ctx.layer_forward(h, X, A, **kw)
+        else:
+            ctx.layer_forward(h, X, torch.empty_like(X), accum_out=A, **kw)
+        chains = [torch.zeros(n, F, device=DEV), torch.zeros(n, F, device=DEV)]
+        for k in range(16):
+            v = torch.nonzero(deg > k).flatten()
+            e = col_ptr[v] + k
+            msg = X[row_idx[e].long()].float()
+            chains[k % 2][v] += msg if weight is None else weight[e][:, None] * msg
+        assert torch.equal(A, chains[0] + chains[1]), (F, dtype, weight is not None)
+    ctx.destroy()
