@@ -98,7 +98,7 @@ void saga_ctx::destroy_stream_set()
 void chunk_grid_drain(saga_ctx* ctx)
 {
     if (ctx->st.s_in) (void)hipStreamSynchronize(ctx->st.s_in);
-    if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
+    (void)hipStreamSynchronize(ctx->stream);  // null is a stream too: the default one
     if (ctx->st.s_out) (void)hipStreamSynchronize(ctx->st.s_out);
 }
 

@@ -75,6 +75,13 @@ extern "C" {
 // a stream's destruction); 2: at random points chosen by a generator seeded with `seed`
 void stub_set_mode(int mode, uint64_t seed);
 void stub_device_synchronize(void);
+// 1: from now on the null handle is the default stream; 0 (as at the start): it is a mistake
+void stub_allow_default_stream(int on);
+// operations that were enqueued on any stream and have not run
+int64_t stub_pending(void);
+// a stream of the test driver's own, for saga_create and saga_set_stream
+hipStream_t stub_stream_create(void);
+void stub_stream_destroy(hipStream_t s);
 // live allocations (device + pinned) and live streams / events, for leak checks at the end of a session
 void stub_live_counts(int64_t* allocations, int64_t* bytes, int64_t* streams, int64_t* events);
 // make the n-th allocation from now on fail once (0: never): error paths

@@ -1,9 +1,10 @@
 """Error paths of the streamed calls on the CPU stand-in of the HIP runtime: the n-th device or pinned allocation of a
 call fails, for n = 1, 2, ... until a call gets through. Every failed call must come back with an error status (never
-a crash, never a half-built tiling that a later call trips over), and the same call repeated without the failure must
-give the oracle's result.
+a crash, never a half-built tiling that a later call trips over), with nothing that the call enqueued still waiting to run
+(the host tensors are the caller's again), and the same call repeated without the failure must give the oracle's result.
 
-  python tests/hoststub/run_alloc_failures.py <library>"""
+  python tests/hoststub/run_alloc_failures.py <library> [own|default|alternate]      which stream the context is on
+  python tests/hoststub/run_alloc_failures.py <library> own 0                        with "overlap" 0"""
 import os
 import sys
 
@@ -23,6 +24,8 @@ from stub_binding import StubContext, dev
 
 def main():
     lib = sys.argv[1]
+    stream = sys.argv[2] if len(sys.argv) > 2 else "own"
+    overlap = int(sys.argv[3]) if len(sys.argv) > 3 else 1
     rng = np.random.default_rng(5)
     n, m = 300, 2500
     g = si.csc_from_lists(n, sorted(set(zip(rng.integers(n, size=m).tolist(), rng.integers(n, size=m).tolist()))))
@@ -41,8 +44,9 @@ def main():
         ref = oracle.layer(cp, ri, X.numpy(), op, w.numpy() if op == "mul_weight" else None, agg="sum", W=W.numpy(), bias=bias.numpy(),
                            act="relu", **okw)
         for mode in (0, 1, 2):
-            ctx = StubContext(lib)
+            ctx = StubContext(lib, stream=stream)
             ctx.set_mode(mode, 3)
+            ctx.set_option("overlap", overlap)
             ctx.set_option("dst_intervals", 2)
             ctx.set_option("src_intervals", 3)
             h = ctx.graph_create_csc(n, g.col_ptr, g.row_idx)
@@ -56,6 +60,7 @@ def main():
                     ok = True
                 except B.SagaError as e:
                     assert e.status in (5, 6), f"{op} mode {mode} allocation {nth}: status {e.status}"
+                    assert ctx.pending() == 0, f"{op} mode {mode} allocation {nth}: {ctx.pending()} operations still to run"
                     ok = False
                     failures += 1
                 ctx.lib.stub_fail_allocation(0)
@@ -78,6 +83,7 @@ def main():
                         ok = True
                     except B.SagaError as e:
                         assert e.status in (5, 6), f"backward mode {mode} allocation {nth}: status {e.status}"
+                        assert ctx.pending() == 0, f"backward mode {mode} allocation {nth}: {ctx.pending()} operations still to run"
                         ok = False
                         failures += 1
                     ctx.lib.stub_fail_allocation(0)

@@ -1,7 +1,7 @@
 """Run seeded random streamed sessions (tests/session_cases.py) on the host code of libsaga built against the CPU
 stand-in of the HIP runtime. Meant to be started as a child process with the AddressSanitizer runtime preloaded:
 
-  python tests/hoststub/run_sessions.py <library> <mode> <first seed> <count> <new_edge_data 0|1>
+  python tests/hoststub/run_sessions.py <library> <mode> <first seed> <count> <new_edge_data 0|1> [own|default|alternate]
 
 mode: 0 operations run when enqueued, 1 as late as the API allows, 2 at seeded random points. Exits non-zero on the
 first failed comparison with the oracle; a memory error ends the process through the sanitizer."""
@@ -24,11 +24,11 @@ from test_gpu_random_cases import _case
 class StubBackend:
     error = B.SagaError
 
-    def __init__(self, lib_path, mode):
-        self.lib_path, self.mode, self.ctxs = lib_path, mode, 0
+    def __init__(self, lib_path, mode, stream):
+        self.lib_path, self.mode, self.stream, self.ctxs = lib_path, mode, stream, 0
 
     def context(self, budget):
-        c = StubContext(self.lib_path, hbm_budget_bytes=budget)
+        c = StubContext(self.lib_path, hbm_budget_bytes=budget, stream=self.stream)
         c.set_mode(self.mode, 77 + self.ctxs)
         self.ctxs += 1
         self.last = c
@@ -52,7 +52,7 @@ class StubBackend:
 
 def main():
     lib, mode, first, count, new_edge_data = sys.argv[1], int(sys.argv[2]), int(sys.argv[3]), int(sys.argv[4]), int(sys.argv[5])
-    be = StubBackend(lib, mode)
+    be = StubBackend(lib, mode, sys.argv[6] if len(sys.argv) > 6 else "own")
     for seed in range(first, first + count):
         # the CPU kernels are stand-ins: the bar only has to tell a right schedule from one that read stale or foreign rows
         streamed_session(be, seed, bool(new_edge_data), _case, log=lambda s: print(s, flush=True) if os.environ.get("SAGA_STUB_VERBOSE") else None,

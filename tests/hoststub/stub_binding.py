@@ -76,7 +76,10 @@ class StubGraph:
 
 
 class StubContext:
-    def __init__(self, lib_path: str, hbm_budget_bytes: int = 0):
+    """stream: "own" (the library makes its stream), "default" (put on the default stream after creation, as the binding does for
+    calls under torch's default stream) or "alternate" (given a stream, and switched between it and the default stream
+    before every layer call, ordered)."""
+    def __init__(self, lib_path: str, hbm_budget_bytes: int = 0, stream: str = "own"):
         self.lib = B.declare_signatures(ctypes.CDLL(lib_path))
         self.lib.stub_set_mode.argtypes = [ctypes.c_int, ctypes.c_uint64]
         self.lib.stub_set_mode.restype = None
@@ -90,11 +93,33 @@ class StubContext:
         self.lib.stub_unregister_device.restype = None
         self.lib.stub_allocator_calls.argtypes = []
         self.lib.stub_allocator_calls.restype = ctypes.c_int64
+        self.lib.stub_allow_default_stream.argtypes = [ctypes.c_int]
+        self.lib.stub_allow_default_stream.restype = None
+        self.lib.stub_pending.argtypes = []
+        self.lib.stub_pending.restype = ctypes.c_int64
+        self.lib.stub_stream_create.argtypes = []
+        self.lib.stub_stream_create.restype = ctypes.c_void_p
+        self.lib.stub_stream_destroy.argtypes = [ctypes.c_void_p]
+        self.lib.stub_stream_destroy.restype = None
+        assert stream in ("own", "default", "alternate")
+        self.lib.stub_allow_default_stream(int(stream != "own"))
+        self._given = self.lib.stub_stream_create() if stream == "alternate" else None
+        self._alternate, self._calls = stream == "alternate", 0
         h = ctypes.c_void_p()
-        st = self.lib.saga_create(ctypes.byref(h), 0, None, hbm_budget_bytes)
+        st = self.lib.saga_create(ctypes.byref(h), 0, self._given, hbm_budget_bytes)
         if st != B.SAGA_OK:
             raise B.SagaError(st, "saga_create failed")
         self._h = h
+        if stream == "default":
+            self._check(self.lib.saga_set_stream(self._h, None, 1))
+
+    def pending(self):
+        return int(self.lib.stub_pending())
+
+    def _next_stream(self):
+        if self._alternate:
+            self._calls += 1
+            self._check(self.lib.saga_set_stream(self._h, None if self._calls % 2 else self._given, 1))
 
     def set_mode(self, mode: int, seed: int = 0):
         self.lib.stub_set_mode(mode, seed)
@@ -141,6 +166,7 @@ class StubContext:
 
     def layer_forward(self, g, X, Y, edge_op="copy", edge_weight=None, W_gate=None, b_gate=None, W_msg=None, W_pool=None, b_pool=None,
                       agg="sum", W=None, bias=None, W_self=None, act="none", accum_out=None, no_alloc=False):
+        self._next_stream()
         keep = [_as_tensor(t) for t in (X, Y, W_gate, b_gate, W_msg, W_pool, b_pool, W, bias, W_self, accum_out)]
         tx, ty, twg, tbg, twm, twp, tbp, tw, tb, tws, tacc = keep
         ew = edge_weight.t if isinstance(edge_weight, Dev) else edge_weight
@@ -155,6 +181,7 @@ class StubContext:
     def layer_backward(self, g, A, dY, W, dW, X=None, Y=None, edge_op="copy", edge_weight=None, agg="sum", bias=None, W_self=None, act="none",
                        dX=None, dbias=None, dW_self=None, W_gate=None, b_gate=None, W_msg=None, dW_gate=None, db_gate=None, dW_msg=None,
                        W_pool=None, b_pool=None, dW_pool=None, db_pool=None):
+        self._next_stream()
         T = _as_tensor
         tx, ta, ty, tdy, tw, tb, tws = T(X), T(A), T(Y), T(dY), T(W), T(bias), T(W_self)
         tdx, tdw, tdb, tdws = T(dX), T(dW), T(dbias), T(dW_self)
@@ -175,3 +202,6 @@ class StubContext:
         if self._h:
             self.lib.saga_destroy(self._h)
             self._h = None
+            if self._given:
+                self.lib.stub_stream_destroy(self._given)
+            self.lib.stub_allow_default_stream(0)

@@ -7,6 +7,9 @@
 // streams therefore shows up as stale data or as a use of freed memory under one of the orders, where the
 // GPU would show it once in thousands of runs.
 //
+// The null handle is the default stream: a queue like the others (the library's own streams do not block on it), once the
+// test driver has said that the context under test is put on it. Until then it is a handle the library forgot to set.
+//
 // Misuse that the real runtime answers with undefined behaviour aborts here with a message: a destroyed
 // stream or event handed back to the API, a free of an unknown pointer, a wait cycle.
 #include <hip/hip_runtime.h>
@@ -84,10 +87,15 @@ uint64_t rnd()
     return x ^ (x >> 31);
 }
 
-void check(hipStream_t s)
+StubStream* g_default = nullptr;  // what the null handle stands for, while that is allowed
+
+// the stream behind a handle
+StubStream* at(hipStream_t s)
 {
-    if (!s) die("null stream (the library creates its streams)");
+    if (!s) s = g_default;
+    if (!s) die("null stream, and the context is on a stream of its own");
     if (!s->alive) die("use of a destroyed stream");
+    return s;
 }
 void check(hipEvent_t e)
 {
@@ -156,10 +164,9 @@ void* alloc_poisoned(size_t bytes)
 
 void stub_enqueue(hipStream_t s, std::function<void()> fn)
 {
-    check(s);
     StubOp op;
     op.fn = std::move(fn);
-    push(s, std::move(op));
+    push(at(s), std::move(op));
 }
 
 extern "C" void stub_set_mode(int mode, uint64_t seed)
@@ -171,11 +178,38 @@ extern "C" void stub_set_mode(int mode, uint64_t seed)
 
 extern "C" void stub_device_synchronize(void) { run_all(); }
 
+extern "C" void stub_allow_default_stream(int on)
+{
+    run_all();
+    if (on && !g_default) {
+        g_default = new StubStream();
+        g_streams.push_back(g_default);
+    } else if (!on && g_default) {
+        g_default->alive = false;
+        g_default = nullptr;
+    }
+}
+
+extern "C" int64_t stub_pending(void)
+{
+    int64_t n = 0;
+    for (StubStream* s : g_streams) n += (int64_t)(s->enq - s->done);
+    return n;
+}
+
+extern "C" hipStream_t stub_stream_create(void)
+{
+    hipStream_t s = nullptr;
+    (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    return s;
+}
+extern "C" void stub_stream_destroy(hipStream_t s) { (void)hipStreamDestroy(s); }
+
 extern "C" void stub_live_counts(int64_t* allocations, int64_t* bytes, int64_t* streams, int64_t* events)
 {
     int64_t b = 0, ns = 0, ne = 0;
     for (auto& kv : g_allocs) b += (int64_t)kv.second;
-    for (StubStream* s : g_streams) ns += s->alive;
+    for (StubStream* s : g_streams) ns += s->alive && s != g_default;
     for (StubEvent* e : g_events) ne += e->alive;
     if (allocations) *allocations = (int64_t)g_allocs.size();
     if (bytes) *bytes = b;
@@ -286,20 +320,21 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
 }
 hipError_t hipStreamDestroy(hipStream_t s)
 {
-    check(s);
+    if (!s) die("the default stream cannot be destroyed");
+    at(s);
     run_until(s, s->enq);  // pending work completes before the stream's resources go
     s->alive = false;
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t s)
 {
-    check(s);
+    s = at(s);
     run_until(s, s->enq);
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
 {
-    check(s);
+    s = at(s);
     check(e);
     if (!e->s) return hipSuccess;  // never recorded: nothing to wait for
     if (!e->s->alive && e->s->done < e->seq) die("wait on an event whose stream was destroyed with the record pending");
@@ -327,7 +362,7 @@ hipError_t hipEventDestroy(hipEvent_t e)
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
     check(e);
-    check(s);
+    s = at(s);
     e->s = s;
     e->seq = s->enq;
     return hipSuccess;
@@ -344,7 +379,7 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b)
 
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t s)
 {
-    check(s);
+    s = at(s);
     if (bytes == 0) return hipSuccess;
     if (!dst || !src) return hipErrorInvalidValue;
     StubOp op;
@@ -355,7 +390,7 @@ hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKin
 hipError_t hipMemcpy2DAsync(void* dst, size_t dpitch, const void* src, size_t spitch, size_t width, size_t height, hipMemcpyKind,
                             hipStream_t s)
 {
-    check(s);
+    s = at(s);
     if (width == 0 || height == 0) return hipSuccess;
     if (!dst || !src || dpitch < width || spitch < width) return hipErrorInvalidValue;
     StubOp op;

@@ -60,8 +60,18 @@ def test_sessions_under_thread_sanitizer():
     assert "ok:" in r.stdout and "ThreadSanitizer" not in r.stderr and "ThreadSanitizer" not in r.stdout, r.stderr[-6000:]
 
 
-def test_failed_allocations_come_back_as_errors(stub_lib):
-    _run("run_alloc_failures.py", stub_lib)
+@pytest.mark.parametrize("stream", ["default", "alternate"])
+@pytest.mark.parametrize("mode", [1, 2])
+def test_random_sessions_on_the_default_stream(stub_lib, mode, stream):
+    """The stream that calls made under torch's default stream run on, all the time or every other call."""
+    _run("run_sessions.py", stub_lib, mode, 2000 + 100 * mode, 15, 1, stream)
+
+
+@pytest.mark.parametrize("stream,overlap", [("own", 1), ("own", 0), ("default", 1), ("default", 0), ("alternate", 1)])
+def test_failed_allocations_come_back_as_errors(stub_lib, stream, overlap):
+    """On the library's own stream and on the default one, with copies on streams of their own and on the same one: nothing is
+    left running over the caller's host tensors."""
+    _run("run_alloc_failures.py", stub_lib, stream, overlap)
 
 
 def test_no_alloc_entry_point_reaches_no_allocator(stub_lib):
