@@ -194,7 +194,7 @@ class Graph:
 
     def destroy(self):
         if self._h:
-            self.ctx.lib.saga_graph_destroy(self._h)
+            self.ctx._release_graph(self._h.value)
             self._h = None
 
     def __del__(self):
@@ -231,6 +231,7 @@ class Context:
         self._follow = stream is None
         self._on_default = False  # the library enqueues on the default stream, not on `stream`
         self._graphs = weakref.WeakSet()
+        self._graph_handles = set()  # what is to be released before the context, whether or not its Graph object can be reached
         _live_contexts.add(self)
 
     def synchronize(self):
@@ -293,7 +294,13 @@ class Context:
                                                        row_idx.data_ptr(), where, ctypes.byref(g)))
         graph = Graph(self, g.value, n, row_idx.numel(), col_ptr.is_cuda)
         self._graphs.add(graph)
+        self._graph_handles.add(g.value)
         return graph
+
+    def _release_graph(self, handle: int):
+        if handle in self._graph_handles:
+            self._graph_handles.remove(handle)
+            self.lib.saga_graph_destroy(handle)
 
     def layer_forward(self, g: Graph, X: torch.Tensor, Y: torch.Tensor, edge_op: str = "copy",
                       edge_weight: Optional[torch.Tensor] = None, W_gate=None, b_gate=None, W_msg=None,
@@ -378,6 +385,9 @@ class Context:
         if self._h:
             for g in list(self._graphs):   # graphs point into the context: release them first
                 g.destroy()
+            # a collector that takes context and graphs together has emptied the weak set already
+            for handle in list(self._graph_handles):
+                self._release_graph(handle)
             self.lib.saga_destroy(self._h)
             self._h = None
 

@@ -1,0 +1,117 @@
+"""What the binding does around the library's calls, with a stand-in for the library and for torch's streams: which call comes
+after which, and which work is ordered behind which."""
+import gc
+
+import pytest
+import torch
+
+from paper_1810_08403_amd import binding as B
+
+
+class Stream:
+    """`seen`: the operations that are done before anything enqueued from now on starts."""
+    def __init__(self, handle):
+        self.cuda_stream, self.seen = handle, set()
+
+    def enqueue(self, what):
+        self.seen.add(what)
+
+    def wait_stream(self, other):
+        self.seen |= other.seen
+
+
+class Library:
+    """Every graph_create is a piece of work on the context's stream; `behind[i]`: what was done before the i-th started."""
+    def __init__(self, streams):
+        self.streams, self.current, self.made = streams, None, Stream("the library's own")
+        self.log, self.behind, self.alive = [], [], set()
+
+    def saga_create(self, out, device, stream, budget):
+        out._obj.value = 77
+        self.alive.add(77)
+        self.current = self.streams[stream.value] if stream.value else self.made
+        return 0
+
+    def saga_set_stream(self, ctx, stream, ordered):
+        to = self.streams[stream or 0]
+        if ordered:
+            to.wait_stream(self.current)
+        self.current = to
+        return 0
+
+    def saga_graph_create_csc(self, ctx, n, nnz, col_ptr, row_idx, where, out):
+        assert 77 in self.alive
+        self.behind.append(set(self.current.seen))
+        self.current.enqueue(("call", len(self.behind) - 1))
+        out._obj.value = 1000 + len(self.behind)
+        self.alive.add(out._obj.value)
+        return 0
+
+    def saga_graph_destroy(self, g):
+        g = getattr(g, "value", g)
+        self.log.append("graph_destroy" if 77 in self.alive else "graph_destroy after its context")
+        self.alive.remove(g)
+        return 0
+
+    def saga_destroy(self, ctx):
+        self.alive.remove(77)
+        self.log.append("destroy")
+        return 0
+
+    def saga_last_error(self, ctx):
+        return b""
+
+
+@pytest.fixture
+def fake(monkeypatch):
+    """(library, streams by handle, what torch's current stream is): handle 0 is the default stream."""
+    streams = {0: Stream(0)}
+    state = {"current": streams[0], "capturing": False}
+
+    def new_stream(device=None):
+        s = Stream(len(streams))
+        streams[s.cuda_stream] = s
+        return s
+
+    lib = Library(streams)
+    monkeypatch.setattr(B, "load_library", lambda: lib)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "Stream", new_stream)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: state["current"])
+    monkeypatch.setattr(torch.cuda, "default_stream", lambda device=None: streams[0])
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
+    return lib, streams, state
+
+
+def _graph(ctx):
+    return ctx.graph_create_csc(1, torch.zeros(2, dtype=torch.int64), torch.zeros(0, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("context_first", [True, False])
+def test_a_context_and_its_graphs_collected_together(fake, context_first):
+    """The collector clears weak references before it calls finalisers, and calls them in any order."""
+    lib = fake[0]
+    gc.collect()
+    ctx = B.Context(0)
+    graphs = [_graph(ctx), _graph(ctx)]
+    if context_first:
+        ctx.cycle = graphs           # (and a graph refers to its context)
+    else:
+        cell = [graphs, ctx]
+        cell.append(cell)
+        del cell
+    del ctx, graphs
+    gc.collect()
+    assert lib.log == ["graph_destroy", "graph_destroy", "destroy"] and not lib.alive
+
+
+def test_graphs_outlive_their_destroyed_context_as_empty_handles(fake):
+    lib = fake[0]
+    ctx = B.Context(0)
+    g, other = _graph(ctx), _graph(ctx)
+    other.destroy()
+    ctx.destroy()
+    assert lib.log == ["graph_destroy", "graph_destroy", "destroy"] and not g._h
+    g.destroy()
+    ctx.destroy()
+    assert len(lib.log) == 3
