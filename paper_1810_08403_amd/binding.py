@@ -233,6 +233,8 @@ class Context:
         self._graphs = weakref.WeakSet()
         self._graph_handles = set()  # what is to be released before the context, whether or not its Graph object can be reached
         _live_contexts.add(self)
+        if self.stream.cuda_stream == 0:  # saga_create takes a null handle as "make a stream"
+            self._check(self.lib.saga_set_stream(h, None, 0))
 
     def synchronize(self):
         self.stream.synchronize()

@@ -115,3 +115,28 @@ def test_graphs_outlive_their_destroyed_context_as_empty_handles(fake):
     g.destroy()
     ctx.destroy()
     assert len(lib.log) == 3
+
+
+def _call(lib, ctx, streams, under):
+    """One call with torch's current stream `under`, after work of the program there; the call's number."""
+    under.enqueue(("before", len(lib.behind)))
+    _graph(ctx)
+    i = len(lib.behind) - 1
+    assert ("before", i) in lib.behind[i], "the call does not wait for what the program enqueued before it"
+    assert ("call", i) in under.seen, "what the program enqueues after the call does not wait for it"
+    return i
+
+
+@pytest.mark.parametrize("given", ["none", "a stream", "the default stream"])
+def test_calls_are_ordered_like_torch_operations(fake, given):
+    """Whichever stream the context was given and whichever is current, also in turn: behind the program's earlier work there,
+    ahead of its later work, and behind the call before (the workspaces are shared)."""
+    lib, streams, state = fake
+    stream = {"none": None, "a stream": torch.cuda.Stream(), "the default stream": streams[0]}[given]
+    ctx = B.Context(0, stream=stream)
+    side = torch.cuda.Stream()
+    for k, under in enumerate([streams[0], streams[0], side, streams[0], side, side, stream or streams[0], streams[0]]):
+        state["current"] = under
+        i = _call(lib, ctx, streams, under)
+        assert k == 0 or ("call", i - 1) in lib.behind[i]
+    ctx.destroy()

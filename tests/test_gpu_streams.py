@@ -4,17 +4,19 @@ import pytest
 import torch
 
 import saga_inputs as si
-from helpers import new_context
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("given", [False, True])   # the library's own choice of stream, a stream given at creation
+# the library's own choice of stream, a stream given at creation, the default stream given at creation (which records no graph)
+@pytest.mark.parametrize("given", [False, True, "default"])
 def test_alternating_streams_without_host_waits(given):
     import paper_1810_08403_amd as saga
     wl = si.workload(2, scale=13, f_in=96, f_out=40)
     n = wl.graph.n
     side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    if given == "default":
+        other = torch.cuda.default_stream()
     ctx = saga.Context(0, stream=other) if given else saga.Context(0)
     h = ctx.graph_create_csc(n, wl.graph.col_ptr.cuda(), wl.graph.row_idx.cuda())
     w, W = wl.edge_weight.cuda(), wl.W.cuda()
@@ -31,7 +33,7 @@ def test_alternating_streams_without_host_waits(given):
     for i, (x, y) in enumerate(zip(X, got)):
         if i % 3 == 0:                                # default stream, input made just before
             layer(x + 0.0, y)
-        elif i % 3 == 1:                              # a side stream that does not wait for the call before
+        elif i % 3 == 1 or given == "default":        # a side stream that does not wait for the call before
             with torch.cuda.stream(side):
                 layer(x, y)
         else:                                         # recorded in between: runs at its replay
