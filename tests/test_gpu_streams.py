@@ -51,3 +51,37 @@ def test_alternating_streams_without_host_waits(given):
     for i in range(len(X)):
         assert torch.equal(got[i], want[i]), f"call {i} differs"
     ctx.destroy()
+
+
+@pytest.mark.parametrize("given", [False, True, "default"])
+def test_workspaces_that_grow_from_stream_to_stream(given):
+    """Every call needs more workspace than the one before and is made under another stream, with no host wait of the test's own
+    between them: a workspace is not given back while a call on the stream before still uses it."""
+    import paper_1810_08403_amd as saga
+    wl = si.workload(2, scale=14, f_in=128, f_out=8)
+    n = wl.graph.n
+    side = torch.cuda.Stream()
+    stream = {False: None, True: torch.cuda.Stream(), "default": torch.cuda.default_stream()}[given]
+    sizes = [(66, 8), (80, 40), (100, 150), (128, 300)]    # one work list: bands of 2,048 rows for all of these widths
+    X = [torch.randn(n, f, device="cuda") for f, _ in sizes]
+    W = [torch.randn(f, fo, device="cuda") for f, fo in sizes]
+    w = wl.edge_weight.cuda()
+    want = []
+    for x, m in zip(X, W):                                 # each with workspaces of its own
+        c = saga.Context(0, stream=stream)
+        want.append(torch.empty(n, m.shape[1], device="cuda"))
+        c.layer_forward(c.graph_create_csc(n, wl.graph.col_ptr.cuda(), wl.graph.row_idx.cuda()), x, want[-1], edge_op="mul_weight", edge_weight=w, W=m)
+        torch.cuda.synchronize()
+        c.destroy()
+    got = [torch.full_like(y, float("nan")) for y in want]
+    torch.cuda.synchronize()
+    ctx = saga.Context(0, stream=stream)
+    h = ctx.graph_create_csc(n, wl.graph.col_ptr.cuda(), wl.graph.row_idx.cuda())
+    for i, (x, m) in enumerate(zip(X, W)):
+        with torch.cuda.stream(side if i % 2 else torch.cuda.default_stream()):
+            ctx.layer_forward(h, x, got[i], edge_op="mul_weight", edge_weight=w, W=m)
+    ctx.synchronize()
+    torch.cuda.synchronize()
+    for i in range(len(X)):
+        assert torch.equal(got[i], want[i]), f"call {i} differs"
+    ctx.destroy()
