@@ -214,16 +214,17 @@ class Context:
     Otherwise it enqueues on `stream`, a torch.cuda.Stream of default priority (a fresh one unless given), ordered after
     the current stream and the current stream after it: two events a call, 29 of the 59 us of a GCN layer over 4,096
     vertices and 13 us of its time on the GPU (17 us a call without them). The default stream is followed and no other,
-    because it is the one stream that cannot be destroyed behind the context.
+    because it is the one stream that cannot be destroyed behind the context. A program that asks for `stream` waits on it or
+    enqueues there: from then on all calls run on it.
     """
 
     def __init__(self, device: int = 0, stream: Optional["torch.cuda.Stream"] = None, hbm_budget_bytes: int = 0):
         self.lib = load_library()
         if not torch.cuda.is_available():
             raise RuntimeError("no GPU visible: libsaga has no CPU path")
-        self.stream = stream if stream is not None else torch.cuda.Stream(device=device)
+        self._stream = stream if stream is not None else torch.cuda.Stream(device=device)
         h = ctypes.c_void_p()
-        st = self.lib.saga_create(ctypes.byref(h), device, ctypes.c_void_p(self.stream.cuda_stream), hbm_budget_bytes)
+        st = self.lib.saga_create(ctypes.byref(h), device, ctypes.c_void_p(self._stream.cuda_stream), hbm_budget_bytes)
         if st != SAGA_OK:
             raise SagaError(st, "saga_create failed")
         self._h = h
@@ -233,16 +234,24 @@ class Context:
         self._graphs = weakref.WeakSet()
         self._graph_handles = set()  # what is to be released before the context, whether or not its Graph object can be reached
         _live_contexts.add(self)
-        if self.stream.cuda_stream == 0:  # saga_create takes a null handle as "make a stream"
+        if self._stream.cuda_stream == 0:  # saga_create takes a null handle as "make a stream"
             self._check(self.lib.saga_set_stream(h, None, 0))
 
     def synchronize(self):
-        self.stream.synchronize()
+        self._stream.synchronize()
         if self._on_default:
             torch.cuda.default_stream(self.device).synchronize()
 
+    @property
+    def stream(self):
+        """The stream that the calls run on: those made so far, those to come, also for a handle that is kept."""
+        self._follow = False
+        if self._h and self._on_default and not torch.cuda.is_current_stream_capturing():  # (else the next call does it)
+            self._switch(False, ordered=True)
+        return self._stream
+
     def _switch(self, to_default: bool, ordered: bool):
-        self._check(self.lib.saga_set_stream(self._h, None if to_default else self.stream.cuda_stream, 1 if ordered else 0))
+        self._check(self.lib.saga_set_stream(self._h, None if to_default else self._stream.cuda_stream, 1 if ordered else 0))
         self._on_default = to_default
 
     def _enter(self):
@@ -259,14 +268,14 @@ class Context:
             # from outside the capture must not enter it.
             back = torch.cuda.is_current_stream_capturing()
             self._switch(False, ordered=not back)
-        if cur == self.stream:
+        if cur == self._stream:
             return None, back
-        self.stream.wait_stream(cur)
+        self._stream.wait_stream(cur)
         return cur, back
 
     def _leave(self, cur, back):
         if cur is not None:
-            cur.wait_stream(self.stream)
+            cur.wait_stream(self._stream)
         if back:
             self._switch(True, ordered=False)
 

@@ -140,3 +140,43 @@ def test_calls_are_ordered_like_torch_operations(fake, given):
         i = _call(lib, ctx, streams, under)
         assert k == 0 or ("call", i - 1) in lib.behind[i]
     ctx.destroy()
+
+
+def test_the_stream_attribute_orders_what_waits_for_it(fake):
+    """`stream` was the stream all calls run on, and programs wait on it: with the context following the default stream, what
+    waits on `stream` still waits for the calls, read after them, read before them and kept, or read twice."""
+    lib, streams, state = fake
+    ctx = B.Context(0)
+    waiting = torch.cuda.Stream()
+    i = _call(lib, ctx, streams, streams[0])
+    assert lib.current is streams[0]           # nobody asked: the call runs on the default stream itself
+    kept = ctx.stream
+    assert kept.cuda_stream != 0               # a stream that can be captured from
+    waiting.wait_stream(kept)
+    assert ("call", i) in waiting.seen
+    for under in (streams[0], waiting, streams[0], kept):
+        state["current"] = under
+        i = _call(lib, ctx, streams, under)
+        later = torch.cuda.Stream()
+        later.wait_stream(kept)
+        assert ("call", i) in later.seen and ctx.stream is kept
+    ctx.destroy()
+    assert ctx.stream is kept
+
+    given = torch.cuda.Stream()
+    assert B.Context(0, stream=given).stream is given
+    assert B.Context(0, stream=streams[0]).stream is streams[0]
+
+
+def test_the_stream_attribute_read_during_a_capture(fake):
+    """No event from outside may enter a capture: the order is made by the first call after it."""
+    lib, streams, state = fake
+    ctx = B.Context(0)
+    i = _call(lib, ctx, streams, streams[0])
+    state["current"], state["capturing"] = torch.cuda.Stream(), True
+    kept = ctx.stream
+    assert not kept.seen
+    state["current"], state["capturing"] = streams[0], False
+    j = _call(lib, ctx, streams, streams[0])
+    assert ("call", i) in lib.behind[j] and ("call", j) in kept.seen
+    ctx.destroy()

@@ -85,3 +85,36 @@ def test_workspaces_that_grow_from_stream_to_stream(given):
     for i in range(len(X)):
         assert torch.equal(got[i], want[i]), f"call {i} differs"
     ctx.destroy()
+
+
+def test_waiting_on_the_stream_attribute():
+    """A side stream that waits on `ctx.stream` alone sees a call made under the default stream, and a graph is captured on it."""
+    import paper_1810_08403_amd as saga
+    wl = si.workload(2, scale=15, f_in=128, f_out=128)
+    n = wl.graph.n
+    side = torch.cuda.Stream()
+    ctx = saga.Context(0)
+    h = ctx.graph_create_csc(n, wl.graph.col_ptr.cuda(), wl.graph.row_idx.cuda())
+    w, W, X = wl.edge_weight.cuda(), torch.randn(128, 128, device="cuda"), torch.randn(n, 128, device="cuda")
+    layer = lambda y: ctx.layer_forward(h, X, y, edge_op="mul_weight", edge_weight=w, W=W)
+    want, got, graphed = (torch.full((n, 128), float("nan"), device="cuda") for _ in range(3))
+    layer(want)
+    torch.cuda.synchronize()
+    seen = torch.full_like(got, float("nan"))
+    for _ in range(20):
+        layer(got)
+    side.wait_stream(ctx.stream)
+    with torch.cuda.stream(side):
+        seen.copy_(got)
+    torch.cuda.synchronize()
+    assert torch.equal(seen, want)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=ctx.stream):
+        layer(graphed)
+    for _ in range(3):
+        graphed.fill_(float("nan"))
+        g.replay()
+        layer(got)
+        torch.cuda.synchronize()
+        assert torch.equal(graphed, want) and torch.equal(got, want)
+    ctx.destroy()
