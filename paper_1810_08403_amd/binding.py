@@ -246,9 +246,13 @@ class Context:
     def stream(self):
         """The stream that the calls run on: those made so far, those to come, also for a handle that is kept."""
         self._follow = False
-        if self._h and self._on_default and not torch.cuda.is_current_stream_capturing():  # (else the next call does it)
+        if self._h and self._on_default and not self._capturing():  # (else the next call does it)
             self._switch(False, ordered=True)
         return self._stream
+
+    def _capturing(self) -> bool:
+        with torch.cuda.device(self.device):  # the question is about the current device's current stream
+            return torch.cuda.is_current_stream_capturing()
 
     def _switch(self, to_default: bool, ordered: bool):
         self._check(self.lib.saga_set_stream(self._h, None if to_default else self._stream.cuda_stream, 1 if ordered else 0))
@@ -266,7 +270,7 @@ class Context:
         if self._on_default:
             # What is being captured runs when the graph is launched, behind whatever its stream is behind then; an event
             # from outside the capture must not enter it.
-            back = torch.cuda.is_current_stream_capturing()
+            back = self._capturing()
             self._switch(False, ordered=not back)
         if cur == self._stream:
             return None, back

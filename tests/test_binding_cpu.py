@@ -66,7 +66,7 @@ class Library:
 def fake(monkeypatch):
     """(library, streams by handle, what torch's current stream is): handle 0 is the default stream."""
     streams = {0: Stream(0)}
-    state = {"current": streams[0], "capturing": False}
+    state = {"current": streams[0], "capturing": False, "device": 0, "capturing_on": 0}
 
     def new_stream(device=None):
         s = Stream(len(streams))
@@ -79,7 +79,19 @@ def fake(monkeypatch):
     monkeypatch.setattr(torch.cuda, "Stream", new_stream)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: state["current"])
     monkeypatch.setattr(torch.cuda, "default_stream", lambda device=None: streams[0])
-    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"] and state["device"] == state["capturing_on"])
+
+    class Device:
+        def __init__(self, device):
+            self.device = device
+
+        def __enter__(self):
+            self.before, state["device"] = state["device"], self.device
+
+        def __exit__(self, *exc):
+            state["device"] = self.before
+
+    monkeypatch.setattr(torch.cuda, "device", Device)
     return lib, streams, state
 
 
@@ -179,4 +191,17 @@ def test_the_stream_attribute_read_during_a_capture(fake):
     state["current"], state["capturing"] = streams[0], False
     j = _call(lib, ctx, streams, streams[0])
     assert ("call", i) in lib.behind[j] and ("call", j) in kept.seen
+    ctx.destroy()
+
+
+def test_a_capture_on_the_context_s_device_is_seen_from_another_device(fake):
+    """Which device is current has no say in it: streams are asked for on the context's."""
+    lib, streams, state = fake
+    ctx = B.Context(1)
+    i = _call(lib, ctx, streams, streams[0])
+    capture = torch.cuda.Stream()
+    state.update(current=capture, capturing=True, capturing_on=1, device=0)
+    _graph(ctx)
+    assert ("call", i) not in lib.behind[-1]     # no event from outside enters the capture, and
+    assert lib.current is streams[0]             # the context is back on the default stream after the call
     ctx.destroy()
