@@ -114,6 +114,7 @@ static saga_status run_propagation(saga_ctx* ctx, saga_graph* view, GatherArgs g
     ga.n_items = view->n_items;
     ga.n_team = view->n_team;
     ga.n_light = view->n_light;
+    ga.light_edges = view->light_edges;
     ga.n_src = view->n;
     ga.n_edges = view->nnz;
     ga.row_idx = static_cast<const int32_t*>(view->d_row_idx.p);
@@ -615,6 +616,7 @@ saga_status resident_backward_bf16(saga_ctx* ctx, saga_graph* g, const saga_tens
         ga.n_items = hybrid ? h.n_items : view->n_items;
         ga.n_team = hybrid ? h.n_team : view->n_team;
         ga.n_light = hybrid ? h.n_light : view->n_light;
+        ga.light_edges = hybrid ? h.light_edges : view->light_edges;
         ga.n_src = view->n;
         ga.n_edges = hybrid ? h.n_rem_edges : view->nnz;
         ga.row_idx = static_cast<const int32_t*>(hybrid ? h.rem_row_idx.p : view->d_row_idx.p);

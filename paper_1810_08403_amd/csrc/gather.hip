@@ -1446,17 +1446,37 @@ uint32_t table_bytes(const GatherArgs& a, int64_t ld, int esize)
     const int64_t b = a.n_src > 0 ? ((a.n_src - 1) * ld + a.F) * esize : 0;
     return b <= (int64_t)kPastTheEnd ? (uint32_t)b : 0u;
 }
+// Are the light columns short enough that this kernel is the faster one? What it saves is a wavefront's latency per column, and
+// once a column is a few wave-wide loads k_gather_narrow loses nothing by it and hides its loads better. By the fragments of a
+// mean light column (edges x lanes): sums and maxima of one row per edge up to 176, and up to 7.5 edges where a row takes more
+// than 16 lanes; 256 and 8.5 where the table is larger than the 256 MB of cache before the memory, which makes every trip
+// longer; gates up to 100, gradients of a maximum up to 80. us, without and with, 262,144 columns of so many edges (p: random,
+// on average; r: all alike), fp32:
+//   sum of 128 features  p5 122 111  p6 137 132  p7 151 151  p8 163 170  r5 111 110  r6 121 129  a million vertices: p6 560 507  p8 672 662
+//           96 features  p7 121 110  p8 131 124  p10 148 153  r6 98 95  r8 118 122               64: r10 106 102  r12 114 121
+//           72 features  p7 116 107  p8 125 121  p10 142 146  r6 95 92  r8 114 119               32: r16 92 75
+//   gated, 128 features  r2 350 339  r3 392 386  r4 420 422     72: p4 308 286  p5 321 315  p6 340 342     64: p5 243 230  p6 252 251  p7 263 270
+//           32 features  r10 166 158  r16 200 213
+//   gradient of a maximum, 128  r2 211 183  r3 234 223  r4 259 260     72: p4 198 197  p5 217 228     64: p5 184 178  p6 195 196  p7 207 214
+// R-MAT graphs have many columns of one and two edges: R-MAT 20 of degree 16 (2.6 on average), sum of 128 features 986 863, gated 2572 2516.
+bool light_is_short(const GatherArgs& a, int ef, int lanes, int esize)
+{
+    const bool far = a.n_src * a.ld_src * esize > (256LL << 20);
+    const int64_t limit = ef == kEfMaxGrad ? 80 : ef != kEfLinear ? 100 : far ? 256 : 176;
+    return a.light_edges * lanes <= limit * a.n_light && (lanes <= 16 || 2 * a.light_edges <= (far ? 17 : 15) * a.n_light);
+}
 // Does k_gather_light take the list's light columns (rows of `vec` elements a fragment, at most 32 of them)?
 template <typename T, bool RAG>
 bool takes_light(const GatherArgs& a, int ef, int vec)
 {
-    if (a.n_light <= 0 || !a.xcd_remap || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
+    if (a.n_light <= 0 || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
     // Enough wavefronts for the chip: half of what it holds where they are nearly all there is; twice what it holds beside
     // other items, which a second launch then waits for (measured with columns of up to 24 edges; forward and backward, us,
     // without and with: 65,536 uniform vertices of degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16
     // and 3 features, 6,000 beside others 950 and 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT
     // 18, 64 pooled features, 50,000 750 and 684).
     const int lanes = (a.F + vec - 1) / vec;
+    if (!light_is_short(a, ef, lanes, (int)sizeof(T))) return false;
     if (a.n_light / (64 / lanes) < (16 * (a.n_items - a.n_light) <= a.n_light ? 4096 : 16384)) return false;
     if (!table_bytes(a, a.ld_src, sizeof(T)) || (ef != kEfLinear && !table_bytes(a, a.ld_src2, sizeof(T))) ||
         (ef_third_row(ef) && !table_bytes(a, a.ld_src3, sizeof(T))))

@@ -143,7 +143,7 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
     out->heavy.clear();
     out->n_slots = 0;
     out->n_team = 0;
-    out->n_light = 0;
+    out->n_light = out->light_edges = 0;
     out->max_degree = 0;
     std::vector<WorkItem> whole, light;
     light.reserve((size_t)n_cols);
@@ -242,6 +242,7 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
     // Columns that are worked side by side in one wavefront are to be equally long: longest first within every 1,024 of
     // them, which are read at about the same time wherever they stand.
     out->n_light = (int64_t)light.size();
+    for (const WorkItem& it : light) out->light_edges += it.e1 - it.e0;
     out->items.resize(out->items.size() + light.size());
     WorkItem* to = out->items.data() + (out->items.size() - light.size());
     for (size_t i = 0; i < light.size(); i += 1024) {
@@ -625,7 +626,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
             ctx->dev_free(&g->saved_lists.front().heavy);
             g->saved_lists.erase(g->saved_lists.begin());
         }
-        g->saved_lists.push_back(saga_graph::SavedList{g->list_params, g->d_items, g->d_heavy, g->n_items, g->n_team, g->n_light, g->n_heavy, g->n_slots});
+        g->saved_lists.push_back(saga_graph::SavedList{g->list_params, g->d_items, g->d_heavy, g->n_items, g->n_team, g->n_light, g->light_edges, g->n_heavy, g->n_slots});
         g->d_items = DevBuf{};
         g->d_heavy = DevBuf{};
         g->list_params = WorkListParams{-1, -1, -1, false, 1, 1};
@@ -639,6 +640,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
         g->n_items = sl.n_items;
         g->n_team = sl.n_team;
         g->n_light = sl.n_light;
+        g->light_edges = sl.light_edges;
         g->n_heavy = sl.n_heavy;
         g->n_slots = sl.n_slots;
         g->list_params = sl.params;
@@ -670,6 +672,7 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
     g->n_items = (int64_t)wl.items.size();
     g->n_team = wl.n_team;
     g->n_light = wl.n_light;
+    g->light_edges = wl.light_edges;
     g->n_heavy = (int64_t)wl.heavy.size();
     g->n_slots = wl.n_slots;
     g->list_params = p;
@@ -783,6 +786,7 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     h.n_items = (int64_t)wl.items.size();
     h.n_team = wl.n_team;
     h.n_light = wl.n_light;
+    h.light_edges = wl.light_edges;
     h.n_heavy = (int64_t)wl.heavy.size();
     h.n_slots = wl.n_slots;
     h.weights_state = 0;
@@ -1644,6 +1648,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     ga.n_items = hybrid ? g->hyb.n_items : g->n_items;
     ga.n_team = hybrid ? g->hyb.n_team : g->n_team;
     ga.n_light = hybrid ? g->hyb.n_light : g->n_light;
+    ga.light_edges = hybrid ? g->hyb.light_edges : g->light_edges;
     ga.n_src = n;
     ga.n_edges = hybrid ? g->hyb.n_rem_edges : g->nnz;
     ga.row_idx = static_cast<const int32_t*>(hybrid ? g->hyb.rem_row_idx.p : g->d_row_idx.p);

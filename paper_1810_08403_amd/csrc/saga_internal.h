@@ -103,6 +103,7 @@ struct WorkList {
     int64_t n_team = 0;
     int64_t n_slots = 0;
     int64_t n_light = 0;  // items at the end of the list that are whole columns of at most kLightEdges edges
+    int64_t light_edges = 0;  // edges of those
     int64_t max_degree = 0;
 };
 
@@ -299,7 +300,7 @@ struct HybridDevice {
     DevBuf chunks, blk_src_tile, blk_e0, blk_tile, de_pos, de_edge, de_w, dt_addr, dt_edge, de_tiles, src_tile_ids, tile_row_slot0;
     int64_t n_list_edges = 0, n_tile_edges = 0, n_tiles = 0;
     DevBuf rem_row_idx, rem_edge, rem_w, items, heavy;
-    int64_t n_items = 0, n_team = 0, n_light = 0, n_heavy = 0, n_slots = 0;
+    int64_t n_items = 0, n_team = 0, n_light = 0, light_edges = 0, n_heavy = 0, n_slots = 0;
     int weights_state = 0;                // 0: de_w / rem_w not packed; 1: packed from the attached edge data; 2: packed as all ones (COPY)
 };
 
@@ -310,13 +311,13 @@ struct saga_graph {
     // resident form; the work list is built at the first call for a given
     // (split, cut_degree, stripe_rows) and rebuilt when those change
     DevBuf d_row_idx, d_items, d_heavy, d_edge_data;
-    int64_t n_items = 0, n_team = 0, n_light = 0, n_heavy = 0, n_slots = 0, max_degree = 0;
+    int64_t n_items = 0, n_team = 0, n_light = 0, light_edges = 0, n_heavy = 0, n_slots = 0, max_degree = 0;
     WorkListParams list_params{-1, -1, -1, false, 1};
     // work lists built earlier for other row widths (layers of different width alternate between them)
     struct SavedList {
         WorkListParams params;
         DevBuf items, heavy;
-        int64_t n_items, n_team, n_light, n_heavy, n_slots;
+        int64_t n_items, n_team, n_light, light_edges, n_heavy, n_slots;
     };
     std::vector<SavedList> saved_lists;
     // host form (streamed)
@@ -367,6 +368,7 @@ struct GatherArgs {
     int64_t n_items;
     int64_t n_team;          // items [0, n_team) are processed by a whole workgroup each
     int64_t n_light;         // the last n_light items are whole columns of at most kLightEdges edges (0: not known)
+    int64_t light_edges;     // edges of those
     int64_t n_src, n_edges;  // rows of src (src2, src3), edges of row_idx; 0: not known
     const int32_t* row_idx;  // source ids, local to the rows of `src`
     const float* edge_w;     // nullable (COPY)

@@ -8,18 +8,22 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-def _graph(n, heavy, seed):
-    """Degrees 0 to 16, the edges among them, in turn (and, with `heavy`, some of 17 and 300, and three at the length from
-    which four wavefronts share an item)."""
+def _graph(n, heavy, seed, lanes):
+    """Degrees 0 to 16, the edges among them, in turn, for rows of more than 8 fragments with four short columns to each, since
+    the kernel takes such rows where columns are short (and, with `heavy`, some of 17 and 300, and four at the lengths from
+    which four wavefronts share an item: 129 of rows up to 256 bytes, 1,025 of a band of wider ones)."""
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
-    deg = torch.tensor([0, 1, 7, 8, 15, 16, 3, 13], device=DEV).repeat((n + 7) // 8)[:n].clone()
+    pattern = [0, 1, 7, 8, 15, 16, 3, 13] + ([1, 0, 2, 1, 1, 0, 1, 2] * 4 if lanes > 8 else [])
+    deg = torch.tensor(pattern, device=DEV).repeat(-(-n // len(pattern)))[:n].clone()
     if heavy:
-        deg[::97] = 17
+        deg[97::97] = 17
         deg[5::4001] = 300
-        deg[3], deg[11], deg[19] = 128, 129, 5000
+        deg[3], deg[11], deg[19], deg[27] = 128, 129, 5000, 1900
     dst = torch.repeat_interleave(torch.arange(n, device=DEV), deg)
     src = torch.randint(1, n - 1, (dst.numel(),), generator=g, device=DEV)   # nothing reads the first and the last row
+    if heavy:
+        src[dst == 27] = torch.randint(1, 2046, (1900,), generator=g, device=DEV)   # some 1,240 of one band
     key = torch.unique(dst * n + src)
     dst = key // n
     col_ptr = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
@@ -43,7 +47,7 @@ def test_linear_messages(F, pad, dtype, heavy):
     vec = 4 if dtype == "f32" else 8
     lanes = -(-Fx // vec) if Fx >= vec else Fx
     n = (64 // lanes) * 4 * (17000 if heavy else 4200) // 3   # past the count from which the kernel is used
-    col_ptr, row_idx, dst, g = _graph(n, heavy, F)
+    col_ptr, row_idx, dst, g = _graph(n, heavy, F, lanes)
     ctx, h = _ctx(n, col_ptr, row_idx)
     big = torch.randn(n, Fx + pad, generator=g, device=DEV).to(tdt)
     big[0], big[n - 1] = float("nan"), float("inf")
@@ -84,7 +88,7 @@ def test_gated_and_pooled_layers_both_ways(F, agg):
     own row is not finite keeps an empty sum, and a vertex without edges keeps its rows to itself."""
     lanes = -(-F // 4) if F >= 4 else F
     n = (64 // lanes) * 4 * 4200 // 3
-    col_ptr, row_idx, dst, g = _graph(n, False, F)
+    col_ptr, row_idx, dst, g = _graph(n, False, F, lanes)
     ctx, h = _ctx(n, col_ptr, row_idx)
     src = row_idx.long()
     t = lambda *s: torch.randn(*s, generator=g, device=DEV) * 0.3
