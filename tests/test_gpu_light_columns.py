@@ -83,12 +83,14 @@ def test_linear_messages(F, pad, dtype, heavy):
 
 @pytest.mark.parametrize("agg", ["sum", "max"])
 @pytest.mark.parametrize("F", [3, 8, 20, 64, 128])
-def test_gated_and_pooled_layers_both_ways(F, agg):
+@pytest.mark.parametrize("heavy", [False, True])
+def test_gated_and_pooled_layers_both_ways(F, agg, heavy):
     """Forward and backward against float64 autograd (dense per edge), degrees and widths as above; a vertex without in-edges whose
-    own row is not finite keeps an empty sum, and a vertex without edges keeps its rows to itself."""
+    own row is not finite keeps an empty sum, and a vertex without edges keeps its rows to itself. With `heavy`, light columns,
+    shared long items and the pieces of cut columns lie in one propagation."""
     lanes = -(-F // 4) if F >= 4 else F
-    n = (64 // lanes) * 4 * 4200 // 3
-    col_ptr, row_idx, dst, g = _graph(n, False, F, lanes)
+    n = (64 // lanes) * 4 * (17000 if heavy else 4200) // 3
+    col_ptr, row_idx, dst, g = _graph(n, heavy, F, lanes)
     ctx, h = _ctx(n, col_ptr, row_idx)
     src = row_idx.long()
     t = lambda *s: torch.randn(*s, generator=g, device=DEV) * 0.3
