@@ -1,0 +1,95 @@
+"""The work lists of resident propagations, as the kernels get them: items that four wavefronts share are those past 128 edges
+(rows of which a band holds 4,096 or more) or past 1,024, and the first of the list; light columns are its end, in the order
+they should have; every edge is in one item; forwards and backwards (edges by source), with and without bands, lists kept
+for another width among them, on the CPU stand-in.
+
+  python tests/hoststub/run_shared_items.py <library>"""
+import ctypes
+import os
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TESTS = os.path.dirname(HERE)
+sys.path[:0] = [os.path.dirname(TESTS), TESTS, HERE]
+
+import numpy as np
+import torch
+
+import oracle
+import saga_inputs as si
+from helpers import assert_sum_close
+from stub_binding import StubContext, dev
+
+
+def last_list(ctx, capacity):
+    items, counts = np.full((capacity, 4), -1, np.int32), (ctypes.c_int64 * 4)()
+    ctx.lib.stub_last_work_list(items.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(capacity), counts)
+    n, team, light, light_edges = counts
+    assert n <= capacity
+    return items[:n].astype(np.int64), team, light, light_edges
+
+
+def check(ctx, col_ptr, long_edges, expect_long):
+    nnz, n = int(col_ptr[-1]), len(col_ptr) - 1
+    items, team, light, light_edges = last_list(ctx, nnz + n)
+    v, e0, e1, slot = items.T
+    length = e1 - e0
+    cover = np.zeros(nnz + 1, np.int64)
+    np.add.at(cover, e0, 1)
+    np.add.at(cover, e1, -1)
+    assert (np.cumsum(cover)[:-1] == 1).all(), "an edge in no item or in two"
+    assert (e0 >= col_ptr[v]).all() and (e1 <= col_ptr[v + 1]).all()
+    assert set(np.flatnonzero(length > long_edges)) == set(range(team)), (team, int((length > long_edges).sum()))
+    assert (team > 0) == expect_long, team
+    is_light = (slot < 0) & (length <= 16)
+    assert is_light.sum() == light and is_light[len(items) - light:].all() and light_edges == length[is_light].sum()
+    ll, lv = length[is_light], v[is_light]
+    for i in range(0, light, 1024):
+        key = (16 - ll[i:i + 1024]) * n + lv[i:i + 1024]
+        assert (np.diff(key) > 0).all()
+    pieces = slot >= 0
+    assert sorted(slot[pieces].tolist()) == list(range(int(pieces.sum())))
+
+
+def main():
+    lib = sys.argv[1]
+    rng = np.random.default_rng(11)
+    n = 6000
+    deg = rng.integers(0, 30, n)
+    deg[[7, 70, 700]] = [5200, 129, 128]
+    pairs = {(v, int(u)) for v in range(n) for u in rng.choice(n, deg[v], replace=False)}
+    pairs |= {(v, 9) for v in range(0, n, 2)}              # a hub in the edges by source
+    g = si.csc_from_lists(n, sorted((u, v) for v, u in pairs))
+    cp, ri = g.col_ptr.numpy(), g.row_idx.numpy()
+    out_deg = np.bincount(ri, minlength=n)
+    cp_out = np.concatenate([[0], np.cumsum(out_deg)])
+    t = lambda *s: torch.as_tensor((rng.standard_normal(s) * 0.3).astype(np.float32))
+    for opts in (dict(), dict(cut_degree=1 << 20), dict(stripe_kb=0, cut_degree=1 << 20), dict(split=16, cut_degree=40)):
+        ctx = StubContext(lib)
+        for k, x in opts.items():
+            ctx.set_option(k, x)
+        h = ctx.graph_create_csc(n, dev(g.col_ptr), dev(g.row_idx))
+        for F in (16, 128, 16):
+            X, W = t(n, F), t(F, 4)
+            # bands of 1 MiB: 4,096 or more of the rows (or none)
+            long_edges = 128 if "stripe_kb" not in opts and F * 4 <= 256 else 1024
+            Y, A = dev(torch.full((n, 4), float("nan"))), dev(torch.full((n, F), float("nan")))
+            ctx.layer_forward(h, dev(X), Y, edge_op="copy", W=dev(W), accum_out=A)
+            ctx.synchronize()
+            # cut at band ends, rows of 128 features make pieces of 2,048 sources at most; uncut, the hub is one item
+            hub_piece = int((ri[cp[7]:cp[7 + 1]] < 2048).sum())
+            check(ctx, cp, long_edges, True if long_edges == 128 or "cut_degree" in opts and opts["cut_degree"] > 5200 else hub_piece > 1024)
+            ref = oracle.layer(cp, ri, X.numpy(), "copy", None, agg="sum", W=W.numpy())
+            assert_sum_close(Y.t.numpy(), ref["Y"], ref["Y_abs"], 1e-4, f"{opts} F {F}")
+            dX, dW = dev(torch.full((n, F), float("nan"))), dev(torch.full((F, 4), float("nan")))
+            ctx.layer_backward(h, A, dev(t(n, 4)), dev(W), dW, X=dev(X), edge_op="copy", dX=dX)
+            ctx.synchronize()
+            width = min(F, 4)                                    # what travels back is the gradient of the narrower side
+            check(ctx, cp_out, 128 if "stripe_kb" not in opts and width * 4 <= 256 else 1024, True)
+        h.destroy()
+        ctx.destroy()
+    print("ok: work lists of resident propagations", flush=True)
+
+
+if __name__ == "__main__":
+    main()

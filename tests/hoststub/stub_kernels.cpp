@@ -4,6 +4,7 @@
 // split workspaces), so that AddressSanitizer checks the sizes the host code allocated and the pointers it
 // formed. They share no code with the HIP kernels and none with the oracle; the numbers only have to be
 // good enough to tell a correct schedule from one that read stale or foreign data.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -48,6 +49,32 @@ float apply_act(float y, int act)
     return y;
 }
 const float kNegInf = -__builtin_huge_valf();
+
+// the work list of the last propagation that ran (stub_last_work_list)
+std::vector<WorkItem> g_list;
+int64_t g_list_team = 0, g_list_light = 0, g_list_light_edges = 0;
+
+// what a propagation says about its list and its tables, on which kernels rely
+void check_list(const GatherArgs& a)
+{
+    if (a.n_team < 0 || a.n_light < 0 || a.n_team > a.n_items || a.n_light > a.n_items - a.n_team) die("counts of a work list out of range");
+    int64_t light_edges = 0;
+    for (int64_t i = a.n_items - a.n_light; i < a.n_items; ++i) {
+        if (a.items[i].e1 - a.items[i].e0 > kLightEdges) die("a long item among the light columns");
+        light_edges += a.items[i].e1 - a.items[i].e0;
+    }
+    if (a.n_light > 0 && light_edges != a.light_edges) die("edges of the light columns miscounted");
+    for (int64_t i = 0; i < a.n_items; ++i) {
+        if (a.n_edges > 0 && a.items[i].e1 > a.n_edges) die("a work item past the edges");
+        if (a.n_src > 0)
+            for (int32_t e = a.items[i].e0; e < a.items[i].e1; ++e)
+                if (a.row_idx[e] >= a.n_src) die("a source id past the table's rows");
+    }
+    g_list.assign(a.items, a.items + a.n_items);
+    g_list_team = a.n_team;
+    g_list_light = a.n_light;
+    g_list_light_edges = a.light_edges;
+}
 
 void store_finished(const GatherArgs& a, float* out, int64_t ld_out, int64_t v, int f, float val, int agg, bool empty, bool with16)
 {
@@ -200,8 +227,21 @@ hipError_t launch_gather(const GatherArgs& a, hipStream_t s)
         if (a.dtype != SAGA_F32) return hipErrorInvalidValue;
     }
     const GatherArgs copy = a;
-    stub_enqueue(s, [copy] { gather_cpu(copy); });
+    stub_enqueue(s, [copy] {
+        check_list(copy);
+        gather_cpu(copy);
+    });
     return hipSuccess;
+}
+
+// items of that list (as many as fit `capacity`); counts: items, of them shared ones at its start, light columns at its end, their edges
+extern "C" void stub_last_work_list(int32_t* items, int64_t capacity, int64_t* counts)
+{
+    counts[0] = (int64_t)g_list.size();
+    counts[1] = g_list_team;
+    counts[2] = g_list_light;
+    counts[3] = g_list_light_edges;
+    memcpy(items, g_list.data(), sizeof(WorkItem) * (size_t)std::min<int64_t>(capacity, counts[0]));
 }
 
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s)

@@ -78,6 +78,10 @@ def test_no_alloc_entry_point_reaches_no_allocator(stub_lib):
     _run("run_no_alloc.py", stub_lib)
 
 
+def test_shared_items_and_light_columns_of_resident_lists(stub_lib):
+    _run("run_shared_items.py", stub_lib)
+
+
 def test_dense_block_plan_and_schedule(stub_lib):
     """The dense-block form of a resident graph (ranks, 64 x 32 blocks as edge lists or finished operands, chunks, the
     partial-row slots shared with the sparse remainder's work list, weight packing) against the oracle."""
