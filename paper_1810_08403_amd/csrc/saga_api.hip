@@ -592,8 +592,10 @@ WorkListParams work_list_params(const saga_ctx* ctx, int64_t row_bytes, int32_t 
 // Items of a resident list that four wavefronts share (WorkListParams::long_edges). Narrow rows fit bands of so many source
 // rows that a hub's column is one piece of thousands of edges, and the launch lasts as long as the one wavefront that works
 // it. Layers, us, with none / items past 128 / 512 / 1,024 edges: two GCN layers in training, 16 and 3 features in the second, 944
-// 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23; wider rows have shorter
-// pieces and gain nothing: CommNet in training, 128 features, 1089 1099 1099 1085.
+// 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23. A band of wider rows is
+// 2,048 of them or fewer, so that only the hubs of small dense graphs have pieces past 1,024 edges: propagation of 128 fp32
+// features, none / 1,024, R-MAT 11 with 64 edges a vertex (both ways) 29 21, R-MAT 12 with 32 28 21, with 120 44 30, R-MAT 14
+// with 64 73.4 72.7, R-MAT 16 194 194; CommNet in training on R-MAT 18 1076 1075.
 // By the rows per band, which is 4,096 or more at 256 bytes a row and 1 MiB a band, and not by the width itself: widths that
 // share a list go on sharing it.
 static int64_t long_edges(const WorkListParams& p)
