@@ -1030,9 +1030,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
 // The columns of a wavefront are about equally long (see build_work_list) and take the longest one's steps; a step past a
 // column's end reads at an offset past the table, which gives zeros and no traffic (buffer loads check their range), and
 // leaves sum and maximum as they are. Bound: the round trips; then the lines read, like the other kernels.
-// Uniform graph of 262,144 vertices, us, k_gather_narrow and this: 3 features, degree 4 64 and 11, 16 72 and 32; 16 features 78
-// and 20, 91 and 66; 64 features 80 and 47, 147 and 156; 128 features 98 and 92, 313 and 316 (the last ones wait for rows that
-// miss the L2). A layer of 22 bf16 features in training, 524,288 vertices of degree 6: 1013 and 630.
+// Uniform graph of 262,144 vertices, us, k_gather_narrow and this: 3 features, degree 4 64 and 12, 16 72 and 32; 16 features 77
+// and 20, 91 and 66; 64 features 80 and 47, 148 and 158; 128 features 97 and 92, 319 and 318 (the last ones wait for rows that
+// miss the L2; the rule below leaves these two to k_gather_narrow). A layer of 22 bf16 features in training, R-MAT 19 of degree
+// 6: 1013 and 617.
 // NI: ids a lane holds of a batch, so that a batch of a narrow row's few lanes still fills the loads in flight.
 // TWO (rows of 17 to 32 fragments, sums): the even and the odd edges of a column in a chain each, added at the end. That is what
 // k_gather_narrow's two lane groups do with such a row, and gives the same bits: which of the two kernels takes a column is a
@@ -1471,10 +1472,10 @@ bool takes_light(const GatherArgs& a, int ef, int vec)
 {
     if (a.n_light <= 0 || a.n_edges <= 0 || a.n_edges >= (1LL << 30) - 64) return false;
     // Enough wavefronts for the chip: half of what it holds where they are nearly all there is; twice what it holds beside
-    // other items, which a second launch then waits for (measured with columns of up to 24 edges; forward and backward, us,
-    // without and with: 65,536 uniform vertices of degree 16, 16 features, 4,096 wavefronts, alone 25 and 10; R-MAT 17, 16
-    // and 3 features, 6,000 beside others 950 and 966; R-MAT 15, 45 gated features, 6,500 beside others 305 and 335; R-MAT
-    // 18, 64 pooled features, 50,000 750 and 684).
+    // other items, which a second launch then waits for. us, without and with: 65,536 uniform vertices of degree 16, 16
+    // features, 4,096 wavefronts, alone 24 and 10; in training, beside others: 45 gated features, R-MAT 15 (6,000 wavefronts) 318
+    // and 360, R-MAT 16 (11,000) 386 and 399, R-MAT 17 (23,000) 650 and 597; 64 pooled features, R-MAT 18, 50,000 749 and 690.
+    // (Sums alone would gain from fewer on: two layers of 16 and 3 features, R-MAT 17, 7,000 and 1,800 wavefronts, 887 and 868.)
     const int lanes = (a.F + vec - 1) / vec;
     if (!light_is_short(a, ef, lanes, (int)sizeof(T))) return false;
     if (a.n_light / (64 / lanes) < (16 * (a.n_items - a.n_light) <= a.n_light ? 4096 : 16384)) return false;
