@@ -1035,10 +1035,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
 // miss the L2; the rule below leaves these two to k_gather_narrow). A layer of 22 bf16 features in training, R-MAT 19 of degree
 // 6: 1013 and 617.
 // NI: ids a lane holds of a batch, so that a batch of a narrow row's few lanes still fills the loads in flight.
-// TWO (rows of 17 to 32 fragments, sums): the even and the odd edges of a column in a chain each, added at the end. That is what
-// k_gather_narrow's two lane groups do with such a row, and gives the same bits: which of the two kernels takes a column is a
-// matter of speed alone. (The pairs and chunks of the other form turned bf16 roundings and ReLU decisions of a 256-wide bf16
-// layer in training by their last fp32 bit: 5e-4 of dX and dW. The chains take as long.)
+// CH (sums of rows of 9 to 32 fragments): edge k of a column is added to chain k mod CH, and the chains by pairs at the end. With
+// two chains for rows of 17 fragments or more and four for 9 to 16 that is what k_gather_narrow's lane groups do, and gives
+// the same bits: which of the two kernels takes a column is a matter of speed alone. (The pairs and chunks of the other form, CH
+// = 0, turned bf16 roundings and ReLU decisions of a 256-wide bf16 layer in training by their last fp32 bit, 5e-4 of dX and dW,
+// and round more often than four chains do: columns of 8 edges 5.11e-8 of the result, not 4.95e-8, of 16 5.8e-8, not 5.6e-8. The
+// chains take as long, within 2 %, but for 9 to 16 fragments of bf16 at two edges a column, 34 us instead of 31.)
 // ---------------------------------------------------------------------------
 struct LightShape {
     int32_t lpr;      // lanes per group: one fragment of the row each (not a power of two in general)
@@ -1061,22 +1063,23 @@ __device__ __forceinline__ void load_in_range(Frag<T, VEC>& f, const __amdgpu_bu
         f.r = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
     }
 }
-constexpr int light_min_waves(int elem_bytes, int agg, int ef, bool rag, int ni, bool two)
+constexpr int light_min_waves(int elem_bytes, int agg, int ef, bool rag, int ni, int ch)  // no spills
 {
     const int w = narrow_min_waves(elem_bytes, agg, ef, rag);
-    return ni == 4 && w > 6 ? 6 : elem_bytes == 2 && two ? 7 : elem_bytes == 2 && agg == SAGA_AGG_MAX && ni == 1 ? 5 : w;  // no spills
+    if (ch == 4) return ef == kEfGateBothMax ? 4 : ef_is_grad(ef) ? 5 : ef == kEfLinear && elem_bytes == 4 ? w : 6;
+    return ni == 4 && w > 6 ? 6 : elem_bytes == 2 && ch > 0 ? 7 : elem_bytes == 2 && agg == SAGA_AGG_MAX && ni == 1 ? 5 : w;
 }
-// TWO: an even number, so that a step's place in its chunk says which chain it belongs to (gated training, R-MAT 18 with 128
-// features: 2204 us with 2 as with 3 and one chain, 2215 with 4, which costs wavefronts)
-constexpr int light_loads(int ef, int ni, bool two) { return ef == kEfLinear ? (ni == 1 ? 6 : 4) : two ? 2 : ni == 1 ? 3 : ni; }
+// CH: a multiple of it, so that a step's place in its chunk says which chain it belongs to (two chains, gated training, R-MAT 18
+// with 128 features: 2204 us with 2 loads as with 3 and one chain, 2215 with 4, which costs wavefronts)
+constexpr int light_loads(int ef, int ni, int ch) { return ch == 4 ? 4 : ef == kEfLinear ? (ni == 1 ? 6 : 4) : ch == 2 ? 2 : ni == 1 ? 3 : ni; }
 
-template <typename T, int VEC, bool RAG, int AGG, int EF, int NI, bool TWO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_waves(sizeof(T), AGG, EF, RAG, NI, TWO), 8))) void k_gather_light(
+template <typename T, int VEC, bool RAG, int AGG, int EF, int NI, int CH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_waves(sizeof(T), AGG, EF, RAG, NI, CH), 8))) void k_gather_light(
     const GatherArgs a, const LightShape sh)
 {
-    constexpr int U = light_loads(EF, NI, TWO);
-    static_assert(!TWO || AGG == SAGA_AGG_SUM, "a maximum does not depend on the order");
-    static_assert(!TWO || (U % 2 == 0 && kLightEdges <= 17), "chunks start at even edges, and one batch of 17 ids holds a column");
+    constexpr int U = light_loads(EF, NI, CH);
+    static_assert(CH == 0 || AGG == SAGA_AGG_SUM, "a maximum does not depend on the order");
+    static_assert(CH == 0 || (U % CH == 0 && NI == 1), "chunks start at edges of the first chain");
     constexpr bool GATED = EF != kEfLinear;
     constexpr bool ROW3 = ef_third_row(EF);
     constexpr bool HAS_W = !GATED || EF == kEfMaxGrad;
@@ -1126,11 +1129,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
     int steps_left = 0;  // the longest column of the wavefront
     for (int g = 0; g < sh.groups; ++g) steps_left = max(steps_left, __builtin_amdgcn_readlane(it.z - it.y, g * lpr));
 
-    float acc[VEC], acc2[VEC], odd[VEC], odd2[VEC], pd[VEC], c2[VEC], c3[VEC];
+    constexpr int NC = CH > 0 ? CH : 1;
+    float accs[NC][VEC], accs2[NC][VEC], pd[VEC], c2[VEC], c3[VEC];
+    float (&acc)[VEC] = accs[0], (&acc2)[VEC] = accs2[0];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) {
-        acc[j] = identity<AGG>();
-        acc2[j] = odd[j] = odd2[j] = pd[j] = c2[j] = c3[j] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            accs[c][j] = identity<AGG>();
+            accs2[c][j] = 0.f;
+        }
+        pd[j] = c2[j] = c3[j] = 0.f;
     }
     if constexpr (GATED) {
         Frag<float, VEC> f;
@@ -1158,7 +1167,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
 #pragma unroll
         for (int j = 0; j < VEC; ++j) c3[j] = f.get(j);
     }
-    const int batch = lpr * NI;
+    const int batch = CH == 4 ? lpr & ~3 : lpr * NI;  // (a batch starts with the first chain; one of 17 ids holds a whole column)
     for (int e = it.y; steps_left > 0;) {
         uint32_t off[NI], off2[GATED ? NI : 1], off3[ROW3 ? NI : 1];
         float wt[HAS_W ? NI : 1];
@@ -1190,10 +1199,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
                 }
             }
             if (ask) fetch_batch(e + batch, id_next, w_next);
-            // Without TWO, sums by pairs of edges, then by chunk, then all: one chain would round once per edge, where the lane groups
+            // Without chains, sums by pairs of edges, then by chunk, then all: one chain would round once per edge, where the lane groups
             // of k_gather_narrow round a handful of times. Error of the result against float64, normal data, here / there: columns
-            // of 2 edges 3.1e-8 / 3.7e-8, of 4 4.1 / 4.6, of 8 4.9 to 5.1 / 4.8 to 5.3, of 16 5.8 to 6.0 / 5.6 to 6.0.
-            constexpr bool TREE = AGG == SAGA_AGG_SUM && !TWO;
+            // of 2 edges 3.1e-8 / 3.7e-8, of 4 4.1 / 4.6, of 8 4.9 / 5.3, of 16 5.8 / 6.0.
+            constexpr bool TREE = AGG == SAGA_AGG_SUM && CH == 0;
             float chunk[VEC], chunk2[VEC], pair[VEC], pair2[VEC];
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
@@ -1211,9 +1220,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
                         float mv = 0.f, tv = 0.f;
                         if constexpr (GATED) mv = m[k].get(j);
                         if constexpr (ROW3) tv = t3[k].get(j);
-                        if constexpr (TWO) {
-                            float& r = k % 2 == 0 ? acc[j] : odd[j];
-                            float& r2 = k % 2 == 0 ? acc2[j] : odd2[j];
+                        if constexpr (CH > 0) {
+                            float &r = accs[k % NC][j], &r2 = accs2[k % NC][j];
                             const float was = r, was2 = r2;
                             if constexpr (ef_is_both(EF))
                                 edge_step_both<EF>(r, r2, x[k].get(j), mv, pd[j], c2[j], tv);
@@ -1244,7 +1252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
             }
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
-                if constexpr (!TWO) {  // (the chains hold their sums already)
+                if constexpr (CH == 0) {  // (the chains hold their sums already)
                     acc[j] = TREE ? acc[j] + chunk[j] : chunk[j];
                     if constexpr (ef_is_both(EF)) acc2[j] += chunk2[j];
                 }
@@ -1269,11 +1277,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(light_min_w
         e = e_batch + batch;
     }
     if (!mine) return;
-    if constexpr (TWO) {
+    if constexpr (CH > 0) {
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            acc[j] += odd[j];
-            acc2[j] += odd2[j];
+            acc[j] += accs[1][j];
+            acc2[j] += accs2[1][j];
+            if constexpr (CH == 4) {
+                acc[j] += accs[2][j] + accs[3][j];
+                acc2[j] += accs2[2][j] + accs2[3][j];
+            }
         }
     }
     const bool empty = it.y == it.z;
@@ -1508,15 +1520,17 @@ hipError_t launch_light(const GatherArgs& a, const int lpr, hipStream_t s)
     sh.same_ld = (EF == kEfLinear || a.ld_src2 == a.ld_src) && (!ef_third_row(EF) || a.ld_src3 == a.ld_src);
     const int64_t blocks = (a.n_items + (int64_t)kWavesPerBlock * sh.groups - 1) / ((int64_t)kWavesPerBlock * sh.groups);
     const dim3 grid((unsigned)blocks), block(256);
-    constexpr bool TWO = AGG == SAGA_AGG_SUM && VEC > 1;
-    if (TWO && lpr > 16)
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, TWO>), grid, block, 0, s, a, sh);
+    constexpr bool CHAINS = AGG == SAGA_AGG_SUM && VEC > 1;
+    if (CHAINS && lpr > 16)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, CHAINS ? 2 : 0>), grid, block, 0, s, a, sh);
+    else if (CHAINS && lpr > 8)
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, CHAINS ? 4 : 0>), grid, block, 0, s, a, sh);
     else if (lpr >= 8)
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, false>), grid, block, 0, s, a, sh);
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 1, 0>), grid, block, 0, s, a, sh);
     else if (lpr >= 4)
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 2, false>), grid, block, 0, s, a, sh);
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 2, 0>), grid, block, 0, s, a, sh);
     else
-        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 4, false>), grid, block, 0, s, a, sh);
+        hipLaunchKernelGGL((k_gather_light<T, VEC, RAG, AGG, EF, 4, 0>), grid, block, 0, s, a, sh);
     return hipGetLastError();
 }
 

@@ -137,12 +137,16 @@ def test_gated_and_pooled_layers_both_ways(F, agg, heavy):
     ctx.destroy()
 
 
-@pytest.mark.parametrize("F,dtype", [(68, "f32"), (69, "f32"), (100, "f32"), (127, "f32"), (128, "f32"), (136, "bf16"), (150, "bf16"), (256, "bf16")])
-def test_rows_of_17_to_32_fragments_keep_the_order_of_the_other_kernel(F, dtype):
-    """Such rows lie two side by side in a wavefront of the kernel for columns of any length: one lane group adds up the even
-    edges, the other the odd ones. Several short columns side by side give the same bits, whichever kernel takes them."""
+@pytest.mark.parametrize("F,dtype", [(36, "f32"), (41, "f32"), (52, "f32"), (61, "f32"), (64, "f32"), (68, "f32"), (69, "f32"), (100, "f32"), (127, "f32"),
+                                     (128, "f32"), (72, "bf16"), (100, "bf16"), (128, "bf16"), (136, "bf16"), (150, "bf16"), (256, "bf16")])
+def test_rows_of_9_to_32_fragments_keep_the_order_of_the_other_kernel(F, dtype):
+    """Two such rows (from 17 fragments on) or four lie side by side in a wavefront of the kernel for columns of any length: each
+    lane group adds up every second or fourth edge. Several short columns side by side give the same bits, whichever kernel
+    takes them."""
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
-    n = 2 * 4 * 4200
+    lanes = -(-F // (4 if dtype == "f32" else 8))
+    C = 4 if lanes <= 16 else 2
+    n = (64 // lanes) * 4 * 4200
     g = torch.Generator(device=DEV)
     g.manual_seed(F)
     # lengths up to the longest such column, and short ones between them: 3.6 edges a column
@@ -166,11 +170,14 @@ def test_rows_of_17_to_32_fragments_keep_the_order_of_the_other_kernel(F, dtype)
             ctx.layer_forward(h, X, A, **kw)
         else:
             ctx.layer_forward(h, X, torch.empty_like(X), accum_out=A, **kw)
-        chains = [torch.zeros(n, F, device=DEV), torch.zeros(n, F, device=DEV)]
+        chains = [torch.zeros(n, F, device=DEV) for _ in range(C)]
         for k in range(16):
             v = torch.nonzero(deg > k).flatten()
             e = col_ptr[v] + k
             msg = X[row_idx[e].long()].float()
-            chains[k % 2][v] += msg if weight is None else weight[e][:, None] * msg
-        assert torch.equal(A, chains[0] + chains[1]), (F, dtype, weight is not None)
+            chains[k % C][v] += msg if weight is None else weight[e][:, None] * msg
+        want = chains[0] + chains[1]
+        if C == 4:
+            want += chains[2] + chains[3]
+        assert torch.equal(A, want), (F, dtype, weight is not None)
     ctx.destroy()
