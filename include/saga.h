@@ -135,7 +135,8 @@ typedef struct saga_timings {
 
 /*
  * Create a context on GPU `device`. hip_stream is a hipStream_t to enqueue on
- * (NULL: the library creates its own, default priority). hbm_budget_bytes caps
+ * (NULL: the library creates its own, default priority; for the default stream, whose
+ * handle is NULL too, call saga_set_stream(ctx, NULL, 0) next). hbm_budget_bytes caps
  * every device byte the library holds for streamed calls (0 = no cap).
  */
 saga_status saga_create(saga_ctx** out, int device, void* hip_stream, size_t hbm_budget_bytes);

@@ -89,12 +89,12 @@ struct HeavyVertex {
     int32_t pad;
 };
 
-// Columns of up to this many edges can be worked several in a wavefront (k_gather_light). Layers, us, measured with sums by
-// pairs at every width and without the rule on mean lengths, with 0 (only columns without edges) / 8 / 16 / 24 / 32 / 48 edges: gated training on R-MAT 18 2148 2113 2098 2111 2121 2120, CommNet training 1071
-// 1066 1060 1050 1045 1045, pooled training 697 686 682 684 693 700, GCN training on 80,207 uniform vertices 131 130 119 117
-// 109 109. Not more than 16: the sum of a longer column rounds more often than over the lane groups of k_gather_narrow (24
-// edges: 6.5e-8 of the result, not 6.1e-8). The 80,207 vertices take 117 with 16 too where the rule counts a list that is
-// nearly all light as one that is.
+// Columns of up to this many edges can be worked several in a wavefront (k_gather_light). Layers, us, with 0 (only columns
+// without edges) / 8 / 16 / 24 / 32 / 48 edges, measured with sums by pairs at every width and without the rule on mean
+// lengths: gated training on R-MAT 18 2148 2113 2098 2111 2121 2120, CommNet training 1071 1066 1060 1050 1045 1045, pooled
+// training 697 686 682 684 693 700, GCN training on 80,207 uniform vertices 131 130 119 117 109 109. Not more than 16: the sum
+// of a longer column rounds more often than over the lane groups of k_gather_narrow (24 edges: 6.5e-8 of the result, not
+// 6.1e-8). The 80,207 vertices take 117 with 16 too where the rule counts a list that is nearly all light as one that is.
 constexpr int kLightEdges = 16;
 
 struct WorkList {
