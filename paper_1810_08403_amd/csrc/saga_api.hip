@@ -224,8 +224,17 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
         return a.it.e0 < b.it.e0;
     });
     out->items.reserve(pieces.size() + whole.size() + light.size());
-    const bool split_long = team == 1 && p.long_edges > 0;
+    bool split_long = team == 1 && p.long_edges > 0;
     auto is_long = [&](const WorkItem& it) { return it.e1 - it.e0 > p.long_edges; };
+    if (split_long && R > 4096) {
+        // Where the longest item is not far above the average one, long items are the launch and not its tail, and a share of
+        // a narrow one is little more than its overhead (sums of 3 and of 16 features, us, 16,384 columns of 200 edges 21 and 25,
+        // shared 24 and 28; 4,000 of 500 edges 9 and 12, shared 11 and 14; of 64 features, bands of 4,096 rows, 27 and 24).
+        int64_t longest = 0;
+        for (const Piece& pc : pieces) longest = std::max<int64_t>(longest, pc.it.e1 - pc.it.e0);
+        for (const WorkItem& it : whole) longest = std::max<int64_t>(longest, it.e1 - it.e0);
+        split_long = longest * (int64_t)(pieces.size() + whole.size() + light.size()) > 4 * col_ptr[n_cols];
+    }
     if (split_long) {
         for (const Piece& pc : pieces)
             if (is_long(pc.it)) out->items.push_back(pc.it);
@@ -592,16 +601,18 @@ WorkListParams work_list_params(const saga_ctx* ctx, int64_t row_bytes, int32_t 
 // Items of a resident list that four wavefronts share (WorkListParams::long_edges). Narrow rows fit bands of so many source
 // rows that a hub's column is one piece of thousands of edges, and the launch lasts as long as the one wavefront that works
 // it. Layers, us, with none / items past 128 / 512 / 1,024 edges: two GCN layers in training, 16 and 3 features in the second, 944
-// 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23. A band of wider rows is
-// 2,048 of them or fewer, so that only the hubs of small dense graphs have pieces past 1,024 edges: propagation of 128 fp32
-// features, none / 1,024, R-MAT 11 with 64 edges a vertex (both ways) 29 21, R-MAT 12 with 32 28 21, with 120 44 30, R-MAT 14
-// with 64 73.4 72.7, R-MAT 16 194 194; CommNet in training on R-MAT 18 1076 1075.
+// 890 887 892; 16 bf16 features on R-MAT 12 26 16 16 19; SpMM of 32 columns on R-MAT 15 34 21 22 23. With none / 128 / 256: sums of
+// 64 features, R-MAT 13 of degree 16 22 12 14, R-MAT 17 of 100 178 168 167; of 3 (bands of 65,536 rows, a wavefront takes 64 edges
+// at a time), R-MAT 15 of 64 82 26 25, R-MAT 17 of 100 199 89 93, R-MAT 20 of 32 251 263 248.
+// A band of wider rows is 2,048 of them or fewer, so that only the hubs of small dense graphs have pieces past 1,024 edges:
+// propagation of 128 fp32 features, none / 1,024, R-MAT 11 with 64 edges a vertex (both ways) 29 21, R-MAT 12 with 32 28 21, with
+// 120 44 30, R-MAT 14 with 64 73.4 72.7, R-MAT 16 194 194; CommNet in training on R-MAT 18 1076 1075.
 // By the rows per band, which is 4,096 or more at 256 bytes a row and 1 MiB a band, and not by the width itself: widths that
 // share a list go on sharing it.
 static int64_t long_edges(const WorkListParams& p)
 {
     if (p.team > 1) return 0;  // every piece is shared already
-    return p.stripe_rows >= 4096 ? 128 : 1024;
+    return p.stripe_rows >= 32768 ? 256 : p.stripe_rows >= 4096 ? 128 : 1024;
 }
 
 static bool same_params(const WorkListParams& a, const WorkListParams& b)

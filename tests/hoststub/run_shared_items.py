@@ -1,7 +1,8 @@
-"""The work lists of resident propagations, as the kernels get them: items that four wavefronts share are those past 128 edges
-(rows of which a band holds 4,096 or more) or past 1,024, and the first of the list; light columns are its end, in the order
-they should have; every edge is in one item; forwards and backwards (edges by source), with and without bands, lists kept
-for another width among them, on the CPU stand-in.
+"""The work lists of resident propagations, as the kernels get them: items that four wavefronts share are those past 128
+edges where a band holds 4,096 rows, past 256 where it holds 32,768, past 1,024 otherwise, and the first of the list, and
+there are none where no item of narrow rows is far above the average; light columns are its end, in the order they should
+have; every edge is in one item; forwards and backwards (edges by source), with and without bands, lists kept for another
+width among them, on the CPU stand-in.
 
   python tests/hoststub/run_shared_items.py <library>"""
 import ctypes
@@ -39,8 +40,11 @@ def check(ctx, col_ptr, long_edges, expect_long):
     np.add.at(cover, e1, -1)
     assert (np.cumsum(cover)[:-1] == 1).all(), "an edge in no item or in two"
     assert (e0 >= col_ptr[v]).all() and (e1 <= col_ptr[v + 1]).all()
-    assert set(np.flatnonzero(length > long_edges)) == set(range(team)), (team, int((length > long_edges).sum()))
-    assert (team > 0) == expect_long, team
+    if expect_long is not None:
+        assert set(np.flatnonzero(length > long_edges)) == set(range(team)), (team, int((length > long_edges).sum()))
+        assert (team > 0) == expect_long, team
+    else:
+        assert team == 0 and (length > long_edges).all()
     is_light = (slot < 0) & (length <= 16)
     assert is_light.sum() == light and is_light[len(items) - light:].all() and light_edges == length[is_light].sum()
     ll, lv = length[is_light], v[is_light]
@@ -71,8 +75,8 @@ def main():
         h = ctx.graph_create_csc(n, dev(g.col_ptr), dev(g.row_idx))
         for F in (16, 128, 16):
             X, W = t(n, F), t(F, 4)
-            # bands of 1 MiB: 4,096 or more of the rows (or none)
-            long_edges = 128 if "stripe_kb" not in opts and F * 4 <= 256 else 1024
+            # bands of 1 MiB: 16,384 rows of 64 bytes, 65,536 of 16, 2,048 of 512 (or no bands)
+            long_edges = 128 if "stripe_kb" not in opts and F == 16 else 1024
             Y, A = dev(torch.full((n, 4), float("nan"))), dev(torch.full((n, F), float("nan")))
             ctx.layer_forward(h, dev(X), Y, edge_op="copy", W=dev(W), accum_out=A)
             ctx.synchronize()
@@ -85,9 +89,22 @@ def main():
             ctx.layer_backward(h, A, dev(t(n, 4)), dev(W), dW, X=dev(X), edge_op="copy", dX=dX)
             ctx.synchronize()
             width = min(F, 4)                                    # what travels back is the gradient of the narrower side
-            check(ctx, cp_out, 128 if "stripe_kb" not in opts and width * 4 <= 256 else 1024, True)
+            assert width == 4
+            check(ctx, cp_out, 256 if "stripe_kb" not in opts else 1024, True)
         h.destroy()
         ctx.destroy()
+    # every column past the limit: shared where a band holds 4,096 rows, not where it holds more of them
+    n, d = 800, 600
+    g = si.csc_from_lists(n, sorted((int(u), v) for v in range(n) for u in rng.choice(n, d, replace=False)))
+    cp = g.col_ptr.numpy()
+    ctx = StubContext(lib)
+    h = ctx.graph_create_csc(n, dev(g.col_ptr), dev(g.row_idx))
+    for F, long_edges, expect_long in ((16, 128, None), (64, 128, True)):
+        ctx.layer_forward(h, dev(t(n, F)), dev(torch.empty(n, F)), edge_op="copy")
+        ctx.synchronize()
+        check(ctx, cp, long_edges, expect_long)
+    h.destroy()
+    ctx.destroy()
     print("ok: work lists of resident propagations", flush=True)
 
 

@@ -10,8 +10,9 @@ DEV = "cuda"
 
 def _graph(n, heavy, seed, lanes):
     """Degrees 0 to 16, the edges among them, in turn, for rows of more than 8 fragments with four short columns to each, since
-    the kernel takes such rows where columns are short (and, with `heavy`, some of 17 and 300, and four at the lengths from
-    which four wavefronts share an item: 129 of rows up to 256 bytes, 1,025 of a band of wider ones)."""
+    the kernel takes such rows where columns are short (and, with `heavy`, some of 17 and 300, and four at or past the
+    lengths from which four wavefronts share an item: 129 edges at up to 256 bytes a row, 257 at up to 32, 1,025 at
+    more)."""
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
     pattern = [0, 1, 7, 8, 15, 16, 3, 13] + ([1, 0, 2, 1, 1, 0, 1, 2] * 4 if lanes > 8 else [])
