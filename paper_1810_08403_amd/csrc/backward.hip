@@ -113,6 +113,7 @@ static saga_status run_propagation(saga_ctx* ctx, saga_graph* view, GatherArgs g
     ga.items = static_cast<const WorkItem*>(view->d_items.p);
     ga.n_items = view->n_items;
     ga.n_team = view->n_team;
+    ga.light = ga.items + ga.n_items;
     ga.n_light = view->n_light;
     ga.light_edges = view->light_edges;
     ga.n_src = view->n;
@@ -615,6 +616,7 @@ saga_status resident_backward_bf16(saga_ctx* ctx, saga_graph* g, const saga_tens
         ga.items = static_cast<const WorkItem*>(hybrid ? h.items.p : view->d_items.p);
         ga.n_items = hybrid ? h.n_items : view->n_items;
         ga.n_team = hybrid ? h.n_team : view->n_team;
+        ga.light = ga.items + ga.n_items;
         ga.n_light = hybrid ? h.n_light : view->n_light;
         ga.light_edges = hybrid ? h.light_edges : view->light_edges;
         ga.n_src = view->n;

@@ -1461,12 +1461,13 @@ uint32_t table_bytes(const GatherArgs& a, int64_t ld, int esize)
 }
 // Are the light columns short enough that this kernel is the faster one? What it saves is a wavefront's latency per column, and
 // once a column is a few wave-wide loads k_gather_narrow loses nothing by it and hides its loads better. By the fragments of a
-// mean light column (edges x lanes): sums and maxima of one row per edge up to 176, and up to 7.5 edges where a row takes more
-// than 16 lanes; 256 and 8.5 where the table is larger than the 256 MB of cache before the memory, which makes every trip
-// longer; gates up to 100, gradients of a maximum up to 80. us, without and with, 262,144 columns of so many edges (p: random,
+// mean light column (edges x lanes): sums and maxima of one row per edge up to 176, and up to 7.5 edges (9 of bf16) where a row
+// takes more than 16 lanes; 256 and 8.5 where the table is larger than the 256 MB of cache before the memory, which makes
+// every trip longer; gates up to 100, gradients of a maximum up to 80. us, without and with, 262,144 columns of so many edges (p: random,
 // on average; r: all alike), fp32:
 //   sum of 128 features  p5 122 111  p6 137 132  p7 151 151  p8 163 170  r5 111 110  r6 121 129  a million vertices: p6 560 507  p8 672 662
 //           96 features  p7 121 110  p8 131 124  p10 148 153  r6 98 95  r8 118 122               64: r10 106 102  r12 114 121
+//          130 bf16  200,000 columns, p9 112 99
 //           72 features  p7 116 107  p8 125 121  p10 142 146  r6 95 92  r8 114 119               32: r16 92 75
 //   gated, 128 features  r2 350 339  r3 392 386  r4 420 422     72: p4 308 286  p5 321 315  p6 340 342     64: p5 243 230  p6 252 251  p7 263 270
 //           32 features  r10 166 158  r16 200 213
@@ -1476,7 +1477,7 @@ bool light_is_short(const GatherArgs& a, int ef, int lanes, int esize)
 {
     const bool far = a.n_src * a.ld_src * esize > (256LL << 20);
     const int64_t limit = ef == kEfMaxGrad ? 80 : ef != kEfLinear ? 100 : far ? 256 : 176;
-    return a.light_edges * lanes <= limit * a.n_light && (lanes <= 16 || 2 * a.light_edges <= (far ? 17 : 15) * a.n_light);
+    return a.light_edges * lanes <= limit * a.n_light && (lanes <= 16 || 2 * a.light_edges <= (esize == 2 ? 18 : far ? 17 : 15) * a.n_light);
 }
 // Does k_gather_light take the list's light columns (rows of `vec` elements a fragment, at most 32 of them)?
 template <typename T, bool RAG>
@@ -1539,14 +1540,14 @@ hipError_t launch_shape(const GatherArgs& a, hipStream_t s)
 {
     const int nvec = (a.F + VEC - 1) / VEC;
     if (nvec <= 32 && takes_light<T, RAG>(a, EF, VEC)) {
-        const int64_t pieces = a.n_items - a.n_light;
+        const int64_t rest = a.n_items - a.n_light;
         GatherArgs b = a;
-        b.items = a.items + pieces;
+        b.items = a.light;
         b.n_items = a.n_light;
         hipError_t e = launch_light<T, VEC, RAG, AGG, EF>(b, nvec, s);
-        if (e != hipSuccess || pieces == 0) return e;
+        if (e != hipSuccess || rest == 0) return e;
         b = a;
-        b.n_items = pieces;
+        b.n_items = rest;
         b.n_light = 0;
         return launch_shape<T, VEC, RAG, AGG, EF>(b, s);
     }

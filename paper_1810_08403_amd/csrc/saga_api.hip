@@ -143,7 +143,8 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
     out->heavy.clear();
     out->n_slots = 0;
     out->n_team = 0;
-    out->n_light = out->light_edges = 0;
+    out->light_edges = 0;
+    out->light.clear();
     out->max_degree = 0;
     std::vector<WorkItem> whole, light;
     light.reserve((size_t)n_cols);
@@ -248,12 +249,17 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
         if (!split_long || !is_long(pc.it)) out->items.push_back(pc.it);
     for (const WorkItem& it : whole)
         if (!split_long || !is_long(it)) out->items.push_back(it);
-    // Columns that are worked side by side in one wavefront are to be equally long: longest first within every 1,024 of
-    // them, which are read at about the same time wherever they stand.
-    out->n_light = (int64_t)light.size();
+    // Short columns last (sums of wide rows on R-MAT 17, 16 edges a vertex, us, so and among the longer ones: 520 fp32 features
+    // 427 and 459, 800 652 and 717) and in column order: a wavefront reads ids and writes rows next to its neighbours'.
+    out->items.insert(out->items.end(), light.begin(), light.end());
+    // A copy in order of length for k_gather_light, unless columns are too few or the list is a streamed chunk's. Columns that are worked side by side in one wavefront
+    // are to be equally long: longest first within every 1,024 of them, which are read at about the same time wherever they
+    // stand. The other kernels are slower in that order (200,000 columns of 8 edges, sums, us, in column order and by length:
+    // 90 fp32 features 119 and 130, 130 160 and 174, 300 bf16 181 and 197).
+    if (p.skip_empty || light.size() < 2048) return;
     for (const WorkItem& it : light) out->light_edges += it.e1 - it.e0;
-    out->items.resize(out->items.size() + light.size());
-    WorkItem* to = out->items.data() + (out->items.size() - light.size());
+    out->light.resize(light.size());
+    WorkItem* to = out->light.data();
     for (size_t i = 0; i < light.size(); i += 1024) {
         const size_t m = std::min<size_t>(1024, light.size() - i);
         size_t at[kLightEdges + 2] = {};  // at[k]: where the next column of kLightEdges - k edges goes
@@ -675,6 +681,8 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
     } catch (...) {
         return ctx->fail(SAGA_ERR_INTERNAL, "out of host memory");
     }
+    const int64_t n_items = (int64_t)wl.items.size();
+    wl.items.insert(wl.items.end(), wl.light.begin(), wl.light.end());  // one buffer for both
     if (saga_status st = ctx->dev_alloc(&g->d_items, sizeof(WorkItem) * std::max<size_t>(wl.items.size(), 1))) return st;
     if (saga_status st = ctx->dev_alloc(&g->d_heavy, sizeof(HeavyVertex) * std::max<size_t>(wl.heavy.size(), 1))) return st;
     if (!wl.items.empty())
@@ -682,9 +690,9 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
     if (!wl.heavy.empty())
         HIP_TRY(ctx, hipMemcpyAsync(g->d_heavy.p, wl.heavy.data(), sizeof(HeavyVertex) * wl.heavy.size(), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // wl goes out of scope below
-    g->n_items = (int64_t)wl.items.size();
+    g->n_items = n_items;
     g->n_team = wl.n_team;
-    g->n_light = wl.n_light;
+    g->n_light = (int64_t)wl.light.size();
     g->light_edges = wl.light_edges;
     g->n_heavy = (int64_t)wl.heavy.size();
     g->n_slots = wl.n_slots;
@@ -759,6 +767,8 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
         const int32_t v = plan.dst_order[i];
         if (v >= 0 && plan.extra_slots[(size_t)v] > 0) tile_row_slot0[i] = slot0_of[(size_t)v];
     }
+    const int64_t n_items = (int64_t)wl.items.size();
+    wl.items.insert(wl.items.end(), wl.light.begin(), wl.light.end());  // one buffer for both
     auto up = [&](DevBuf* b, const void* src, size_t bytes) -> saga_status {
         if (saga_status st = ctx->dev_alloc(b, std::max<size_t>(bytes, 16))) return st;
         if (bytes) HIP_TRY(ctx, hipMemcpyAsync(b->p, src, bytes, hipMemcpyHostToDevice, ctx->stream));
@@ -796,9 +806,9 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     h.n_blocks = (int64_t)plan.blk_src_tile.size();
     h.n_dense_edges = plan.n_dense_edges;
     h.n_rem_edges = (int64_t)plan.rem_row_idx.size();
-    h.n_items = (int64_t)wl.items.size();
+    h.n_items = n_items;
     h.n_team = wl.n_team;
-    h.n_light = wl.n_light;
+    h.n_light = (int64_t)wl.light.size();
     h.light_edges = wl.light_edges;
     h.n_heavy = (int64_t)wl.heavy.size();
     h.n_slots = wl.n_slots;
@@ -1145,6 +1155,7 @@ saga_status saga_plan_work_list(int64_t n, const int64_t* col_ptr, const int32_t
     if (n_split_vertices) *n_split_vertices = (int64_t)wl.heavy.size();
     if (n_slots) *n_slots = wl.n_slots;
     if (items_out) {
+        std::copy(wl.light.begin(), wl.light.end(), wl.items.end() - (ptrdiff_t)wl.light.size());  // as k_gather_light has them
         const int64_t m = std::min<int64_t>(capacity, (int64_t)wl.items.size());
         memcpy(items_out, wl.items.data(), sizeof(WorkItem) * (size_t)m);
     }
@@ -1660,6 +1671,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     ga.items = static_cast<const WorkItem*>(hybrid ? g->hyb.items.p : g->d_items.p);
     ga.n_items = hybrid ? g->hyb.n_items : g->n_items;
     ga.n_team = hybrid ? g->hyb.n_team : g->n_team;
+    ga.light = ga.items + ga.n_items;
     ga.n_light = hybrid ? g->hyb.n_light : g->n_light;
     ga.light_edges = hybrid ? g->hyb.light_edges : g->light_edges;
     ga.n_src = n;

@@ -102,8 +102,10 @@ struct WorkList {
     std::vector<HeavyVertex> heavy;
     int64_t n_team = 0;
     int64_t n_slots = 0;
-    int64_t n_light = 0;  // items at the end of the list that are whole columns of at most kLightEdges edges
-    int64_t light_edges = 0;  // edges of those
+    // The whole columns of at most kLightEdges edges at the end of the list, where k_gather_light may take them (else empty):
+    // longest first within every 1,024.
+    std::vector<WorkItem> light;
+    int64_t light_edges = 0;  // their edges
     int64_t max_degree = 0;
 };
 
@@ -367,9 +369,6 @@ struct GatherArgs {
     const WorkItem* items;
     int64_t n_items;
     int64_t n_team;          // items [0, n_team) are processed by a whole workgroup each
-    int64_t n_light;         // the last n_light items are whole columns of at most kLightEdges edges (0: not known)
-    int64_t light_edges;     // edges of those
-    int64_t n_src, n_edges;  // rows of src (src2, src3), edges of row_idx; 0: not known
     const int32_t* row_idx;  // source ids, local to the rows of `src`
     const float* edge_w;     // nullable (COPY)
     // LINEAR ops: src = X (dtype), ld_src elements between rows, F features.
@@ -408,6 +407,12 @@ struct GatherArgs {
     // to every finished row (whole-column items here, cut columns in the combine pass); not with `accumulate`
     const float* bias;       // [F] fp32, nullable
     int32_t act;             // saga_act
+    // for the launch alone, behind what the kernels read: the last n_light items again, whole columns of at most kLightEdges
+    // edges, in order of length (n_light 0: no such copy)
+    const WorkItem* light;
+    int64_t n_light;
+    int64_t light_edges;     // edges of those
+    int64_t n_src, n_edges;  // rows of src (src2, src3), edges of row_idx; 0: not known
 };
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
 

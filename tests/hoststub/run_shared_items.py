@@ -1,7 +1,7 @@
 """The work lists of resident propagations, as the kernels get them: items that four wavefronts share are those past 128
 edges where a band holds 4,096 rows, past 256 where it holds 32,768, past 1,024 otherwise, and the first of the list, and
-there are none where no item of narrow rows is far above the average; light columns are its end, in the order they should
-have; every edge is in one item; forwards and backwards (edges by source), with and without bands, lists kept for another
+there are none where no item of narrow rows is far above the average; light columns end it,
+and lie behind it once more in order of length; every edge is in one item; forwards and backwards (edges by source), with and without bands, lists kept for another
 width among them, on the CPU stand-in.
 
   python tests/hoststub/run_shared_items.py <library>"""
@@ -23,16 +23,16 @@ from stub_binding import StubContext, dev
 
 
 def last_list(ctx, capacity):
-    items, counts = np.full((capacity, 4), -1, np.int32), (ctypes.c_int64 * 4)()
-    ctx.lib.stub_last_work_list(items.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(capacity), counts)
+    items, by_length, counts = np.full((capacity, 4), -1, np.int32), np.full((capacity, 4), -1, np.int32), (ctypes.c_int64 * 4)()
+    ctx.lib.stub_last_work_list(items.ctypes.data_as(ctypes.c_void_p), by_length.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(capacity), counts)
     n, team, light, light_edges = counts
     assert n <= capacity
-    return items[:n].astype(np.int64), team, light, light_edges
+    return items[:n].astype(np.int64), by_length[:light].astype(np.int64), team, light, light_edges
 
 
-def check(ctx, col_ptr, long_edges, expect_long):
+def check(ctx, col_ptr, long_edges, expect_long, expect_light):
     nnz, n = int(col_ptr[-1]), len(col_ptr) - 1
-    items, team, light, light_edges = last_list(ctx, nnz + n)
+    items, by_length, team, light, light_edges = last_list(ctx, nnz + n)
     v, e0, e1, slot = items.T
     length = e1 - e0
     cover = np.zeros(nnz + 1, np.int64)
@@ -45,12 +45,17 @@ def check(ctx, col_ptr, long_edges, expect_long):
         assert (team > 0) == expect_long, team
     else:
         assert team == 0 and (length > long_edges).all()
+    # the light columns end the list, in column order; their copy has the longest first within every 1,024
     is_light = (slot < 0) & (length <= 16)
-    assert is_light.sum() == light and is_light[len(items) - light:].all() and light_edges == length[is_light].sum()
-    ll, lv = length[is_light], v[is_light]
+    n_light = int(is_light.sum())
+    assert is_light[len(items) - n_light:].all() and (np.diff(v[is_light]) > 0).all()
+    assert light == (n_light if expect_light else 0)
+    if light:
+        assert light_edges == length[is_light].sum()
     for i in range(0, light, 1024):
-        key = (16 - ll[i:i + 1024]) * n + lv[i:i + 1024]
-        assert (np.diff(key) > 0).all()
+        part = by_length[i:i + 1024]
+        assert (np.diff((16 - (part[:, 2] - part[:, 1])) * n + part[:, 0]) > 0).all()
+        assert np.array_equal(part[np.argsort(part[:, 0])], items[is_light][i:i + 1024])
     pieces = slot >= 0
     assert sorted(slot[pieces].tolist()) == list(range(int(pieces.sum())))
 
@@ -82,7 +87,7 @@ def main():
             ctx.synchronize()
             # cut at band ends, rows of 128 features make pieces of 2,048 sources at most; uncut, the hub is one item
             hub_piece = int((ri[cp[7]:cp[7 + 1]] < 2048).sum())
-            check(ctx, cp, long_edges, True if long_edges == 128 or "cut_degree" in opts and opts["cut_degree"] > 5200 else hub_piece > 1024)
+            check(ctx, cp, long_edges, True if long_edges == 128 or "cut_degree" in opts and opts["cut_degree"] > 5200 else hub_piece > 1024, True)
             ref = oracle.layer(cp, ri, X.numpy(), "copy", None, agg="sum", W=W.numpy())
             assert_sum_close(Y.t.numpy(), ref["Y"], ref["Y_abs"], 1e-4, f"{opts} F {F}")
             dX, dW = dev(torch.full((n, F), float("nan"))), dev(torch.full((F, 4), float("nan")))
@@ -90,7 +95,7 @@ def main():
             ctx.synchronize()
             width = min(F, 4)                                    # what travels back is the gradient of the narrower side
             assert width == 4
-            check(ctx, cp_out, 256 if "stripe_kb" not in opts else 1024, True)
+            check(ctx, cp_out, 256 if "stripe_kb" not in opts else 1024, True, True)
         h.destroy()
         ctx.destroy()
     # every column past the limit: shared where a band holds 4,096 rows, not where it holds more of them
@@ -102,7 +107,7 @@ def main():
     for F, long_edges, expect_long in ((16, 128, None), (64, 128, True)):
         ctx.layer_forward(h, dev(t(n, F)), dev(torch.empty(n, F)), edge_op="copy")
         ctx.synchronize()
-        check(ctx, cp, long_edges, expect_long)
+        check(ctx, cp, long_edges, expect_long, False)
     h.destroy()
     ctx.destroy()
     print("ok: work lists of resident propagations", flush=True)

@@ -51,7 +51,7 @@ float apply_act(float y, int act)
 const float kNegInf = -__builtin_huge_valf();
 
 // the work list of the last propagation that ran (stub_last_work_list)
-std::vector<WorkItem> g_list;
+std::vector<WorkItem> g_list, g_list_sorted;
 int64_t g_list_team = 0, g_list_light = 0, g_list_light_edges = 0;
 
 // what a propagation says about its list and its tables, on which kernels rely
@@ -59,11 +59,12 @@ void check_list(const GatherArgs& a)
 {
     if (a.n_team < 0 || a.n_light < 0 || a.n_team > a.n_items || a.n_light > a.n_items - a.n_team) die("counts of a work list out of range");
     int64_t light_edges = 0;
-    for (int64_t i = a.n_items - a.n_light; i < a.n_items; ++i) {
-        if (a.items[i].e1 - a.items[i].e0 > kLightEdges) die("a long item among the light columns");
-        light_edges += a.items[i].e1 - a.items[i].e0;
+    for (int64_t i = 0; i < a.n_light; ++i) {
+        if (a.light[i].e1 - a.light[i].e0 > kLightEdges) die("a long item among the light columns");
+        light_edges += a.light[i].e1 - a.light[i].e0;
     }
     if (a.n_light > 0 && light_edges != a.light_edges) die("edges of the light columns miscounted");
+    g_list_sorted.assign(a.light, a.light + a.n_light);
     for (int64_t i = 0; i < a.n_items; ++i) {
         if (a.n_edges > 0 && a.items[i].e1 > a.n_edges) die("a work item past the edges");
         if (a.n_src > 0)
@@ -234,9 +235,11 @@ hipError_t launch_gather(const GatherArgs& a, hipStream_t s)
     return hipSuccess;
 }
 
-// items of that list (as many as fit `capacity`); counts: items, of them shared ones at its start, light columns at its end, their edges
-extern "C" void stub_last_work_list(int32_t* items, int64_t capacity, int64_t* counts)
+// Items of that list and the light columns' copy in order of length, if there is one (as many as fit `capacity`); counts: items,
+// shared ones at their start, light columns, their edges.
+extern "C" void stub_last_work_list(int32_t* items, int32_t* light, int64_t capacity, int64_t* counts)
 {
+    memcpy(light, g_list_sorted.data(), sizeof(WorkItem) * std::min<size_t>((size_t)capacity, g_list_sorted.size()));
     counts[0] = (int64_t)g_list.size();
     counts[1] = g_list_team;
     counts[2] = g_list_light;
