@@ -224,7 +224,7 @@ void build_work_list(const int64_t* col_ptr, const int32_t* row_idx, int64_t n_c
         if (a.it.v != b.it.v) return a.it.v < b.it.v;
         return a.it.e0 < b.it.e0;
     });
-    out->items.reserve(pieces.size() + whole.size() + light.size());
+    out->items.reserve(pieces.size() + whole.size() + 2 * light.size());  // (callers append the copy of the light ones)
     bool split_long = team == 1 && p.long_edges > 0;
     auto is_long = [&](const WorkItem& it) { return it.e1 - it.e0 > p.long_edges; };
     if (split_long && R > 4096) {
