@@ -375,6 +375,8 @@ saga_status saga_get_timings(saga_ctx* ctx, saga_timings* out); /* synchronises 
  *   "team"       0/1, a piece of a cut column is worked by a whole workgroup whose four
  *                wavefronts reduce through LDS, and holds at least 4 * split edges (default 0:
  *                fewer partial rows, but measured slower than one wavefront per piece)
+ *   "small_layer" 0/1, a COPY or MUL_WEIGHT layer of a few thousand fp32 rows, without W_self, in one launch, with the
+ *                same results (default 1)
  *   "xcd_remap"  0/1, keep neighbouring work items on one XCD (default 1)
  *   "mma"        0/1 (default 0): sums over COPY / MUL_WEIGHT messages of bf16 rows of 264..512 features
  *                form `acc += w_e * x` on the matrix unit instead of the vector ALUs. Edge weights enter

@@ -1373,6 +1373,9 @@ saga_status saga_set_option(saga_ctx* ctx, const char* name, int64_t value)
     } else if (!strcmp(name, "mma")) {
         if (value != 0 && value != 1) return ctx->fail(SAGA_ERR_INVALID_ARG, "mma must be 0 or 1");
         ctx->opt_mma = (int)value;
+    } else if (!strcmp(name, "small_layer")) {
+        if (value != 0 && value != 1) return ctx->fail(SAGA_ERR_INVALID_ARG, "small_layer must be 0 or 1");
+        ctx->opt_small = (int)value;
     } else if (!strcmp(name, "xcd_remap")) {
         if (value != 0 && value != 1) return ctx->fail(SAGA_ERR_INVALID_ARG, "xcd_remap must be 0 or 1");
         ctx->opt_xcd_remap = (int)value;
@@ -1618,6 +1621,37 @@ saga_status saga_graph_info(const saga_graph* g, int64_t* max_in_degree, int64_t
 // ---------------------------------------------------------------------------
 // one layer, everything resident in HBM
 // ---------------------------------------------------------------------------
+// Does the one-launch kernel take the layer whose propagation is `ga`?
+static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_tensor* X, const saga_edge_params* ep, const saga_vertex_params* vp,
+                        const saga_tensor* Y, const GatherArgs& ga, int64_t n_slots)
+{
+    if (!launch_layer_small || !ctx->opt_small || !ctx->opt_fused || ctx->opt_team || !vp || !vp->W || vp->W_self) return false;
+    if ((ep->op != SAGA_EDGE_COPY && ep->op != SAGA_EDGE_MUL_WEIGHT) || X->dtype != SAGA_F32) return false;
+    if (g->nnz == 0 || g->nnz >= (1LL << 30) - 64 || X->cols < kSmallMinF || X->cols > kSmallMaxF) return false;
+    if (((g->n - 1) * X->ld + X->cols) * 4 >= 0xffff0000LL) return false;
+    // Whole columns, none so long that the workgroup waits for one of its 32; weights that fit its LDS as split units; and not so many
+    // rows that the latency of a launch is a small part of it: then the general kernels have more wavefronts in flight, and a
+    // workgroup here makes the weights' units for 32 rows only. Layers of so many vertices of 8 / 30 edges, features x outputs, us,
+    // two or three launches and one (10 is the host's part of a call):
+    //   1,024   64x64 15.0 10.0 / 14.9 10.4   64x256 14.9 11.5 / 15.0 13.3   128x16 17.0 11.1 / 17.7 14.3   128x128 16.9 13.0 / 17.6 16.4
+    //   4,096   64x64 15.0  9.9 / 15.0 10.7   64x256 16.1 12.1 / 16.4 13.9   128x16 17.5 11.1 / 19.1 14.4   128x128 23.3 13.4 / 24.6 16.7
+    //   8,192   64x64 19.6 10.4 / 20.7 11.4   64x256 18.3 12.8 / 19.4 15.3   128x16 20.1 11.8 / 23.2 16.4   128x128 22.6 14.7 / 25.3 19.5
+    //   16,384  64x64 20.5 12.9 / 23.6 18.2   64x256 23.4 25.0 / 26.3 31.2   128x16 23.6 19.2 / 34.6 32.5   128x128 26.5 30.0 / 38.1 43.9
+    //   32,768  16x16 19.8 14.6 / 23.3 18.3   64x64  28.4 23.6 / 36.5 38.3   128x16 33.0 32.6 / 68.9 68.5   128x128 39.4 59.0 / 76.7 96.4
+    //   65,536  16x16 31.5 28.6 / 36.6 38.0   64x64  44.5 43.5 / 77.6 79.2
+    const int64_t F = X->cols, N = vp->W->cols, n = g->n;
+    if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || (N + 31) / 32 * ((F + 31) / 32 * 2) > kSmallUnits) return false;
+    if (n > 32768 || n * F * N > (n <= 16384 ? 1LL << 27 : 1LL << 25)) return false;
+    // Two launches read everything before they write results; one must not write what its other workgroups read.
+    auto apart = [](const void* p, int64_t bytes, const void* q, int64_t more) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+        return !p || !q || a + (uintptr_t)bytes <= b || b + (uintptr_t)more <= a;
+    };
+    auto extent = [](const saga_tensor* t) { return t ? ((t->rows - 1) * t->ld + t->cols) * 4 : 0; };
+    return apart(X->data, extent(X), Y->data, extent(Y)) && apart(vp->W->data, extent(vp->W), Y->data, extent(Y)) &&
+           apart(vp->bias ? vp->bias->data : nullptr, extent(vp->bias), Y->data, extent(Y)) && apart(ga.edge_w, g->nnz * 4, Y->data, extent(Y));
+}
+
 static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_tensor* X, const saga_edge_params* ep,
                                     int32_t agg, const saga_vertex_params* vp, saga_tensor* Y, saga_tensor* accum_out)
 {
@@ -1771,6 +1805,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         if (saga_status st = ctx->dev_alloc(&ctx->ws_partials, sizeof(float) * (size_t)n_slots * ga.F)) return st;
         ga.partials = static_cast<float*>(ctx->ws_partials.p);
     }
+    const bool small = !tf && !hybrid && small_layer(ctx, g, X, ep, vp, Y, ga, n_slots);
     bool dense_forked = false;
     if (hybrid) {
         const bool weighted = ep->op == SAGA_EDGE_MUL_WEIGHT;
@@ -1799,7 +1834,31 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         ga.op = SAGA_EDGE_COPY;
         ga.mma = 0;
     }
-    HIP_TRY(ctx, launch_gather(ga, s));
+    if (small) {
+        SmallLayerArgs sa{};
+        sa.items = ga.items;
+        sa.n_items = ga.n_items;
+        sa.row_idx = ga.row_idx;
+        sa.edge_w = ga.edge_w;
+        sa.X = static_cast<const float*>(ga.src);
+        sa.ldx = ga.ld_src;
+        sa.n_src = n;
+        sa.n_edges = g->nnz;
+        sa.F = F;
+        sa.N = (int32_t)vp->W->cols;
+        sa.W = static_cast<const float*>(vp->W->data);
+        sa.ldw = vp->W->ld;
+        sa.bias = vp->bias ? static_cast<const float*>(vp->bias->data) : nullptr;
+        sa.act = vp->act;
+        sa.agg = agg;
+        sa.Y = static_cast<float*>(Y->data);
+        sa.ldy = Y->ld;
+        sa.A = accum_out ? static_cast<float*>(accum_out->data) : nullptr;
+        sa.lda = accum_out ? accum_out->ld : 0;
+        HIP_TRY(ctx, launch_layer_small(sa, s));
+    } else {
+        HIP_TRY(ctx, launch_gather(ga, s));
+    }
     if (dense_forked) HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_join, 0));
     if (es) HIP_TRY(ctx, hipEventRecord(es->ev[2], s));
 
@@ -1822,7 +1881,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     }
     if (es) HIP_TRY(ctx, hipEventRecord(es->ev[3], s));
 
-    if (has_w && !tf) {
+    if (has_w && !tf && !small) {
         const void* A = bf16 ? static_cast<const void*>(ga.out16) : static_cast<const void*>(ga.out);
         const int64_t lda = bf16 ? ga.ld_out16 : ga.ld_out;
         if (saga_status st = run_apply_vertex(ctx, A, lda, X->dtype, n, Fm, vp, X->data, X->ld, F, Y->data, Y->ld, Y->dtype))

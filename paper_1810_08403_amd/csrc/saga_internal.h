@@ -205,6 +205,7 @@ struct saga_ctx {
     int64_t opt_stripe_kb = 1024;  // source-row band one piece may span, in KiB of feature rows (0 = cut by count)
     bool opt_stripe_set = false;   // the caller has chosen it (the remainder of the dense-block path otherwise takes wider bands for 1 KiB rows)
     int opt_piece_order = 1;       // see WorkListParams::order
+    int opt_small = 1;             // 1: propagation and ApplyVertex of small fp32 layers in one launch (small.hip)
     int opt_xcd_remap = 1;
     int opt_mma = 0;               // 1: bf16 sum propagation with the multiply-accumulate on the matrix unit (measured: a tie)
     int opt_team = 0;              // 1: a piece of a cut column is worked by a whole workgroup (measured slower)
@@ -415,6 +416,31 @@ struct GatherArgs {
     int64_t n_src, n_edges;  // rows of src (src2, src3), edges of row_idx; 0: not known
 };
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
+
+// A small fp32 layer, propagation (COPY, MUL_WEIGHT) and ApplyVertex, in one launch (small.hip): whole columns only, no self
+// operand, n_items < 2^31. Weak: a stand-in for the kernels need not have it.
+struct SmallLayerArgs {
+    const WorkItem* items;
+    int64_t n_items;
+    const int32_t* row_idx;
+    const float* edge_w;     // nullable
+    const float* X;
+    int64_t ldx;
+    int64_t n_src, n_edges;
+    int32_t F, N;
+    const float* W;          // F x N, row-major
+    int64_t ldw;
+    const float* bias;       // [N], nullable
+    int32_t act, agg;
+    float* Y;
+    int64_t ldy;
+    float* A;                // the propagation's rows, nullable
+    int64_t lda;
+};
+constexpr int kSmallMinF = 13, kSmallMaxF = 128;  // rows of 4 to 32 fragments
+constexpr int kSmallMaxN = 256;                    // 32 columns a wavefront
+constexpr int kSmallUnits = 32;                    // 32 columns x 16 k of the weights, 3 KiB of LDS each
+hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s) __attribute__((weak));
 
 struct CombineArgs {
     const HeavyVertex* heavy;

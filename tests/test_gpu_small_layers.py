@@ -1,0 +1,111 @@
+"""Small fp32 layers in one launch: propagation and ApplyVertex together (option small_layer), at the edges of its tiles, batches and
+widths, against the general kernels, whose results it gives bit for bit, and float64 products of the rows."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _graph(n, seed, longest=96):
+    """Columns of every length at which a batch of ids or a group of reads ends, empty ones among them."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    pattern = [0, 1, 3, 4, 5, 15, 16, 17, 0, 31, 32, 33, 2, 48, 64, longest]
+    deg = torch.tensor(pattern, device=DEV).repeat(-(-n // len(pattern)))[:n].clamp(max=n)
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), deg)
+    first = torch.repeat_interleave(torch.cumsum(deg, 0) - deg, deg)
+    start = torch.randint(0, n, (n,), generator=g, device=DEV)
+    step = next(s for s in (7, 11, 13, 17) if n % s)
+    src = (start[dst] + step * (torch.arange(dst.numel(), device=DEV) - first)) % n   # no source twice in a column
+    key = torch.sort(dst * n + src).values
+    col_ptr = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    torch.cumsum(deg, 0, out=col_ptr[1:])
+    return col_ptr, (key % n).int(), g
+
+
+def _context(n, col_ptr, row_idx, small):
+    import paper_1810_08403_amd as saga
+    ctx = saga.Context(0)
+    ctx.set_option("small_layer", small)
+    return ctx, ctx.graph_create_csc(n, col_ptr, row_idx)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 250, 4099])
+@pytest.mark.parametrize("F,N", [(13, 1), (16, 16), (17, 15), (31, 64), (32, 65), (33, 17), (64, 64), (64, 256), (64, 257), (65, 128), (127, 33), (128, 128)])
+@pytest.mark.parametrize("agg", ["sum", "max"])
+def test_rows_and_products(n, F, N, agg):
+    col_ptr, row_idx, g = _graph(n, F + N)
+    w = torch.randn(max(1, row_idx.numel()), generator=g, device=DEV)[:row_idx.numel()]
+    X = torch.randn(n, F + 3, generator=g, device=DEV)[:, :F]
+    W = torch.randn(F, N + 2, generator=g, device=DEV)[:, :N]
+    bias = torch.randn(N, generator=g, device=DEV)
+    for weight, act in ((w, "none"), (None, "relu")):
+        if weight is not None and row_idx.numel() == 0:
+            continue
+        out = []
+        for small in (0, 1):
+            ctx, h = _context(n, col_ptr, row_idx, small)
+            args = dict(edge_op="copy" if weight is None else "mul_weight", agg=agg, W=W, bias=bias, act=act)
+            if weight is not None:
+                args["edge_weight"] = weight
+            A = torch.full((n, F), float("nan"), device=DEV)
+            Y = torch.full((n, N + 1), 7.0, device=DEV)
+            ctx.layer_forward(h, X, Y[:, :N], accum_out=A, **args)
+            alone = torch.empty(n, N, device=DEV)
+            ctx.layer_forward(h, X, alone, **args)
+            torch.cuda.synchronize()
+            assert torch.equal(alone, Y[:, :N]) and bool((Y[:, N] == 7.0).all())
+            out.append((A, alone))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+        A, Y = out[1]
+        ref = A.double() @ W.double() + bias.double()
+        size = A.double().abs() @ W.double().abs() + bias.double().abs()
+        if act == "relu":
+            ref = ref.clamp(min=0)
+        # a rounding per 16 values of k, of the two sums and of the bias, and the products left out, 2^-26 of each
+        assert bool(((Y.double() - ref).abs() <= (-(-F // 16) + 4) * 2.0**-24 * size).all())
+
+
+@pytest.mark.parametrize("longest", [96, 97])
+def test_columns_at_the_longest_taken(longest):
+    n, F = 400, 64
+    col_ptr, row_idx, g = _graph(n, 5, longest)
+    X, W = torch.randn(n, F, generator=g, device=DEV), torch.randn(F, F, generator=g, device=DEV)
+    ctx, h = _context(n, col_ptr, row_idx, 1)
+    Y = torch.empty(n, F, device=DEV)
+    ctx.layer_forward(h, X, Y, edge_op="copy", W=W, act="none")
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), col_ptr[1:] - col_ptr[:-1])
+    ref = torch.zeros(n, F, dtype=torch.float64, device=DEV).index_add_(0, dst, X.double()[row_idx.long()]) @ W.double()
+    assert float((Y.double() - ref).norm() / ref.norm()) < 3e-7
+
+
+def test_results_in_the_place_of_the_features():
+    """Y may be X's own memory: then no row may be written while others are still read."""
+    n, F = 3000, 64
+    col_ptr, row_idx, g = _graph(n, 9)
+    X, W = torch.randn(n, F, generator=g, device=DEV), torch.randn(F, F, generator=g, device=DEV)
+    ctx, h = _context(n, col_ptr, row_idx, 1)
+    Y = torch.empty(n, F, device=DEV)
+    ctx.layer_forward(h, X, Y, edge_op="copy", W=W, act="relu")
+    ctx.layer_forward(h, X, X, edge_op="copy", W=W, act="relu")
+    assert float((X - Y).norm() / Y.norm()) < 1e-6
+
+
+def test_not_finite_values_reach_their_own_columns_only():
+    n, F = 640, 48
+    col_ptr, row_idx, g = _graph(n, 11)
+    X, W = torch.randn(n, F, generator=g, device=DEV), torch.randn(F, F, generator=g, device=DEV)
+    X[5], X[77, 3] = float("nan"), float("inf")
+    ctx, h = _context(n, col_ptr, row_idx, 1)
+    Y, A = torch.empty(n, F, device=DEV), torch.empty(n, F, device=DEV)
+    ctx.layer_forward(h, X, Y, accum_out=A, edge_op="copy", W=W, act="none")
+    ctx0, h0 = _context(n, col_ptr, row_idx, 0)
+    Y0 = torch.empty(n, F, device=DEV)
+    ctx0.layer_forward(h0, X, Y0, edge_op="copy", W=W, act="none")
+    assert torch.equal(torch.nan_to_num(Y, 1e3, 2e3, 3e3), torch.nan_to_num(Y0, 1e3, 2e3, 3e3))
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), col_ptr[1:] - col_ptr[:-1])
+    hit = torch.zeros(n, dtype=torch.bool, device=DEV)
+    hit[dst[(row_idx == 5) | (row_idx == 77)]] = True
+    assert bool(hit.any()) and not bool(hit.all())
+    assert bool((torch.isfinite(Y).all(1) == ~hit).all()) and bool((torch.isfinite(A).all(1) == ~hit).all())
