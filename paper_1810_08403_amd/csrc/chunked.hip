@@ -364,8 +364,12 @@ saga_status streamed_forward(saga_ctx* ctx, saga_graph* g, const saga_tensor* X,
     int Q = ctx->opt_dst_intervals, P = ctx->opt_src_intervals;
     int64_t y_tile_rows = 0;
     auto tile_rows_for = [&](int q) {
-        const int64_t Dq = (n + q - 1) / q;
-        return std::min<int64_t>(Dq, std::max<int64_t>(4096, (64 << 20) / (F_out * 4)));  // about 64 MiB per tile
+        // About 64 MiB a tile, but a sixteenth of a smaller budget, down to 8 MiB: two tiles stand beside the accumulator, and the
+        // fewer destination intervals that leaves, the less often all vertex data cross the link (256 MiB, 262,144 vertices of 256
+        // features in and out: 64 MiB three intervals and 23.9 ms, 16 MiB two and 16.7, 8 MiB two and 17.0).
+        const int64_t Dq = (n + q - 1) / q, mib = 1 << 20;
+        const int64_t tile = ctx->budget > 0 ? std::min(64 * mib, std::max<int64_t>(8 * mib, (int64_t)(ctx->budget / 16))) : 64 * mib;
+        return std::min<int64_t>(Dq, std::max<int64_t>(4096, tile / (F_out * 4)));
     };
     const bool same_grid = g->grid && g->grid->wlp.min_edges == wlp.min_edges && g->grid->wlp.cut_degree == wlp.cut_degree &&
                            g->grid->wlp.stripe_rows == wlp.stripe_rows && g->grid->wlp.team == wlp.team &&
