@@ -10,7 +10,9 @@
 // which that is cheaper than the sparse kernel (build_hybrid_plan), the sparse kernel keeps the rest.
 //
 // One workgroup works a chunk of consecutive blocks of one destination tile; its four wavefronts own 128
-// features each (512 per pass over the chunk). Per block:
+// features each (512 per pass over the chunk). Rows of up to 256 features have work for two such wavefronts, of 128
+// for one: there a wavefront owns 128 features of 32 or 16 of the 64 destinations (MT of the four 16-row sub-tiles), so
+// that all four multiply. Per block:
 //   - every wavefront loads its 256-byte slice of the block's 32 source rows, a lane 8 rows x 16 bytes, and
 //     turns the 8 x 8 (row x feature) patch it holds into the instruction's B operands (8 sources of one
 //     feature per lane) with byte permutes;
@@ -45,8 +47,15 @@ __device__ __forceinline__ uint16_t bf16_rne(float f)
 // Wave-uniform reads through the constant address space arrive in scalar registers (read-only scalar loads).
 typedef const int32_t __attribute__((address_space(4))) * c_i32;
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense_blocks(const DenseArgs a)
+// MT: 16-destination sub-tiles per wavefront. A wavefront of fewer sub-tiles reads the same source rows as its neighbour (through the
+// L1) and has registers for both parts of the weights, so it forms each B operand once instead of once per part; every
+// accumulator takes the same products in the same order whatever MT is. 3,747 blocks in chunks of 16, four sub-tiles a
+// wavefront and two of the four idle: 45 us at 256 features, now 35; at 128 features 37, now 34 (layer forward and backward 714 ->
+// 702 and 417 -> 400).
+template <int MT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 3 : 2, MT == 1 ? 4 : 2))) void k_dense_blocks(const DenseArgs a)
 {
+    constexpr int kSlices = MT;  // 128-feature slices a pass covers: 4 / MT wavefronts on each
     // [buffer][part: 0 high, 1 low][cell], cells in the lane order of the A operand
     __shared__ __attribute__((aligned(16))) uint16_t lds[3][2][kCells];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -55,7 +64,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 c_ft = (c_i32)(uintptr_t)a.blk_tile;
     const int ch_tile = c_chunks[4 * (int64_t)blockIdx.x], ch_b0 = c_chunks[4 * (int64_t)blockIdx.x + 1],
               ch_b1 = c_chunks[4 * (int64_t)blockIdx.x + 2], ch_cidx = c_chunks[4 * (int64_t)blockIdx.x + 3];
-    const int n_pass = (a.F + 511) / 512;
+    const int n_pass = (a.F + 128 * kSlices - 1) / (128 * kSlices);
+    const int slice = wave & (kSlices - 1), mt0 = MT == 4 ? 0 : wave / kSlices * MT;
 
     auto clear = [&](int buf) {  // 8 KiB: 32 bytes per thread
         u32x4* p = reinterpret_cast<u32x4*>(&lds[buf][0][0]);
@@ -105,7 +115,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto id_of = [&](const Bounds& bd) { return a.src_tile_ids[(int64_t)bd.tile * kDenseK + (tid & (kDenseK - 1))]; };
 
     for (int pass = 0; pass < n_pass; ++pass) {
-        const int col = (pass * 4 + wave) * 128 + oct * 8;  // first feature of this lane's octet
+        const int col = (pass * kSlices + slice) * 128 + oct * 8;  // first feature of this lane's octet
         const bool active = col < a.F;                       // F is a multiple of 128: a wavefront's slice is all there or not at all
         // a row fragment's address is the (wave-uniform) base of X plus a 32-bit byte offset: the launcher checks that X
         // is smaller than 4 GiB, and eight 64-bit addresses per lane would not fit the register budget of this kernel
@@ -119,9 +129,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const u32x4*>(xbase + ((uint32_t)id[j] * ldb + colb));
         };
 
-        f32x4 acc[4][8];
+        f32x4 acc[MT][8];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int f = 0; f < 8; ++f) acc[mt][f] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -170,31 +180,56 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             id_reg = id_of(bd3);                          // ids of block b + 3
             const Bounds bd4 = bounds_of(b + 4);
             clear(old);                                   // (read for the last time in the previous block)
-            if (active) {
-                // the high parts of the weights, then the low parts, with the same B operands formed twice: byte permutes
-                // are cheaper than the 16 registers that keeping both parts of A (or the operands) would cost
+            // the B operands of feature pair (2p, 2p + 1) of the octet: dword p of every row fragment
+            auto operands = [&](const int p, bf16x8& b0v, bf16x8& b1v) __attribute__((always_inline)) {
+                u32x4 blo, bhi;
 #pragma unroll
-                for (int part = 0; part < 2; ++part) {
-                    if (part == 1 && !a.use_low) break;
-                    u32x4 av[4];
+                for (int q = 0; q < 4; ++q) {
+                    blo[q] = __builtin_amdgcn_perm(xc[2 * q + 1][p], xc[2 * q][p], kPermLow);
+                    bhi[q] = __builtin_amdgcn_perm(xc[2 * q + 1][p], xc[2 * q][p], kPermHigh);
+                }
+                b0v = __builtin_bit_cast(bf16x8, blo);
+                b1v = __builtin_bit_cast(bf16x8, bhi);
+            };
+            auto weights = [&](const int part, u32x4 (&av)[MT]) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) av[mt] = *reinterpret_cast<const u32x4*>(&lds[cur][part][(mt * 64 + lane) * 8]);
+                for (int mt = 0; mt < MT; ++mt) av[mt] = *reinterpret_cast<const u32x4*>(&lds[cur][part][((mt0 + mt) * 64 + lane) * 8]);
+            };
+            auto multiply = [&](const int p, const u32x4 (&av)[MT], const bf16x8 b0v, const bf16x8 b1v) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) {  // feature pair (2p, 2p + 1) of the octet: dword p of every row fragment
-                        u32x4 blo, bhi;
+                for (int mt = 0; mt < MT; ++mt) {
+                    const bf16x8 a8 = __builtin_bit_cast(bf16x8, av[mt]);
+                    acc[mt][2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b0v, acc[mt][2 * p], 0, 0, 0);
+                    acc[mt][2 * p + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b1v, acc[mt][2 * p + 1], 0, 0, 0);
+                }
+            };
+            if constexpr (MT == 4) {
+                if (active) {
+                    // the high parts of the weights, then the low parts, with the same B operands formed twice: byte permutes
+                    // are cheaper than the 16 registers that keeping both parts of A (or the operands) would cost
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            blo[q] = __builtin_amdgcn_perm(xc[2 * q + 1][p], xc[2 * q][p], kPermLow);
-                            bhi[q] = __builtin_amdgcn_perm(xc[2 * q + 1][p], xc[2 * q][p], kPermHigh);
-                        }
-                        const bf16x8 b0v = __builtin_bit_cast(bf16x8, blo), b1v = __builtin_bit_cast(bf16x8, bhi);
+                    for (int part = 0; part < 2; ++part) {
+                        if (part == 1 && !a.use_low) break;
+                        u32x4 av[MT];
+                        weights(part, av);
 #pragma unroll
-                        for (int mt = 0; mt < 4; ++mt) {
-                            const bf16x8 a8 = __builtin_bit_cast(bf16x8, av[mt]);
-                            acc[mt][2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b0v, acc[mt][2 * p], 0, 0, 0);
-                            acc[mt][2 * p + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, b1v, acc[mt][2 * p + 1], 0, 0, 0);
+                        for (int p = 0; p < 4; ++p) {
+                            bf16x8 b0v, b1v;
+                            operands(p, b0v, b1v);
+                            multiply(p, av, b0v, b1v);
                         }
                     }
+                }
+            } else if (active) {
+                u32x4 high[MT], low[MT];
+                weights(0, high);
+                if (a.use_low) weights(1, low);
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    bf16x8 b0v, b1v;
+                    operands(p, b0v, b1v);
+                    multiply(p, high, b0v, b1v);
+                    if (a.use_low) multiply(p, low, b0v, b1v);
                 }
             }
             if (copied) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's share of the copied operand has landed
@@ -210,10 +245,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // features col .. col + 7 (one per accumulator f): eight consecutive floats of that destination's partial row
         if (active) {
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int m = mt * 16 + kg * 4 + r;
+                    const int m = (mt0 + mt) * 16 + kg * 4 + r;
                     const int slot0 = a.tile_row_slot0[(int64_t)ch_tile * kDenseM + m];
                     if (slot0 < 0) continue;
                     float* p = a.partials + (int64_t)(slot0 + ch_cidx) * a.F + col;
@@ -259,7 +294,13 @@ hipError_t launch_dense_blocks(const DenseArgs& a, hipStream_t s)
     if (a.F <= 0 || a.F % 128 != 0 || a.ld % 8 != 0 || (reinterpret_cast<uintptr_t>(a.X) & 15u) || (reinterpret_cast<uintptr_t>(a.partials) & 15u) ||
         (reinterpret_cast<uintptr_t>(a.de_tiles) & 15u) || a.n_chunks > 0x7fffffffLL)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dense_blocks, dim3((unsigned)a.n_chunks), dim3(256), 0, s, a);
+    const dim3 grid((unsigned)a.n_chunks);
+    if (a.F <= 128)
+        hipLaunchKernelGGL(k_dense_blocks<1>, grid, dim3(256), 0, s, a);
+    else if (a.F <= 256)
+        hipLaunchKernelGGL(k_dense_blocks<2>, grid, dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_dense_blocks<4>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -142,3 +142,33 @@ def test_dense_blocks_in_the_bf16_backward_pass(scale, ef, sym, F, Fo, op, attac
         ctx.destroy()
     if op == "mul_weight":
         assert not torch.equal(results[0], results[1]), "the dense-block path was not taken in the backward pass"
+
+
+@pytest.mark.parametrize("F", [128, 256, 384, 512, 640])
+@pytest.mark.parametrize("op", ["mul_weight", "copy"])
+@pytest.mark.parametrize("chunk", [0, 2])
+def test_rows_of_every_number_of_slices(F, op, chunk):
+    """Wavefronts that own all, half or a quarter of a block's destinations (rows of more than 256, up to 256 and up to 128
+    features), with chunks of the default length and chunks of two blocks, a tile's last one shorter."""
+    import paper_1810_08403_amd as saga
+    g = _rmat(9, 40, True)
+    n = g.n
+    rng = np.random.default_rng(F)
+    t = lambda *shape: torch.as_tensor(rng.standard_normal(shape).astype(np.float32))
+    X, w = si.round_to_bf16(t(n, F)), t(g.nnz)
+    ref = oracle.layer(g.col_ptr.numpy(), g.row_idx.numpy(), X.numpy(), op, w.numpy() if op == "mul_weight" else None, agg="sum", W=None, act="none")
+    ctx = saga.Context(0)
+    for k, v in dict(dense_min_edges=8, dense_tile_gain=0, dense_chunk=chunk).items():
+        ctx.set_option(k, v)
+    h = ctx.graph_create_csc(n, g.col_ptr.cuda(), g.row_idx.cuda())
+    if op == "mul_weight":
+        h.set_edge_data(w.cuda())
+    Y = torch.full((n, F), float("nan"), device="cuda", dtype=torch.bfloat16)
+    A = torch.full((n, F), float("nan"), device="cuda")
+    ctx.set_profiling(True)
+    ctx.layer_forward(h, X.cuda().to(torch.bfloat16), Y, edge_op=op, agg="sum", accum_out=A)
+    torch.cuda.synchronize()
+    assert ctx.get_timings()["n_dense_blocks"] > 0
+    # fp32 sums of exact bf16 products with two-part bf16 weights (2^-17 relative)
+    assert_sum_close(A.cpu().numpy(), ref["A"], ref["A_abs"], 2e-5, f"F={F} {op} chunk={chunk}")
+    h.destroy()
