@@ -348,7 +348,7 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
     out->blk_tile.assign((size_t)nb, -1);
     std::vector<int64_t> blk_t0((size_t)nb + 1, 0);  // offsets of the finished operands' edges in dt_addr / dt_edge
     int64_t nde = 0, ndt = 0, n_tiles = 0;
-    const int64_t ch = std::max<int64_t>(1, hp.max_chunk_blocks);
+    const int64_t ch = hp.max_chunk_blocks > 0 ? hp.max_chunk_blocks : std::min<int64_t>(kDenseChunkMax, kDenseChunkMin + nb / kDenseResident);
     for (int64_t t = 0; t < n_dt; ++t) {
         const TilePlan& p = tp[(size_t)t];
         const int64_t b0 = tile_b0[(size_t)t], k = (int64_t)p.st.size();
@@ -366,7 +366,7 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
         if (k == 0) continue;
         const int64_t n_chunks = (k + ch - 1) / ch;
         for (int64_t c = 0; c < n_chunks; ++c)
-            out->chunks.push_back(DenseChunk{(int32_t)t, (int32_t)(b0 + c * ch), (int32_t)std::min(b0 + k, b0 + (c + 1) * ch), (int32_t)c});
+            out->chunks.push_back(DenseChunk{(int32_t)t, (int32_t)(b0 + k * c / n_chunks), (int32_t)(b0 + k * (c + 1) / n_chunks), (int32_t)c});
         for (int m = 0; m < kDenseM; ++m) {
             const int32_t v = out->dst_order[(size_t)t * kDenseM + m];
             if (v >= 0) out->extra_slots[(size_t)v] = (int32_t)n_chunks;

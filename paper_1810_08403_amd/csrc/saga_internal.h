@@ -148,8 +148,19 @@ struct HybridParams {
     // (256 features) 3.43 ms at 192, 3.51 at 208, 3.66 at 256.
     int64_t min_block_edges = 200;
     int64_t min_tile_gain = 512;    // edges beyond min_block_edges, summed over a destination tile's blocks, that pay for its partial rows
-    int32_t max_chunk_blocks = 128; // blocks of one destination tile worked by one workgroup (one partial row per destination each)
+    int32_t max_chunk_blocks = 0;   // blocks of one destination tile worked by one workgroup (one partial row per destination each); 0: by the rule below
 };
+// A workgroup takes its blocks one after the other, some 1.4 us each, and the chip holds two workgroups per compute unit: with few
+// blocks the longest chunk is the launch. Against that, a chunk costs what five more blocks do (its first round trips, 64 partial
+// rows that k_combine reads again). Rule: what is one chunk's share if all workgroups are to run at once, and five.
+// Measured (dense kernel, then a whole layer forward and backward, us; 256 bf16 features, R-MAT):
+//   193 blocks      chunks of 16  24, 143   8  17, 131   4  13, 126   2  12, 126
+//   3,747           128 180, 977   64 104, 815   32 60, 734   16 35, 702   12 33, 700   8 37, 718
+//   12,877          128 187, 1357  64 111, 1192  48 93, 1152  32 64, 1120  24 77, 1145
+//   21,621          128 188, 2669  64 111, 2521  48 95, 2488  32 115, 2534
+//   66,159          128 220, 3375  64 238, 3430
+//   148,828 (512 features, forward)  128 643, 4171  64 685, 4246  32 831, 4445
+constexpr int kDenseChunkMin = 5, kDenseChunkMax = 128, kDenseResident = 2 * 256;
 // A block's weights reach the kernel in one of two forms: as a list of (cell, weight) pairs that the workgroup scatters
 // into a cleared LDS operand (blocks of up to kDenseListMax edges: one pair per thread), or, for fuller blocks, as the
 // finished 64 x 32 operand itself (two bf16 parts, 8 KiB), which is copied into LDS as it is.
