@@ -212,7 +212,7 @@ static saga_status param_grad(saga_ctx* ctx, const void* P, int64_t ldp, int32_t
     const size_t one = sizeof(float) * (size_t)FP * FQ;
     const int64_t room = grow || one == 0 ? 1024 : (int64_t)(ctx->ws_splitk.bytes / one);
     if (room < 1) return ctx->fail(SAGA_ERR_INTERNAL, "split workspace too small");
-    gemm_tn_plan(n, FP, FQ, &ta.rows_per_split, &ta.n_split, room);
+    gemm_tn_plan(n, FP, FQ, &ta.rows_per_split, &ta.n_split, room, grow && ctx->budget == 0);
     if (grow)
         if (saga_status st = ctx->dev_alloc(&ctx->ws_splitk, one * (size_t)ta.n_split)) return st;
     ta.part = static_cast<float*>(ctx->ws_splitk.p);

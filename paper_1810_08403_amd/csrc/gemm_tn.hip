@@ -78,8 +78,8 @@ __device__ __forceinline__ void operands(const uint16_t (&v)[8], uint32_t flip, 
 // through LDS) -> now, product + reduction of the partials: 262,144 x 64 x 64 56 + 8 -> 29 + 7 us; 131,072 x 602 x 41
 // 158 + 11 -> 118 + 6; 500 x 16 58 + 9 -> 47 + 8; 1,048,576 x 128 x 128 315 -> 288; as backward calls without dX: 262,144 x 128 x
 // 128 189 -> 133, 131,072 x 256 x 256 245 -> 190, 512 x 256 371 -> 314, but 65,536 x 640 x 300 348 -> 377, 640 x 640 542 ->
-// 618: every tile of C splits its own operands again. The small products in accumulators of their own through all
-// steps: the same times.
+// 618: every tile of C splits its own operands again (now 488 for 131,072 x 640 x 300, 430 for 65,536 x 640 x 640: see gemm_tn_plan).
+// The small products in accumulators of their own through all steps: the same times.
 template <typename TP, typename TQ, int MTF, int NTF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_gemm_tn(const GemmTnArgs a, const int wm_count, const int tiles_m,
                                                                                              const int tiles_n)
