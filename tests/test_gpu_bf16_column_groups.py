@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
                                              (65505, 65, 96, False),      # three, a last row tile of one row
                                              (65600, 128, 127, True),     # four, two operand pairs
                                              (70001, 301, 300, False),    # two groups of five, odd widths
-                                             (65536, 400, 129, False),    # the largest K whose five tiles fit
-                                             (65536, 449, 129, False),    # past it: two tiles
+                                             (65536, 384, 129, False),    # the largest K whose five tiles fit
+                                             (65536, 385, 129, False),    # past it: two tiles
                                              (65504, 300, 130, False)])   # one row tile too few
 def test_columns_together_and_apart(n, K, N, with_self):
     import paper_1810_08403_amd as saga
