@@ -415,7 +415,9 @@ saga_status saga_get_timings(saga_ctx* ctx, saga_timings* out); /* synchronises 
  *   "dense_min_edges"  edges from which a block goes to the matrix cores (0 = default 200; at most 2048)
  *   "dense_tile_gain"  edges beyond dense_min_edges, summed over the blocks of a destination tile, from which the tile
  *                uses the dense path at all (it costs a partial row per destination; -1 = default 512)
- *   "dense_chunk"  blocks of one destination tile worked by one workgroup (0, the default: 5 to 128, by their number)
+ *   "dense_chunk"  blocks of one destination tile worked by one workgroup (0, the default: 5 to 128, by their number; twice,
+ *                four times, ... as many, up to 128, where the partial rows of the shorter chunks would not fit the scratch
+ *                memory of saga_layer_forward_noalloc and those of the longer ones do; 128 in a context with a budget)
  *   "dense_overlap"  0/1 (default 0): 1 runs the dense kernel on a second stream beside the sparse kernel (measured:
  *                no gain, the two fill the chip one after the other)
  *   "bwd_tile_rows"  streamed backward calls: rows per tile of the backward-ApplyVertex pass (default 0 = as

@@ -606,23 +606,24 @@ saga_status resident_backward_bf16(saga_ctx* ctx, saga_graph* g, const saga_tens
         // matrix cores where the rows allow it, and the sparse kernel keeps the remainder.
         saga_graph* view = g->tr;
         bool hybrid = hybrid_applies(ctx, width, ld, src);
+        const HybridCut* cut = nullptr;
         if (hybrid) {
-            if (saga_status e = ensure_hybrid(ctx, view, (int64_t)width * 2, width)) return e;
+            if (saga_status e = ensure_hybrid(ctx, view, (int64_t)width * 2, width, -1, &cut)) return e;
             hybrid = view->hyb.usable;
         }
         if (!hybrid)
             if (saga_status e = ensure_work_list(ctx, view, (int64_t)width * 2, width)) return e;
         const HybridDevice& h = view->hyb;
-        ga.items = static_cast<const WorkItem*>(hybrid ? h.items.p : view->d_items.p);
-        ga.n_items = hybrid ? h.n_items : view->n_items;
-        ga.n_team = hybrid ? h.n_team : view->n_team;
+        ga.items = static_cast<const WorkItem*>(hybrid ? cut->items.p : view->d_items.p);
+        ga.n_items = hybrid ? cut->n_items : view->n_items;
+        ga.n_team = hybrid ? cut->n_team : view->n_team;
         ga.light = ga.items + ga.n_items;
-        ga.n_light = hybrid ? h.n_light : view->n_light;
-        ga.light_edges = hybrid ? h.light_edges : view->light_edges;
+        ga.n_light = hybrid ? cut->n_light : view->n_light;
+        ga.light_edges = hybrid ? cut->light_edges : view->light_edges;
         ga.n_src = view->n;
         ga.n_edges = hybrid ? h.n_rem_edges : view->nnz;
         ga.row_idx = static_cast<const int32_t*>(hybrid ? h.rem_row_idx.p : view->d_row_idx.p);
-        const int64_t n_slots = hybrid ? h.n_slots : view->n_slots, n_heavy = hybrid ? h.n_heavy : view->n_heavy;
+        const int64_t n_slots = hybrid ? cut->n_slots : view->n_slots, n_heavy = hybrid ? cut->n_heavy : view->n_heavy;
         ga.dtype = SAGA_BF16;
         ga.agg = SAGA_AGG_SUM;
         ga.xcd_remap = ctx->opt_xcd_remap;
@@ -633,13 +634,13 @@ saga_status resident_backward_bf16(saga_ctx* ctx, saga_graph* g, const saga_tens
         }
         bool forked = false;
         if (hybrid)  // the weights in the edge order by source: the view's own copy of attached data, or this call's permuted ones
-            if (saga_status e = hybrid_dense_launch(ctx, view, &ga, w_t != nullptr, w_t, w_t != nullptr && !ep->edge_weight, nullptr, &forked))
+            if (saga_status e = hybrid_dense_launch(ctx, view, *cut, &ga, w_t != nullptr, w_t, w_t != nullptr && !ep->edge_weight, nullptr, &forked))
                 return e;
         HIP_TRY(ctx, launch_gather(ga, s));
         if (forked) HIP_TRY(ctx, hipStreamWaitEvent(s, ctx->ev_join, 0));
         if (n_heavy > 0) {
             CombineArgs ca{};
-            ca.heavy = static_cast<const HeavyVertex*>(hybrid ? h.heavy.p : view->d_heavy.p);
+            ca.heavy = static_cast<const HeavyVertex*>(hybrid ? cut->heavy.p : view->d_heavy.p);
             ca.n_heavy = n_heavy;
             ca.partials = ga.partials;
             ca.F = width;

@@ -295,7 +295,6 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
         out->dst_order[(size_t)r] = dorder[(size_t)r];
         out->src_tile_ids[(size_t)r] = sorder[(size_t)r];
     }
-    out->extra_slots.assign((size_t)n, 0);
 
     // pass 1: per destination tile, the dense source tiles (ascending) and their edge counts
     struct TilePlan {
@@ -339,7 +338,8 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
     if (failed) throw std::bad_alloc();
 
     // blocks, chunks and offsets
-    std::vector<int64_t> tile_b0((size_t)n_dt + 1, 0);
+    std::vector<int64_t>& tile_b0 = out->tile_b0;
+    tile_b0.assign((size_t)n_dt + 1, 0);
     for (int64_t t = 0; t < n_dt; ++t) tile_b0[(size_t)t + 1] = tile_b0[(size_t)t] + (int64_t)tp[(size_t)t].st.size();
     const int64_t nb = tile_b0[(size_t)n_dt];
     if (nb > 0x7fffffffLL - 1) throw std::bad_alloc();
@@ -348,7 +348,6 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
     out->blk_tile.assign((size_t)nb, -1);
     std::vector<int64_t> blk_t0((size_t)nb + 1, 0);  // offsets of the finished operands' edges in dt_addr / dt_edge
     int64_t nde = 0, ndt = 0, n_tiles = 0;
-    const int64_t ch = hp.max_chunk_blocks > 0 ? hp.max_chunk_blocks : std::min<int64_t>(kDenseChunkMax, kDenseChunkMin + nb / kDenseResident);
     for (int64_t t = 0; t < n_dt; ++t) {
         const TilePlan& p = tp[(size_t)t];
         const int64_t b0 = tile_b0[(size_t)t], k = (int64_t)p.st.size();
@@ -363,15 +362,8 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
                 nde += p.cnt[(size_t)i];
             }
         }
-        if (k == 0) continue;
-        const int64_t n_chunks = (k + ch - 1) / ch;
-        for (int64_t c = 0; c < n_chunks; ++c)
-            out->chunks.push_back(DenseChunk{(int32_t)t, (int32_t)(b0 + k * c / n_chunks), (int32_t)(b0 + k * (c + 1) / n_chunks), (int32_t)c});
-        for (int m = 0; m < kDenseM; ++m) {
-            const int32_t v = out->dst_order[(size_t)t * kDenseM + m];
-            if (v >= 0) out->extra_slots[(size_t)v] = (int32_t)n_chunks;
-        }
     }
+    divide_dense_blocks(out, n, hp.max_chunk_blocks > 0 ? hp.max_chunk_blocks : dense_chunk_length(nb));
     if (nde > 0x7fffffffLL - 1 || ndt > 0x7fffffffLL - 1 || n_tiles * kDenseTileElems > 0x7fffffffLL - 1) throw std::bad_alloc();
     out->blk_e0[(size_t)nb] = (int32_t)nde;
     blk_t0[(size_t)nb] = ndt;
@@ -452,6 +444,26 @@ void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n
     });
 }
 
+int64_t divide_dense_blocks(HybridPlan* plan, int64_t n, int64_t length)
+{
+    plan->chunks.clear();
+    plan->extra_slots.assign((size_t)n, 0);
+    int64_t rows = 0;
+    for (int64_t t = 0; t < plan->n_dst_tiles; ++t) {
+        const int64_t b0 = plan->tile_b0[(size_t)t], k = plan->tile_b0[(size_t)t + 1] - b0, n_chunks = (k + length - 1) / length;
+        if (k == 0) continue;
+        for (int64_t c = 0; c < n_chunks; ++c)
+            plan->chunks.push_back(DenseChunk{(int32_t)t, (int32_t)(b0 + k * c / n_chunks), (int32_t)(b0 + k * (c + 1) / n_chunks), (int32_t)c});
+        for (int m = 0; m < kDenseM; ++m) {
+            const int32_t v = plan->dst_order[(size_t)t * kDenseM + m];
+            if (v < 0) continue;
+            plan->extra_slots[(size_t)v] = (int32_t)n_chunks;
+            rows += n_chunks;
+        }
+    }
+    return rows;
+}
+
 namespace {
 
 const char* kVersion = "saga-mi355x 0.1 (gfx950)";
@@ -500,6 +512,15 @@ static PackBlock columns_of(PackBlock b, int32_t c0, int32_t c1, size_t elem)
     return b;
 }
 
+// The matrices as the scratch memory counts them: whole 128 columns of whole 64 bytes of k. A 32-column tile packs into
+// less, so one always fits.
+static size_t counted_weights(int64_t cols, int32_t K, int32_t K2, int32_t dtype)
+{
+    const int64_t k16 = dtype == SAGA_F32 ? 16 : 64;
+    const int64_t k_counted = ((int64_t)K + k16 - 1) / k16 * k16 + ((int64_t)K2 + k16 - 1) / k16 * k16;
+    return (size_t)((cols + 127) / 128 * 128 * k_counted) * (dtype == SAGA_F32 ? 4 : 2);
+}
+
 // Products over columns of one packed matrix of N columns: product i over columns [col0[i], col0[i] + g[i].N), col0 a multiple
 // of 32. All at once where the packed weights fit; in a call that must not allocate they may not (three bf16 parts a value,
 // widths rounded up to 32, against the fp32 matrices that its scratch memory is counted by): then some 32-column tiles at a
@@ -510,17 +531,13 @@ static saga_status multiply(saga_ctx* ctx, const PackBlock* blocks, int n_blocks
     hipStream_t s = ctx->stream;
     const int n_ks = packed_k_steps(K, dtype) + (K2 > 0 ? packed_k_steps(K2, dtype) : 0);
     const size_t es = dtype == SAGA_F32 ? 4 : 2;
-    // the matrices as the scratch memory counts them: whole 128 columns of whole 64 bytes of k. A 32-column tile packs into
-    // less, so one always fits.
     int64_t cols = 0;
     for (int i = 0; i < n_blocks; ++i) cols += blocks[i].k0 == 0 ? blocks[i].n1 - blocks[i].n0 : 0;
-    const int64_t k16 = dtype == SAGA_F32 ? 16 : 64;
-    const int64_t k_counted = ((int64_t)K + k16 - 1) / k16 * k16 + ((int64_t)K2 + k16 - 1) / k16 * k16;
     const size_t tile = packed_weight_bytes(32, n_ks, dtype);
     if (tile == 0 || N <= 0) HIP_TRY(ctx, hipErrorInvalidValue);  // an operand without columns
     void* p;
     size_t room;
-    if (saga_status st = ctx->weights_alloc(&ctx->ws_bt, packed_weight_bytes(N, n_ks, dtype), (size_t)((cols + 127) / 128 * 128 * k_counted) * es, &p, &room))
+    if (saga_status st = ctx->weights_alloc(&ctx->ws_bt, packed_weight_bytes(N, n_ks, dtype), counted_weights(cols, K, K2, dtype), &p, &room))
         return st;
     if (room < tile) return ctx->fail(SAGA_ERR_INTERNAL, "no room for packed weights");
     const int32_t step = (int32_t)std::min<int64_t>((N + 31) / 32, (int64_t)(room / tile)) * 32;
@@ -702,10 +719,11 @@ saga_status ensure_work_list(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, in
 
 void hybrid_free(saga_ctx* ctx, HybridDevice* h)
 {
-    for (DevBuf* b : {&h->chunks, &h->blk_src_tile, &h->blk_e0, &h->blk_tile, &h->de_pos, &h->de_edge, &h->de_w, &h->dt_addr, &h->dt_edge, &h->de_tiles,
-                      &h->src_tile_ids, &h->tile_row_slot0,
-                      &h->rem_row_idx, &h->rem_edge, &h->rem_w, &h->items, &h->heavy})
+    for (DevBuf* b : {&h->blk_src_tile, &h->blk_e0, &h->blk_tile, &h->de_pos, &h->de_edge, &h->de_w, &h->dt_addr, &h->dt_edge, &h->de_tiles,
+                      &h->src_tile_ids, &h->rem_row_idx, &h->rem_edge, &h->rem_w})
         ctx->dev_free(b);
+    for (HybridCut& c : h->cuts)
+        for (DevBuf* b : {&c.chunks, &c.tile_row_slot0, &c.items, &c.heavy}) ctx->dev_free(b);
     *h = HybridDevice{};
 }
 
@@ -718,10 +736,23 @@ static HybridParams hybrid_params(const saga_ctx* ctx)
     return hp;
 }
 
+static size_t whole256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+// Which of the plan's chunk lengths a layer takes (see kDenseChunkMin)
+static int64_t chunk_length_for(const saga_ctx* ctx, const std::vector<HybridDevice::Length>& lengths, int32_t width, int64_t beside)
+{
+    if (ctx->budget > 0) return lengths.back().length;
+    if (beside >= 0)
+        for (const HybridDevice::Length& l : lengths)
+            if ((size_t)beside + whole256(sizeof(float) * (size_t)l.n_slots * width) <= kScratchBytes) return l.length;
+    return lengths.front().length;
+}
+
 // The dense-block form of a resident graph for rows of `row_bytes` (the remainder's work list depends on the row width
 // like any other): built on the host at the first call that can use it, kept in the graph handle.
-saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32_t width)
+saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32_t width, int64_t beside, const HybridCut** cut)
 {
+    *cut = nullptr;
     HybridDevice& h = g->hyb;
     // The remainder's piece size goes by the bytes of a source row, not by the narrow-row rule of the general list: its
     // columns have lost their heavy blocks. Rows of 256 and 512 bytes keep 64 edges per piece (backward pass of the R-MAT
@@ -729,7 +760,6 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     // fewer (forward layer of the same workload, 512 bf16 features, bands of 1 MiB: 4.11 ms at 48, 4.21 at 40, 4.23 at 56
     // and 64, 4.32 at 32, 4.73 at 80: longer pieces reach over more bands of source rows, shorter ones cost k_combine more
     // than the sparse kernel gains). Columns are cut from 128 edges on either way.
-    (void)width;
     WorkListParams p = work_list_params(ctx, row_bytes, 0);
     // Rows of 1 KiB also take bands of 2 MiB of them instead of 1 MiB, and with those pieces of 40 edges: what is left of a
     // column after its well-filled blocks have gone has few edges per band, and a piece then ends at the next band
@@ -741,15 +771,27 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     p.long_edges = long_edges(p);
     const HybridParams hp = hybrid_params(ctx);
     auto same = same_params;
-    if (h.built && same(p, h.list_params) && hp.min_block_edges == h.hp.min_block_edges && hp.min_tile_gain == h.hp.min_tile_gain &&
-        hp.max_chunk_blocks == h.hp.max_chunk_blocks)
-        return SAGA_OK;
+    const bool there = h.built && same(p, h.list_params) && hp.min_block_edges == h.hp.min_block_edges &&
+                       hp.min_tile_gain == h.hp.min_tile_gain && hp.max_chunk_blocks == h.hp.max_chunk_blocks;
+    if (there) {
+        if (!h.usable) return SAGA_OK;
+        const int64_t length = chunk_length_for(ctx, h.lengths, width, beside);
+        for (const HybridCut& c : h.cuts)
+            if (c.length == length) *cut = &c;
+        if (*cut) return SAGA_OK;
+        if (ctx->arena_active)  // one that another layer made (its vertex stage had other widths) will do
+            for (const HybridCut& c : h.cuts)
+                if ((size_t)beside + whole256(sizeof(float) * (size_t)c.n_slots * width) <= kScratchBytes && (!*cut || c.length < (*cut)->length)) *cut = &c;
+        if (*cut) return SAGA_OK;
+    }
     if (ctx->arena_active)
         return ctx->fail(SAGA_ERR_UNSUPPORTED, "no dense-block plan for this row width yet: call saga_layer_forward once with the same shapes first");
-    hybrid_free(ctx, &h);
-    h.list_params = p;
-    h.hp = hp;
-    h.built = true;
+    if (!there) {
+        hybrid_free(ctx, &h);
+        h.list_params = p;
+        h.hp = hp;
+        h.built = true;
+    }
     if (g->nnz == 0 || g->n >= (1LL << 30)) return SAGA_OK;
     std::vector<int32_t> h_row((size_t)g->nnz);
     HIP_TRY(ctx, hipMemcpyAsync(h_row.data(), g->d_row_idx.p, sizeof(int32_t) * (size_t)g->nnz, hipMemcpyDeviceToHost, ctx->stream));
@@ -759,6 +801,24 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     if (plan.chunks.empty()) return SAGA_OK;  // nothing dense enough: the sparse kernel takes the whole graph
     WorkList wl;
     build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
+    if (!there) {
+        // what longer chunks would take: the same pieces of the remainder, fewer rows of chunks
+        const int64_t first = hp.max_chunk_blocks > 0 ? hp.max_chunk_blocks : dense_chunk_length((int64_t)plan.blk_src_tile.size());
+        int64_t rows = 0;
+        for (int32_t k : plan.extra_slots) rows += k;
+        h.lengths.push_back({first, wl.n_slots});
+        for (int64_t l = first; hp.max_chunk_blocks == 0 && l < kDenseChunkMax;) {
+            l = std::min<int64_t>(2 * l, kDenseChunkMax);
+            h.lengths.push_back({l, wl.n_slots - rows + divide_dense_blocks(&plan, g->n, l)});
+        }
+    }
+    HybridCut c;
+    c.length = chunk_length_for(ctx, h.lengths, width, beside);
+    divide_dense_blocks(&plan, g->n, c.length);
+    if (c.length != h.lengths.front().length) {
+        wl = WorkList{};
+        build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
+    }
     // first partial row of every destination that has dense blocks, by destination rank
     std::vector<int32_t> slot0_of((size_t)g->n, -1);
     for (const HeavyVertex& hv : wl.heavy) slot0_of[(size_t)hv.v] = hv.slot0;
@@ -775,8 +835,29 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
         return SAGA_OK;
     };
     saga_status st;
-    if ((st = up(&h.chunks, plan.chunks.data(), sizeof(DenseChunk) * plan.chunks.size())) ||
-        (st = up(&h.blk_src_tile, plan.blk_src_tile.data(), 4 * plan.blk_src_tile.size())) ||
+    if ((st = up(&c.chunks, plan.chunks.data(), sizeof(DenseChunk) * plan.chunks.size())) ||
+        (st = up(&c.tile_row_slot0, tile_row_slot0.data(), 4 * tile_row_slot0.size())) ||
+        (st = up(&c.items, wl.items.data(), sizeof(WorkItem) * wl.items.size())) ||
+        (st = up(&c.heavy, wl.heavy.data(), sizeof(HeavyVertex) * wl.heavy.size()))) {
+        (void)hipStreamSynchronize(ctx->stream);
+        for (DevBuf* b : {&c.chunks, &c.tile_row_slot0, &c.items, &c.heavy}) ctx->dev_free(b);
+        if (!there) hybrid_free(ctx, &h);
+        return st;
+    }
+    c.n_chunks = (int64_t)plan.chunks.size();
+    c.n_items = n_items;
+    c.n_team = wl.n_team;
+    c.n_light = (int64_t)wl.light.size();
+    c.light_edges = wl.light_edges;
+    c.n_heavy = (int64_t)wl.heavy.size();
+    c.n_slots = wl.n_slots;
+    h.cuts.push_back(c);
+    *cut = &h.cuts.back();
+    if (there) {
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host vectors go out of scope below
+        return SAGA_OK;
+    }
+    if ((st = up(&h.blk_src_tile, plan.blk_src_tile.data(), 4 * plan.blk_src_tile.size())) ||
         (st = up(&h.blk_e0, plan.blk_e0.data(), 4 * plan.blk_e0.size())) ||
         (st = up(&h.blk_tile, plan.blk_tile.data(), 4 * plan.blk_tile.size())) ||
         (st = up(&h.de_pos, plan.de_pos.data(), 2 * plan.de_pos.size())) ||
@@ -785,11 +866,8 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
         (st = up(&h.dt_edge, plan.dt_edge.data(), 4 * plan.dt_edge.size())) ||
         (st = ctx->dev_alloc(&h.de_tiles, std::max<size_t>(2 * (size_t)plan.n_tiles * kDenseTileElems, 16))) ||
         (st = up(&h.src_tile_ids, plan.src_tile_ids.data(), 4 * plan.src_tile_ids.size())) ||
-        (st = up(&h.tile_row_slot0, tile_row_slot0.data(), 4 * tile_row_slot0.size())) ||
         (st = up(&h.rem_row_idx, plan.rem_row_idx.data(), 4 * plan.rem_row_idx.size())) ||
         (st = up(&h.rem_edge, plan.rem_edge.data(), 4 * plan.rem_edge.size())) ||
-        (st = up(&h.items, wl.items.data(), sizeof(WorkItem) * wl.items.size())) ||
-        (st = up(&h.heavy, wl.heavy.data(), sizeof(HeavyVertex) * wl.heavy.size())) ||
         (st = ctx->dev_alloc(&h.de_w, std::max<size_t>(4 * plan.de_pos.size(), 16))) ||
         (st = ctx->dev_alloc(&h.rem_w, std::max<size_t>(4 * plan.rem_row_idx.size(), 16)))) {
         (void)hipStreamSynchronize(ctx->stream);
@@ -802,16 +880,9 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     h.n_list_edges = (int64_t)plan.de_pos.size();
     h.n_tile_edges = (int64_t)plan.dt_addr.size();
     h.n_tiles = plan.n_tiles;
-    h.n_chunks = (int64_t)plan.chunks.size();
     h.n_blocks = (int64_t)plan.blk_src_tile.size();
     h.n_dense_edges = plan.n_dense_edges;
     h.n_rem_edges = (int64_t)plan.rem_row_idx.size();
-    h.n_items = n_items;
-    h.n_team = wl.n_team;
-    h.n_light = (int64_t)wl.light.size();
-    h.light_edges = wl.light_edges;
-    h.n_heavy = (int64_t)wl.heavy.size();
-    h.n_slots = wl.n_slots;
     h.weights_state = 0;
     h.usable = true;
     return SAGA_OK;
@@ -829,7 +900,7 @@ bool hybrid_applies(const saga_ctx* ctx, int32_t F, int64_t ld, const void* rows
 // remainder's edge order) are packed here: attached data (`w_attached`: w_src is the view's own copy, which
 // saga_graph_set_edge_data invalidates) once, data passed with the call every call, COPY packs ones once.
 // *forked: the kernel went to the context's second stream and the caller waits for ev_join after its own launch.
-saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, GatherArgs* ga, bool weighted, const float* w_src, bool w_attached,
+saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, const HybridCut& cut, GatherArgs* ga, bool weighted, const float* w_src, bool w_attached,
                                 saga_ctx::EventSet* es, bool* forked)
 {
     hipStream_t s = ctx->stream;
@@ -854,8 +925,8 @@ saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, GatherArgs* ga,
     }
     if (weighted) ga->edge_w = static_cast<const float*>(h.rem_w.p);
     DenseArgs da{};
-    da.chunks = static_cast<const DenseChunk*>(h.chunks.p);
-    da.n_chunks = h.n_chunks;
+    da.chunks = static_cast<const DenseChunk*>(cut.chunks.p);
+    da.n_chunks = cut.n_chunks;
     da.blk_src_tile = static_cast<const int32_t*>(h.blk_src_tile.p);
     da.blk_e0 = static_cast<const int32_t*>(h.blk_e0.p);
     da.blk_tile = static_cast<const int32_t*>(h.blk_tile.p);
@@ -863,7 +934,7 @@ saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, GatherArgs* ga,
     da.de_pos = static_cast<const uint16_t*>(h.de_pos.p);
     da.de_w = static_cast<const uint32_t*>(h.de_w.p);
     da.src_tile_ids = static_cast<const int32_t*>(h.src_tile_ids.p);
-    da.tile_row_slot0 = static_cast<const int32_t*>(h.tile_row_slot0.p);
+    da.tile_row_slot0 = static_cast<const int32_t*>(cut.tile_row_slot0.p);
     da.X = static_cast<const uint16_t*>(ga->src);
     da.ld = ga->ld_src;
     da.F = ga->F;
@@ -1167,7 +1238,7 @@ saga_status saga_plan_dense_blocks(int64_t n, const int64_t* col_ptr, const int3
                                    int64_t block_capacity, int32_t* remainder_row_idx_out, int32_t* remainder_edge_out, int64_t* remainder_col_ptr_out,
                                    int32_t* dense_edge_out, int32_t* dense_block_of_edge_out)
 {
-    if (n < 0 || !col_ptr || !counts || min_block_edges < 1 || min_tile_gain < 0 || max_chunk_blocks < 1) return SAGA_ERR_INVALID_ARG;
+    if (n < 0 || !col_ptr || !counts || min_block_edges < 1 || min_tile_gain < 0 || max_chunk_blocks < 0) return SAGA_ERR_INVALID_ARG;
     if (col_ptr[n] > 0 && !row_idx) return SAGA_ERR_INVALID_ARG;
     try {
         HybridPlan plan;
@@ -1676,8 +1747,13 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     const int64_t ld_g = tf ? (int64_t)Fo_tf : X->ld;
     bool hybrid = bf16 && agg == SAGA_AGG_SUM && (ep->op == SAGA_EDGE_COPY || ep->op == SAGA_EDGE_MUL_WEIGHT) &&
                   hybrid_applies(ctx, Fg, ld_g, tf ? nullptr : X->data);
+    const HybridCut* cut = nullptr;
     if (hybrid) {
-        if (saga_status st = ensure_hybrid(ctx, g, row_bytes, Fg)) return st;
+        // the rows between the propagation and the product (or before it) and the weights
+        const int64_t beside = has_w ? (int64_t)(whole256(sizeof(uint16_t) * (size_t)n * Fg) +
+                                                 whole256(counted_weights(vp->W->cols, F, vp->W_self ? F : 0, SAGA_BF16)))
+                                     : 0;
+        if (saga_status st = ensure_hybrid(ctx, g, row_bytes, Fg, beside, &cut)) return st;
         hybrid = g->hyb.usable;
     }
     if (!hybrid)
@@ -1702,18 +1778,18 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     }
 
     GatherArgs ga{};
-    ga.items = static_cast<const WorkItem*>(hybrid ? g->hyb.items.p : g->d_items.p);
-    ga.n_items = hybrid ? g->hyb.n_items : g->n_items;
-    ga.n_team = hybrid ? g->hyb.n_team : g->n_team;
+    ga.items = static_cast<const WorkItem*>(hybrid ? cut->items.p : g->d_items.p);
+    ga.n_items = hybrid ? cut->n_items : g->n_items;
+    ga.n_team = hybrid ? cut->n_team : g->n_team;
     ga.light = ga.items + ga.n_items;
-    ga.n_light = hybrid ? g->hyb.n_light : g->n_light;
-    ga.light_edges = hybrid ? g->hyb.light_edges : g->light_edges;
+    ga.n_light = hybrid ? cut->n_light : g->n_light;
+    ga.light_edges = hybrid ? cut->light_edges : g->light_edges;
     ga.n_src = n;
     ga.n_edges = hybrid ? g->hyb.n_rem_edges : g->nnz;
     ga.row_idx = static_cast<const int32_t*>(hybrid ? g->hyb.rem_row_idx.p : g->d_row_idx.p);
-    const int64_t n_slots = hybrid ? g->hyb.n_slots : g->n_slots;
-    const int64_t n_heavy = hybrid ? g->hyb.n_heavy : g->n_heavy;
-    const HeavyVertex* heavy = static_cast<const HeavyVertex*>(hybrid ? g->hyb.heavy.p : g->d_heavy.p);
+    const int64_t n_slots = hybrid ? cut->n_slots : g->n_slots;
+    const int64_t n_heavy = hybrid ? cut->n_heavy : g->n_heavy;
+    const HeavyVertex* heavy = static_cast<const HeavyVertex*>(hybrid ? cut->heavy.p : g->d_heavy.p);
     ga.F = Fm;
     ga.agg = agg;
     ga.op = pool ? (int32_t)SAGA_EDGE_COPY : ep->op;
@@ -1810,7 +1886,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     if (hybrid) {
         const bool weighted = ep->op == SAGA_EDGE_MUL_WEIGHT;
         const float* w_src = !weighted ? nullptr : (ep->edge_weight ? ep->edge_weight : static_cast<const float*>(g->d_edge_data.p));
-        if (saga_status st = hybrid_dense_launch(ctx, g, &ga, weighted, w_src, weighted && !ep->edge_weight, es, &dense_forked)) return st;
+        if (saga_status st = hybrid_dense_launch(ctx, g, *cut, &ga, weighted, w_src, weighted && !ep->edge_weight, es, &dense_forked)) return st;
     }
     if (!ctx->opt_fused) {
         // the baseline of Section 6.2: the stages one by one through a materialised per-edge tensor, which the fused
@@ -1892,7 +1968,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         HIP_TRY(ctx, hipEventRecord(es->ev[4], s));
         ctx->ev_used += 1;
     }
-    ctx->acc.n_work_items = hybrid ? g->hyb.n_items : g->n_items;
+    ctx->acc.n_work_items = hybrid ? cut->n_items : g->n_items;
     ctx->acc.n_split_vertices = n_heavy;
     ctx->acc.n_dense_blocks = hybrid ? g->hyb.n_blocks : 0;
     ctx->acc.n_dense_edges = hybrid ? g->hyb.n_dense_edges : 0;

@@ -160,6 +160,10 @@ struct HybridParams {
 //   21,621          128 188, 2669  64 111, 2521  48 95, 2488  32 115, 2534
 //   66,159          128 220, 3375  64 238, 3430
 //   148,828 (512 features, forward)  128 643, 4171  64 685, 4246  32 831, 4445
+// Short chunks are more partial rows, 64 of F fp32 values each. Where a layer's scratch memory would not fit what
+// saga_layer_forward_noalloc has, and with longer chunks does, it takes the first of twice, four times, ... the length that fits;
+// the ordinary call takes the same, for the same bits. Under a budget always the longest: streamed calls plan with what is left of
+// it. (65,536 vertices, R-MAT of 32 edges both ways, 256 bf16 features: 55 to 62 MiB with chunks of 128, 67 or more with 9.)
 constexpr int kDenseChunkMin = 5, kDenseChunkMax = 128, kDenseResident = 2 * 256;
 // A block's weights reach the kernel in one of two forms: as a list of (cell, weight) pairs that the workgroup scatters
 // into a cleared LDS operand (blocks of up to kDenseListMax edges: one pair per thread), or, for fuller blocks, as the
@@ -183,12 +187,16 @@ struct HybridPlan {
     std::vector<int32_t> de_edge;        // the edge's number in the caller's edge order
     std::vector<int32_t> dt_addr;        // edges of finished operands: operand * kDenseTileElems + cell (the high part; the low part is kDenseM * kDenseK further)
     std::vector<int32_t> dt_edge;
-    std::vector<DenseChunk> chunks;
+    std::vector<int64_t> tile_b0;        // n_dst_tiles + 1: a destination tile's blocks
+    std::vector<DenseChunk> chunks;      // (chunks and extra_slots: divide_dense_blocks)
     std::vector<int32_t> extra_slots;    // per vertex: chunks of its destination tile (0: the tile has no dense blocks)
     std::vector<int64_t> rem_col_ptr;    // the remainder as a CSC of its own (sources ascending inside a column)
     std::vector<int32_t> rem_row_idx, rem_edge;
 };
 void build_hybrid_plan(const int64_t* col_ptr, const int32_t* row_idx, int64_t n, const HybridParams& hp, HybridPlan* out);
+// Every tile's blocks into chunks of at most `length`, alike up to one block; returns the partial rows they write.
+int64_t divide_dense_blocks(HybridPlan* plan, int64_t n, int64_t length);
+inline int64_t dense_chunk_length(int64_t n_blocks) { return std::min<int64_t>(kDenseChunkMax, kDenseChunkMin + n_blocks / kDenseResident); }
 
 // ---------------------------------------------------------------------------
 // device buffers with accounting
@@ -305,16 +313,26 @@ struct saga_ctx {
 
 struct ChunkGrid;  // streamed representation (chunked.hip)
 
+// One division of a graph's dense blocks into chunks, and the remainder's work list, whose partial rows stand behind theirs
+struct HybridCut {
+    int64_t length = 0;                   // blocks per chunk
+    DevBuf chunks, tile_row_slot0, items, heavy;
+    int64_t n_chunks = 0, n_items = 0, n_team = 0, n_light = 0, light_edges = 0, n_heavy = 0, n_slots = 0;
+};
 // The dense-block form of a resident graph on the device (built at the first call that can use it).
 struct HybridDevice {
     bool built = false, usable = false;   // usable: the graph has dense blocks worth taking
     WorkListParams list_params{-1, -1, -1, false, 1};
     HybridParams hp;
-    int64_t n_chunks = 0, n_blocks = 0, n_dense_edges = 0, n_rem_edges = 0;
-    DevBuf chunks, blk_src_tile, blk_e0, blk_tile, de_pos, de_edge, de_w, dt_addr, dt_edge, de_tiles, src_tile_ids, tile_row_slot0;
+    int64_t n_blocks = 0, n_dense_edges = 0, n_rem_edges = 0;
+    DevBuf blk_src_tile, blk_e0, blk_tile, de_pos, de_edge, de_w, dt_addr, dt_edge, de_tiles, src_tile_ids;
     int64_t n_list_edges = 0, n_tile_edges = 0, n_tiles = 0;
-    DevBuf rem_row_idx, rem_edge, rem_w, items, heavy;
-    int64_t n_items = 0, n_team = 0, n_light = 0, light_edges = 0, n_heavy = 0, n_slots = 0;
+    DevBuf rem_row_idx, rem_edge, rem_w;
+    struct Length {
+        int64_t length, n_slots;          // blocks per chunk, partial rows of the whole propagation
+    };
+    std::vector<Length> lengths;          // what a layer chooses from, shortest first
+    std::vector<HybridCut> cuts;          // those chosen so far; they stay while the plan does
     int weights_state = 0;                // 0: de_w / rem_w not packed; 1: packed from the attached edge data; 2: packed as all ones (COPY)
 };
 
@@ -542,10 +560,11 @@ bool gemm_takes_row_list(const GemmArgs& a);  // a with row_ids set: would launc
 // The dense-block form of a bf16 sum propagation (hybrid.hip) over one edge order of a graph: the plan and its device
 // copy (ensure_hybrid; view->hyb.usable says whether the graph has blocks worth it), whether a call qualifies
 // (hybrid_applies: options, rows of a multiple of 128 bf16 values, 16-byte aligned), the launch of the dense half
-// (hybrid_dense_launch) and the release of the plan.
-saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* view, int64_t row_bytes, int32_t width = 0);
+// (hybrid_dense_launch) and the release of the plan. beside: what else the layer would carve from the scratch memory of a call that
+// must not allocate (-1: no such call exists); *cut, set if the plan is usable, is valid until the next call.
+saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* view, int64_t row_bytes, int32_t width, int64_t beside, const HybridCut** cut);
 bool hybrid_applies(const saga_ctx* ctx, int32_t F, int64_t ld, const void* rows);
-saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, GatherArgs* ga, bool weighted, const float* w_src, bool w_attached,
+saga_status hybrid_dense_launch(saga_ctx* ctx, saga_graph* view, const HybridCut& cut, GatherArgs* ga, bool weighted, const float* w_src, bool w_attached,
                                 saga_ctx::EventSet* es, bool* forked);
 void hybrid_free(saga_ctx* ctx, HybridDevice* h);
 

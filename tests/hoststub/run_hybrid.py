@@ -10,6 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 TESTS = os.path.dirname(HERE)
 sys.path[:0] = [os.path.dirname(TESTS), TESTS, HERE]
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -19,8 +21,38 @@ from helpers import assert_sum_close
 from stub_binding import StubContext, dev
 
 
+def chunk_lengths(lib):
+    """The length of chunks by the number of blocks: 5, one more for every 512 blocks, 128 at most; a tile's blocks divided evenly."""
+    plan = ctypes.CDLL(lib).saga_plan_dense_blocks
+    i64, ptr = ctypes.c_int64, ctypes.c_void_p
+    plan.argtypes = [i64, ptr, ptr, i64, i64, ctypes.c_int32, ptr, ptr, i64, ptr, i64, ptr, ptr, ptr, ptr, ptr]
+    rng = np.random.default_rng(5)
+    seen = []
+    for n, m in ((512, 12000), (1500, 40000), (4096, 60000), (16384, 600000)):
+        key = np.unique(rng.integers(0, n * n, m))
+        col_ptr = np.zeros(n + 1, np.int64)
+        np.cumsum(np.bincount(key // n, minlength=n), out=col_ptr[1:])
+        row_idx = (key % n).astype(np.int32)
+        counts, chunks = np.zeros(4, np.int64), np.zeros((200000, 4), np.int32)
+        at = lambda x: x.ctypes.data
+        assert plan(n, at(col_ptr), at(row_idx), 1, 0, 0, at(counts), at(chunks), len(chunks), None, 0, None, None, None, None, None) == 0
+        n_chunks, nb = int(counts[0]), int(counts[1])
+        length = min(128, 5 + nb // 512)
+        seen.append(length)
+        c = chunks[:n_chunks]
+        assert (c[1:, 1] == c[:-1, 2]).all() and c[0, 1] == 0 and c[-1, 2] == nb     # every block once, in order
+        for t in np.unique(c[:, 0]):
+            of = c[c[:, 0] == t]
+            k = of[:, 2] - of[:, 1]
+            assert (of[:, 3] == np.arange(len(of))).all() and len(of) == -(-int(k.sum()) // length)
+            assert k.min() > 0 and k.max() <= length and k.max() - k.min() <= 1
+        assert plan(n, at(col_ptr), at(row_idx), 1, 0, -1, at(counts), None, 0, None, 0, None, None, None, None, None) == 1
+    assert seen[0] == 5 and 5 < seen[1] < seen[2] < 128 and seen[3] == 128, seen
+
+
 def main():
     lib = sys.argv[1]
+    chunk_lengths(lib)
     rng = np.random.default_rng(31)
     t = lambda *shape, s=1.0: torch.as_tensor((rng.standard_normal(shape) * s).astype(np.float32))
     checked = 0

@@ -18,6 +18,70 @@ from paper_1810_08403_amd import binding as B
 from stub_binding import StubContext, dev
 
 
+def dense_blocks_near_the_limit(lib, rng):
+    """bf16 sums whose dense blocks, in chunks of the length that is taken by their number, write more partial rows than the
+    scratch array holds, and in longer chunks do not: accepted, with the ordinary call's bits; and in a context with a budget, no more
+    partial rows than the longest chunks write."""
+    src, dst = si.rmat_edges(9, 40 << 9, 909)
+    g = si.build_csc(1 << 9, src, dst, symmetrise=True, self_loops=True)
+
+    def context(budget=0, **options):
+        ctx = StubContext(lib, budget)
+        for k, v in dict(dense_min_edges=8, dense_tile_gain=0, stripe_kb=0, **options).items():  # (no bands: the same pieces for every width)
+            ctx.set_option(k, v)
+        ctx.set_profiling(True)
+        return ctx, ctx.graph_create_csc(g.n, dev(g.col_ptr), dev(g.row_idx))
+
+    def layer(F, Fo):
+        X = dev(torch.as_tensor(rng.standard_normal((g.n, F)).astype(np.float32)).to(torch.bfloat16))
+        kw = dict(W=dev(torch.full((F, Fo), 0.01).to(torch.bfloat16))) if Fo else {}
+
+        def call(ctx, h, no_alloc=False):
+            Y = dev(torch.full((g.n, Fo or F), float("nan"), dtype=torch.bfloat16))
+            before = ctx.lib.stub_allocator_calls()
+            ctx.layer_forward(h, X, Y, edge_op="copy", no_alloc=no_alloc, **kw)
+            calls = ctx.lib.stub_allocator_calls() - before
+            ctx.synchronize()
+            assert not torch.isnan(Y.t.float()).any() and not (no_alloc and calls)
+            return Y.t, calls, ctx.get_timings()["n_partial_rows"]
+        return call
+
+    rows = {}
+    for chunk in (5, 10, 128):
+        ctx, h = context(dense_chunk=chunk)
+        rows[chunk] = layer(128, 0)(ctx, h)[2]
+        h.destroy()
+        ctx.destroy()
+    mib = lambda n_rows, F: n_rows * F * 4 / 2 ** 20
+    wide, narrow = 11008, 128
+    beside = 2 * wide * (512 + 128) / 2 ** 20     # bf16 rows before the product, and weights of up to 128 columns
+    assert mib(rows[128], wide) < mib(rows[10], wide) + beside < 64 < mib(rows[5], wide) + beside and mib(rows[5], wide) < 64, rows
+    assert mib(rows[5], 16384) > 64 > mib(rows[10], 16384)
+    checked = 0
+    for F, Fo, budget, length in ((wide, 3, 0, 10), (16384, 0, 0, 10), (narrow, 3, 0, 5), (narrow, 3, 1 << 30, 128)):
+        ctx, h = context(budget)
+        call = layer(F, Fo)
+        Y0, _, n0 = call(ctx, h)
+        Y1, _, n1 = call(ctx, h, no_alloc=True)
+        assert n0 == n1 == rows[length], (F, Fo, budget, n0, n1, rows)
+        assert torch.equal(Y0, Y1)
+        h.destroy()
+        ctx.destroy()
+        checked += 1
+    # two layers of one width, of which one fits with the shortest chunks and the other does not: a call that finds only the other's
+    # chunks takes those, and each keeps its own
+    ctx, h = context()
+    with_w, without = layer(wide, 3), layer(wide, 0)
+    assert with_w(ctx, h)[2] == without(ctx, h, no_alloc=True)[2] == rows[10]
+    Y = without(ctx, h)[0]
+    assert torch.equal(without(ctx, h, no_alloc=True)[0], Y)
+    assert with_w(ctx, h, no_alloc=True)[2] == rows[10]
+    assert with_w(ctx, h)[1] == without(ctx, h)[1] == 0, "a plan that was there is built again"
+    h.destroy()
+    ctx.destroy()
+    return checked + 1
+
+
 def main():
     lib = sys.argv[1]
     rng = np.random.default_rng(11)
@@ -98,6 +162,7 @@ def main():
         checked += 1
     h.destroy()
     ctx.destroy()
+    checked += dense_blocks_near_the_limit(lib, rng)
     print(f"ok: {checked} layers, no allocator reached", flush=True)
 
 
