@@ -1696,7 +1696,7 @@ saga_status saga_graph_info(const saga_graph* g, int64_t* max_in_degree, int64_t
 static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_tensor* X, const saga_edge_params* ep, const saga_vertex_params* vp,
                         const saga_tensor* Y, const GatherArgs& ga, int64_t n_slots)
 {
-    if (!launch_layer_small || !ctx->opt_small || !ctx->opt_fused || ctx->opt_team || !vp || !vp->W || vp->W_self) return false;
+    if (!ctx->opt_small || !ctx->opt_fused || ctx->opt_team || !vp || !vp->W || vp->W_self) return false;
     if ((ep->op != SAGA_EDGE_COPY && ep->op != SAGA_EDGE_MUL_WEIGHT) || X->dtype != SAGA_F32) return false;
     if (g->nnz == 0 || g->nnz >= (1LL << 30) - 64 || X->cols < kSmallMinF || X->cols > kSmallMaxF) return false;
     if (((g->n - 1) * X->ld + X->cols) * 4 >= 0xffff0000LL) return false;

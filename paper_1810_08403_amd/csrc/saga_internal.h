@@ -447,7 +447,7 @@ struct GatherArgs {
 hipError_t launch_gather(const GatherArgs& a, hipStream_t s);
 
 // A small fp32 layer, propagation (COPY, MUL_WEIGHT) and ApplyVertex, in one launch (small.hip): whole columns only, no self
-// operand, n_items < 2^31. Weak: a stand-in for the kernels need not have it.
+// operand, n_items < 2^31.
 struct SmallLayerArgs {
     const WorkItem* items;
     int64_t n_items;
@@ -469,7 +469,7 @@ struct SmallLayerArgs {
 constexpr int kSmallMinF = 13, kSmallMaxF = 128;  // rows of 4 to 32 fragments
 constexpr int kSmallMaxN = 256;                    // 32 columns a wavefront
 constexpr int kSmallUnits = 32;                    // 32 columns x 16 k of the weights, 3 KiB of LDS each
-hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s) __attribute__((weak));
+hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s);
 
 struct CombineArgs {
     const HeavyVertex* heavy;

@@ -1,0 +1,109 @@
+"""Which layers go out in one launch, and their results, on the CPU stand-in: inside the rule, at its borders, and where outputs
+share memory with each other or with something that is read.
+
+  python tests/hoststub/run_small_layers.py <library>"""
+import ctypes
+import os
+import sys
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TESTS = os.path.dirname(HERE)
+sys.path[:0] = [os.path.dirname(TESTS), TESTS, HERE]
+
+import numpy as np
+import torch
+
+import oracle
+from helpers import assert_sum_close
+from stub_binding import Dev, StubContext, dev
+
+
+def regular(n, deg):
+    """Every column with `deg` sources, the first with one edge more."""
+    rows = [np.sort((v * 7 + np.arange(deg + (v == 0)) * 3) % n) for v in range(n)]
+    return torch.from_numpy(np.concatenate([[0], np.cumsum([len(r) for r in rows])])), torch.from_numpy(np.concatenate(rows).astype(np.int32))
+
+
+def main():
+    lib = sys.argv[1]
+    rng = np.random.default_rng(3)
+    t = lambda *s: torch.as_tensor(rng.standard_normal(s).astype(np.float32))
+    ctx = StubContext(lib)
+    ctx.lib.stub_small_launches.restype = ctypes.c_int64
+    checked = 0
+
+    def graph(n, deg):
+        cp, ri = regular(n, deg)
+        return n, cp, ri, ctx.graph_create_csc(n, dev(cp), dev(ri))
+
+    def layer(g, F, N, one_launch, place=None, op="copy", agg="sum", act="relu", self_=False):
+        nonlocal checked
+        n, cp, ri, h = g
+        X, W, bias = t(n, F), t(F, N), t(N)
+        w = t(ri.numel())
+        # (views keep their strides as Dev tensors of their own)
+        mem = torch.full((n, F + N), float("nan"))
+        Xd, Wd, bd, wd = dev(X), dev(W), dev(bias), dev(w)
+        Yd, Ad = dev(torch.full((n, N), float("nan"))), dev(torch.full((n, F), float("nan")))
+
+        def view(x):
+            d = Dev(torch.empty(0))
+            d.t = x
+            return d
+        if place == "Y in X":
+            Xd, Yd = view(mem[:, :F]), view(mem[:, :N])
+            Xd.t.copy_(X)
+        elif place == "A in Y":
+            Yd, Ad = view(mem[:, :N]), view(mem[:, 1:1 + F])
+        elif place == "A in W":
+            Wd = view(mem.view(-1)[F:F + F * N].view(F, N))
+            Wd.t.copy_(W)
+            Ad = view(mem.view(-1)[:n * F].view(n, F))
+        elif place == "A in bias":
+            bd = view(mem.view(-1)[F:F + N])
+            bd.t.copy_(bias)
+            Ad = view(mem.view(-1)[:n * F].view(n, F))
+        elif place == "no A":
+            Ad = None
+        kw = dict(W=Wd, bias=bd, act=act, agg=agg, edge_op=op, accum_out=Ad)
+        if op == "mul_weight":
+            kw["edge_weight"] = wd
+        if self_:
+            kw["W_self"] = dev(t(F, N))
+        before = ctx.lib.stub_small_launches()
+        ctx.layer_forward(h, Xd, Yd, **kw)
+        ctx.synchronize()
+        took = ctx.lib.stub_small_launches() - before
+        assert took == int(one_launch), (n, F, N, place, op, agg, took)
+        ref = oracle.layer(cp.numpy(), ri.numpy(), X.numpy(), op, w.numpy() if op == "mul_weight" else None, agg=agg, W=W.numpy(), bias=bias.numpy(), act=act)
+        if place in (None, "no A", "Y in X") and not self_:
+            assert_sum_close(Yd.t.numpy(), ref["Y"], ref["Y_abs"], 1e-5, f"{n} {F} {N} {place}")
+            if Ad is not None:
+                assert_sum_close(Ad.t.numpy(), ref["A"], ref["A_abs"], 1e-5, f"{n} {F} {N} {place} A")
+        checked += 1
+
+    g = graph(700, 8)
+    for op in ("copy", "mul_weight"):
+        for agg in ("sum", "max"):
+            layer(g, 64, 64, True, op=op, agg=agg)
+            layer(g, 64, 64, True, op=op, agg=agg, place="no A", act="sigmoid")
+    for F, N, one in ((12, 16, False), (13, 16, True), (128, 16, True), (129, 16, False), (64, 256, True), (64, 257, False), (96, 160, True), (96, 161, False)):
+        layer(g, F, N, one)
+    layer(g, 64, 64, False, self_=True)
+    for place in ("Y in X",):
+        layer(g, 64, 64, False, place=place)
+    long = graph(300, 95)
+    layer(long, 64, 64, True)                     # the first column has 96 edges
+    longer = graph(300, 96)
+    layer(longer, 64, 64, False)                   # 97
+    ctx.set_option("small_layer", 0)
+    layer(g, 64, 64, False)
+    ctx.set_option("small_layer", 1)
+    for x in (g, long, longer):
+        x[3].destroy()
+    ctx.destroy()
+    print(f"ok: {checked} layers", flush=True)
+
+
+if __name__ == "__main__":
+    main()

@@ -235,6 +235,46 @@ hipError_t launch_gather(const GatherArgs& a, hipStream_t s)
     return hipSuccess;
 }
 
+// A layer in one launch: a workgroup's 32 rows are propagated into memory of its own, multiplied and written before the next
+// workgroup reads anything, which is one of the orders in which they may run.
+static int64_t g_small_launches = 0;
+extern "C" int64_t stub_small_launches() { return g_small_launches; }
+hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s)
+{
+    if (a.n_items <= 0) return hipSuccess;
+    if (a.F < kSmallMinF || a.F > kSmallMaxF || a.N < 1 || a.N > kSmallMaxN || (a.F + 31) / 32 * 2 * ((a.N + 31) / 32) > kSmallUnits ||
+        a.n_src < 1 || a.n_edges < 0 || a.ldx < a.F)
+        return hipErrorInvalidValue;
+    ++g_small_launches;
+    stub_enqueue(s, [a] {
+        std::vector<float> rows((size_t)32 * a.F);
+        for (int64_t i0 = 0; i0 < a.n_items; i0 += 32) {
+            const int64_t m = std::min<int64_t>(32, a.n_items - i0);
+            for (int64_t i = 0; i < m; ++i) {
+                const WorkItem it = a.items[i0 + i];
+                if (it.v < 0 || it.slot >= 0 || it.e0 > it.e1 || it.e1 > a.n_edges) die("an item that is no whole column in a one-launch layer");
+                for (int f = 0; f < a.F; ++f) {
+                    double acc = a.agg == SAGA_AGG_SUM ? 0.0 : (double)kNegInf;
+                    for (int32_t e = it.e0; e < it.e1; ++e) {
+                        if (a.row_idx[e] < 0 || a.row_idx[e] >= a.n_src) die("a source id past the table's rows");
+                        const float msg = (a.edge_w ? a.edge_w[e] : 1.f) * a.X[(int64_t)a.row_idx[e] * a.ldx + f];
+                        acc = a.agg == SAGA_AGG_SUM ? acc + (double)msg : std::max(acc, (double)msg);
+                    }
+                    rows[(size_t)(i * a.F + f)] = it.e0 == it.e1 ? 0.f : (float)acc;
+                    if (a.A) a.A[(int64_t)it.v * a.lda + f] = rows[(size_t)(i * a.F + f)];
+                }
+            }
+            for (int64_t i = 0; i < m; ++i)
+                for (int n = 0; n < a.N; ++n) {
+                    double y = a.bias ? (double)a.bias[n] : 0.0;
+                    for (int f = 0; f < a.F; ++f) y += (double)rows[(size_t)(i * a.F + f)] * a.W[(int64_t)f * a.ldw + n];
+                    a.Y[(int64_t)a.items[i0 + i].v * a.ldy + n] = apply_act((float)y, a.act);
+                }
+        }
+    });
+    return hipSuccess;
+}
+
 // Items of that list and the light columns' copy in order of length, if there is one (as many as fit `capacity`); counts: items,
 // shared ones at their start, light columns, their edges.
 extern "C" void stub_last_work_list(int32_t* items, int32_t* light, int64_t capacity, int64_t* counts)

@@ -78,6 +78,10 @@ def test_no_alloc_entry_point_reaches_no_allocator(stub_lib):
     _run("run_no_alloc.py", stub_lib)
 
 
+def test_which_layers_go_out_in_one_launch(stub_lib):
+    _run("run_small_layers.py", stub_lib)
+
+
 def test_shared_items_and_light_columns_of_resident_lists(stub_lib):
     _run("run_shared_items.py", stub_lib)
 
