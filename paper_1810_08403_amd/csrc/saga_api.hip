@@ -1694,7 +1694,7 @@ saga_status saga_graph_info(const saga_graph* g, int64_t* max_in_degree, int64_t
 // ---------------------------------------------------------------------------
 // Does the one-launch kernel take the layer whose propagation is `ga`?
 static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_tensor* X, const saga_edge_params* ep, const saga_vertex_params* vp,
-                        const saga_tensor* Y, const GatherArgs& ga, int64_t n_slots)
+                        const saga_tensor* Y, const saga_tensor* accum_out, const GatherArgs& ga, int64_t n_slots)
 {
     if (!ctx->opt_small || !ctx->opt_fused || ctx->opt_team || !vp || !vp->W || vp->W_self) return false;
     if ((ep->op != SAGA_EDGE_COPY && ep->op != SAGA_EDGE_MUL_WEIGHT) || X->dtype != SAGA_F32) return false;
@@ -1713,14 +1713,19 @@ static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_ten
     const int64_t F = X->cols, N = vp->W->cols, n = g->n;
     if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || (N + 31) / 32 * ((F + 31) / 32 * 2) > kSmallUnits) return false;
     if (n > 32768 || n * F * N > (n <= 16384 ? 1LL << 27 : 1LL << 25)) return false;
-    // Two launches read everything before they write results; one must not write what its other workgroups read.
+    // Separate launches read everything before they write results, and all of A before any of Y; one must not write what its other
+    // workgroups read, nor one result over the other.
     auto apart = [](const void* p, int64_t bytes, const void* q, int64_t more) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
         return !p || !q || a + (uintptr_t)bytes <= b || b + (uintptr_t)more <= a;
     };
     auto extent = [](const saga_tensor* t) { return t ? ((t->rows - 1) * t->ld + t->cols) * 4 : 0; };
-    return apart(X->data, extent(X), Y->data, extent(Y)) && apart(vp->W->data, extent(vp->W), Y->data, extent(Y)) &&
-           apart(vp->bias ? vp->bias->data : nullptr, extent(vp->bias), Y->data, extent(Y)) && apart(ga.edge_w, g->nnz * 4, Y->data, extent(Y));
+    auto from_inputs = [&](const saga_tensor* out) {
+        return apart(X->data, extent(X), out->data, extent(out)) && apart(vp->W->data, extent(vp->W), out->data, extent(out)) &&
+               apart(vp->bias ? vp->bias->data : nullptr, extent(vp->bias), out->data, extent(out)) &&
+               apart(ga.edge_w, g->nnz * 4, out->data, extent(out));
+    };
+    return from_inputs(Y) && (!accum_out || (from_inputs(accum_out) && apart(accum_out->data, extent(accum_out), Y->data, extent(Y))));
 }
 
 static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_tensor* X, const saga_edge_params* ep,
@@ -1881,7 +1886,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         if (saga_status st = ctx->dev_alloc(&ctx->ws_partials, sizeof(float) * (size_t)n_slots * ga.F)) return st;
         ga.partials = static_cast<float*>(ctx->ws_partials.p);
     }
-    const bool small = !tf && !hybrid && small_layer(ctx, g, X, ep, vp, Y, ga, n_slots);
+    const bool small = !tf && !hybrid && small_layer(ctx, g, X, ep, vp, Y, accum_out, ga, n_slots);
     bool dense_forked = false;
     if (hybrid) {
         const bool weighted = ep->op == SAGA_EDGE_MUL_WEIGHT;

@@ -90,7 +90,7 @@ def main():
     for F, N, one in ((12, 16, False), (13, 16, True), (128, 16, True), (129, 16, False), (64, 256, True), (64, 257, False), (96, 160, True), (96, 161, False)):
         layer(g, F, N, one)
     layer(g, 64, 64, False, self_=True)
-    for place in ("Y in X",):
+    for place in ("Y in X", "A in Y", "A in W", "A in bias"):
         layer(g, 64, 64, False, place=place)
     long = graph(300, 95)
     layer(long, 64, 64, True)                     # the first column has 96 edges
