@@ -1712,6 +1712,9 @@ static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_ten
     //   65,536  16x16 31.5 28.6 / 36.6 38.0   64x64  44.5 43.5 / 77.6 79.2
     const int64_t F = X->cols, N = vp->W->cols, n = g->n;
     if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || (N + 31) / 32 * ((F + 31) / 32 * 2) > kSmallUnits) return false;
+    // Sums of rows of eight fragments over 32,768 columns of at most 16 edges: k_gather_light adds a column in one chain there (see
+    // takes_light and launch_light), this kernel in eight sums.
+    if (ga.agg == SAGA_AGG_SUM && (F + 3) / 4 == 8 && ga.n_light >= 32768) return false;
     if (n > 32768 || n * F * N > (n <= 16384 ? 1LL << 27 : 1LL << 25)) return false;
     // Separate launches read everything before they write results, and all of A before any of Y; one must not write what its other
     // workgroups read, nor one result over the other.

@@ -99,7 +99,12 @@ def main():
     ctx.set_option("small_layer", 0)
     layer(g, 64, 64, False)
     ctx.set_option("small_layer", 1)
-    for x in (g, long, longer):
+    # 32,768 columns of at most 16 edges: sums of rows of eight fragments are k_gather_light's in separate launches, which adds them in
+    # another order
+    light = graph(32768, 2)
+    for F, agg, one in ((28, "sum", True), (29, "sum", False), (32, "sum", False), (32, "max", True), (33, "sum", True)):
+        layer(light, F, 8, one, agg=agg, place="no A")
+    for x in (g, long, longer, light):
         x[3].destroy()
     ctx.destroy()
     print(f"ok: {checked} layers", flush=True)

@@ -80,6 +80,31 @@ def test_columns_at_the_longest_taken(longest):
     assert float((Y.double() - ref).norm() / ref.norm()) < 3e-7
 
 
+@pytest.mark.parametrize("n", [16384, 32768])
+@pytest.mark.parametrize("F,N", [(13, 16), (16, 3), (28, 32), (29, 8), (32, 32), (33, 16), (64, 16), (100, 8)])
+def test_short_columns_of_many_vertices(n, F, N):
+    """Graphs whose columns all have at most 16 edges, which the general propagation may take several to a wavefront: the same bits
+    in one launch, and where it would add in another order the layer is not taken."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + F)
+    deg = torch.tensor([1, 3, 16, 0, 5, 15, 2, 9], device=DEV).repeat(n // 8)
+    col_ptr = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    torch.cumsum(deg, 0, out=col_ptr[1:])
+    dst = torch.repeat_interleave(torch.arange(n, device=DEV), deg)
+    start = torch.randint(0, n, (n,), generator=g, device=DEV)
+    src = (start[dst] + 7 * (torch.arange(dst.numel(), device=DEV) - col_ptr[dst])) % n
+    row_idx = (torch.sort(dst * n + src).values % n).int()
+    w = torch.randn(dst.numel(), generator=g, device=DEV)
+    X, W = torch.randn(n, F, generator=g, device=DEV), torch.randn(F, N, generator=g, device=DEV)
+    out = []
+    for small in (0, 1):
+        ctx, h = _context(n, col_ptr, row_idx, small)
+        A, Y = torch.full((n, F), float("nan"), device=DEV), torch.full((n, N), float("nan"), device=DEV)
+        ctx.layer_forward(h, X, Y, edge_op="mul_weight", edge_weight=w, W=W, accum_out=A)
+        out.append((A, Y))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 def test_results_in_the_place_of_the_features():
     """Y may be X's own memory: then no row may be written while others are still read."""
     n, F = 3000, 64
