@@ -117,7 +117,7 @@ typedef struct saga_timings {
     int64_t n_calls;         /* saga_layer_forward calls accumulated */
     double ms_total;         /* first to last event of each call, summed */
     double ms_hoist;         /* per-vertex gate/message products (gated only) */
-    double ms_gather;        /* fused Scatter-ApplyEdge-Gather kernels */
+    double ms_gather;        /* fused Scatter-ApplyEdge-Gather kernels; of a layer in one launch (option "small_layer") all of it */
     double ms_combine;       /* combining the partial rows of split heavy vertices */
     double ms_apply_vertex;  /* ApplyVertex product + activation */
     int64_t n_gather_launches;

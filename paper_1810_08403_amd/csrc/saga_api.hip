@@ -1851,6 +1851,8 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
     //   fp32: accum_out if given, else Y itself when there is no ApplyVertex, else workspace
     //   bf16: a bf16 copy feeds the ApplyVertex product (or is Y itself without one);
     //         the fp32 rows are written only when accum_out asks for them
+    // In one launch it stays in the kernel but for accum_out.
+    const bool small = !tf && !hybrid && small_layer(ctx, g, X, ep, vp, Y, accum_out, ga, n_slots);
     if (tf) {
         if (bf16) {
             ga.out16 = static_cast<uint16_t*>(Y->data);
@@ -1866,7 +1868,7 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         } else if (!has_w) {
             ga.out = static_cast<float*>(Y->data);
             ga.ld_out = Y->ld;
-        } else {
+        } else if (!small) {
             if (saga_status st = ctx->dev_alloc(&ctx->ws_accum, sizeof(float) * (size_t)n * Fm)) return st;
             ga.out = static_cast<float*>(ctx->ws_accum.p);
             ga.ld_out = Fm;
@@ -1889,7 +1891,6 @@ static saga_status resident_forward(saga_ctx* ctx, saga_graph* g, const saga_ten
         if (saga_status st = ctx->dev_alloc(&ctx->ws_partials, sizeof(float) * (size_t)n_slots * ga.F)) return st;
         ga.partials = static_cast<float*>(ctx->ws_partials.p);
     }
-    const bool small = !tf && !hybrid && small_layer(ctx, g, X, ep, vp, Y, accum_out, ga, n_slots);
     bool dense_forked = false;
     if (hybrid) {
         const bool weighted = ep->op == SAGA_EDGE_MUL_WEIGHT;

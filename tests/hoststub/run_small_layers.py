@@ -107,6 +107,20 @@ def main():
     for x in (g, long, longer, light):
         x[3].destroy()
     ctx.destroy()
+    # no memory for rows that stay in the kernel
+    n, cp, ri = 700, *regular(700, 8)
+    peak = []
+    for small in (0, 1):
+        ctx = StubContext(lib)
+        ctx.set_option("small_layer", small)
+        h = ctx.graph_create_csc(n, dev(cp), dev(ri))
+        at = ctx.peak_device_bytes()
+        ctx.layer_forward(h, dev(t(n, 64)), dev(torch.empty(n, 64)), edge_op="copy", W=dev(t(64, 64)))
+        ctx.synchronize()
+        peak.append(ctx.peak_device_bytes() - at)
+        h.destroy()
+        ctx.destroy()
+    assert peak[1] < n * 64 * 4 < peak[0], peak
     print(f"ok: {checked} layers", flush=True)
 
 
