@@ -281,24 +281,37 @@ struct ItemView {
 };
 // An item is one wave-wide scalar read: a lane's read of it took a vector round trip and four moves to scalar registers ahead of the
 // first id (layers, us: GCN of two layers in training 888 -> 883, pooled 681 -> 676, 300 bf16 features 725 -> 720, others 0.2 to 0.5 %).
+// SCALAR false: the lanes read it. With gates the scalar read took k_gather_narrow from 58 registers to 72 (ragged rows 59 to 78,
+// the maximum spilled), one wavefront less per SIMD.
 typedef const int32_t __attribute__((address_space(4))) * const_item_ptr;
+template <bool SCALAR = true>
 __device__ __forceinline__ bool fetch_item(const GatherArgs& a, ItemView* it)
 {
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wave = SCALAR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : (int)threadIdx.x >> 6;
     const int64_t blk = logical_block(a.xcd_remap);
     const bool team = blk < a.n_team;
     const int64_t id = team ? blk : a.n_team + (blk - a.n_team) * kWavesPerBlock + wave;
     if (id >= a.n_items) return false;  // only in the last solo block, where no barrier follows
-    const const_item_ptr raw = (const_item_ptr)(uintptr_t)(a.items + id);
-    it->v = raw[0];
-    int e0 = raw[1], e1 = raw[2];
-    it->slot = raw[3];
+    int e0, e1;
+    if constexpr (SCALAR) {
+        const const_item_ptr raw = (const_item_ptr)(uintptr_t)(a.items + id);
+        it->v = raw[0];
+        e0 = raw[1];
+        e1 = raw[2];
+        it->slot = raw[3];
+    } else {
+        const int4 raw = *reinterpret_cast<const int4*>(a.items + id);
+        it->v = __builtin_amdgcn_readfirstlane(raw.x);
+        e0 = __builtin_amdgcn_readfirstlane(raw.y);
+        e1 = __builtin_amdgcn_readfirstlane(raw.z);
+        it->slot = __builtin_amdgcn_readfirstlane(raw.w);
+    }
     it->team = team;
     it->empty_item = e0 == e1;
     if (team) {
         // equal shares, rounded up to the unroll width of the edge loop
         const int per = (((e1 - e0 + kWavesPerBlock - 1) / kWavesPerBlock) + 7) & ~7;
-        e0 = min(e1, e0 + wave * per);
+        e0 = min(e1, e0 + __builtin_amdgcn_readfirstlane(wave) * per);
         e1 = min(e1, e0 + per);
     }
     it->e0 = e0;
@@ -841,11 +854,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 // throughput is the number of resident wavefronts over that chain (CommNet on R-MAT 20: 19 wavefronts per compute unit
 // on average at six per SIMD, propagation 1.24 ms; 1.18 ms at eight). The gate-gradient variants and the bf16 maximum
 // need more registers: five and six.
-// Ragged rows keep one more value per lane: seven. Gates, with the item in scalar registers (fetch_item), fit seven: at eight they
-// spill (a gated layer of 128 features, R-MAT 20, 3.47 ms instead of 3.05).
+// Ragged rows keep one more value per lane: seven.
 constexpr int narrow_min_waves(int elem_bytes, int agg, int ef, bool rag)
 {
-    return ef_is_grad(ef) ? 5 : (elem_bytes == 2 && agg == SAGA_AGG_MAX) ? 6 : ef == kEfGate ? (rag ? 6 : 7) : rag ? 7 : 8;
+    return ef_is_grad(ef) ? 5 : (elem_bytes == 2 && agg == SAGA_AGG_MAX) ? 6 : rag ? 7 : 8;
 }
 template <typename T, int VEC, bool RAG, int AGG, int EF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_waves(sizeof(T), AGG, EF, RAG), 8))) void k_gather_narrow(
@@ -853,7 +865,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(narrow_min_
 {
     constexpr bool GATED = EF != kEfLinear;
     ItemView it;
-    if (!fetch_item(a, &it)) return;
+    if (!fetch_item<EF != kEfGate>(a, &it)) return;
     const int lane = threadIdx.x & 63;
     const int F = a.F;
     const int nvec = (F + VEC - 1) / VEC;
