@@ -631,9 +631,9 @@ inline TnShape tn_shape(int FP, int FQ)
 constexpr int kTnStep = 16;  // vertices per step of the product
 // How many splits, and their rows. max_splits: what a workspace that is there already has room for. The number of splits does
 // not grow with n everywhere (65,537 x 256 x 256: 125; the 32,768 rows of a part of it: 128), because the rows of a split are
-// whole steps: a workspace sized by the plan of n rows holds any part of them only through max_splits. two_rounds: up to twice the
-// splits (never without it: streamed calls plan their budget around them).
-inline void gemm_tn_plan(int64_t n, int32_t FP, int32_t FQ, int64_t* rows_per_split, int32_t* n_split, int64_t max_splits = 1024, bool two_rounds = false)
+// whole steps: a workspace sized by the plan of n rows holds any part of them only through max_splits. may_grow: up to twice the
+// splits (streamed calls plan their budget around those they get without it).
+inline void gemm_tn_plan(int64_t n, int32_t FP, int32_t FQ, int64_t* rows_per_split, int32_t* n_split, int64_t max_splits = 1024, bool may_grow = false)
 {
     const TnShape t = tn_shape(FP, FQ);
     // eight wavefronts per compute unit, and at least 256 vertices per split; more splits are more partials to write, to add
@@ -642,18 +642,16 @@ inline void gemm_tn_plan(int64_t n, int32_t FP, int32_t FQ, int64_t* rows_per_sp
     int64_t want = std::max<int64_t>(1, 2048 / waves);
     // The workgroups of a split run on one XCD, which holds 256 of those wavefronts. Long splits: as many on each XCD as it holds at once,
     // so that none waits for the others and runs a round of its own; where that leaves more than a fortieth of it empty, as many as
-    // it holds in two rounds (two_rounds: the workspace may grow), whose sums are shorter too. Backward calls without dX, us, and error
+    // it holds in two rounds, whose sums are shorter too. Not where the workspace may not grow: without the second round there are
+    // fewer splits, and the longer sums have the larger error (3.0 -> 3.1e-7, 4.8 -> 4.9e-7 below). Backward calls without dX, us, and error
     // against 64 bits, before / one round / two:
     //   262,144 x 384 x 128 (12 wavefronts a split; 66 workgroups on two XCDs that hold 64)  271, 3.1e-7 / 240, 3.1e-7 / 245, 2.3e-7
     //   131,072 x 320 x 130 (24)  248, 3.0e-7 / 192, 3.1e-7 / 195, 2.2e-7    x 640 x 300 (60)  660, 4.8e-7 / 489, 4.9e-7 / 488, 3.4e-7
     //    65,536 x 640 x 640 (100) 580, 4.4e-7 / 480, 4.9e-7 / 430, 3.1e-7    131,072 x 384 x 384 (36)  331 / 323 / 328
     // Splits of fewer than 1,024 rows are some 10 us and stay as they are.
-    if (n >= want * 1024 && waves <= 256) {
+    if (may_grow && n >= want * 1024 && waves <= 256) {
         const int64_t held = 256 / waves;
-        if (held * waves >= (two_rounds ? 250 : 230))
-            want = 8 * held;
-        else if (two_rounds)
-            want = 8 * (512 / waves);
+        want = 8 * (held * waves >= 250 ? held : 512 / waves);
     }
     want = std::min<int64_t>(want, std::max<int64_t>(1, n / 256));
     want = std::min<int64_t>(want, std::max<int64_t>(1, std::min<int64_t>(max_splits, 1024)));

@@ -34,6 +34,10 @@ def main():
                 if m <= n:
                     more += plan(ctx.lib, m, FP, FQ) > room
                     assert plan(ctx.lib, m, FP, FQ, room) <= room, (n, m, FP, FQ)
+    # where the workspace may not grow (streamed calls, contexts with a budget) the splits are those of eight wavefronts per compute
+    # unit: fewer are longer sums, whose error is larger
+    for n, FP, FQ, splits in ((131072, 320, 130, 85), (131072, 640, 300, 34), (262144, 384, 128, 169), (65536, 640, 640, 20)):
+        assert plan(ctx.lib, n, FP, FQ) == splits, (n, FP, FQ, plan(ctx.lib, n, FP, FQ))
     assert more >= 3, "no part here has more splits than the whole: the cases test nothing"
     # 21,505 rows: 41 splits; the second of two source intervals, 10,752 rows: 42
     n, F, Fo = 21505, 8, 3000

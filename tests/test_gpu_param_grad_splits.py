@@ -1,5 +1,5 @@
 """Parameter gradients of backward-ApplyVertex (Section 2.2) whose vertex range is divided over as many splits as the chip holds in one
-round, in two, and in neither (few rows a split), against float64."""
+round, in two, and in neither (few rows a split, or a workspace that may not grow), against float64."""
 import pytest
 import torch
 
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
     (40001, 640, 640, 1 << 32),  # the same under a budget: the division it always had
     (20479, 640, 640, 0),        # one row too few a split for either
     (174080, 384, 128, 0),       # 12: one round of 168
-    (90117, 320, 130, 1 << 32),  # 24: one round under a budget, 80
+    (90117, 320, 130, 1 << 32),  # 24 under a budget: the division it always had
     (90117, 320, 130, 0),        # two rounds
     (35000, 64, 1000, 0)])       # a wide Q
 def test_dw_against_float64(n, f_in, f_out, budget):
