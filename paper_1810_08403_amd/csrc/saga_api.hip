@@ -1700,22 +1700,41 @@ static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_ten
     if ((ep->op != SAGA_EDGE_COPY && ep->op != SAGA_EDGE_MUL_WEIGHT) || X->dtype != SAGA_F32) return false;
     if (g->nnz == 0 || g->nnz >= (1LL << 30) - 64 || X->cols < kSmallMinF || X->cols > kSmallMaxF) return false;
     if (((g->n - 1) * X->ld + X->cols) * 4 >= 0xffff0000LL) return false;
-    // Whole columns, none so long that the workgroup waits for one of its 32; weights that fit its LDS as split units; and not so many
-    // rows that the latency of a launch is a small part of it: then the general kernels have more wavefronts in flight, and a
-    // workgroup here makes the weights' units for 32 rows only. Layers of so many vertices of 8 / 30 edges, features x outputs, us,
-    // two or three launches and one (10 is the host's part of a call):
-    //   1,024   64x64 15.0 10.0 / 14.9 10.4   64x256 14.9 11.5 / 15.0 13.3   128x16 17.0 11.1 / 17.7 14.3   128x128 16.9 13.0 / 17.6 16.4
-    //   4,096   64x64 15.0  9.9 / 15.0 10.7   64x256 16.1 12.1 / 16.4 13.9   128x16 17.5 11.1 / 19.1 14.4   128x128 23.3 13.4 / 24.6 16.7
-    //   8,192   64x64 19.6 10.4 / 20.7 11.4   64x256 18.3 12.8 / 19.4 15.3   128x16 20.1 11.8 / 23.2 16.4   128x128 22.6 14.7 / 25.3 19.5
-    //   16,384  64x64 20.5 12.9 / 23.6 18.2   64x256 23.4 25.0 / 26.3 31.2   128x16 23.6 19.2 / 34.6 32.5   128x128 26.5 30.0 / 38.1 43.9
-    //   32,768  16x16 19.8 14.6 / 23.3 18.3   64x64  28.4 23.6 / 36.5 38.3   128x16 33.0 32.6 / 68.9 68.5   128x128 39.4 59.0 / 76.7 96.4
-    //   65,536  16x16 31.5 28.6 / 36.6 38.0   64x64  44.5 43.5 / 77.6 79.2
+    // Whole columns, weights that fit its LDS as split units, and what its time goes by: the steps a wavefront takes one after the
+    // other, four, two or one edges each (rows of up to 16, 32 and 64 values) or one edge in two passes. All 8,192 rows that 256
+    // workgroups hold run at once, and the longest column decides with the average one; of more rows, some wait for others.
+    // Times of a call, one launch over several, median and 95th of 100, of 25,000 layers of 256 to 32,768 vertices, 13 to 128
+    // features, 3 to 256 outputs, columns all alike, random and skewed, by the steps (several launches are 15 us or more):
+    //                                          < 30       60         90         120        180        250        400
+    //    8,192 rows, up to 16 units of W        .65 .68    .66 .70    .67 .74    .75 .85    .78 .89    .89 1.02   .98 1.12
+    //                more, > 64 features        .67 .76    .70 .79    .77 .84    .82 .89    .84 .95    .91 1.10  1.10 1.22
+    //                more, up to 64             .67 .73    .71 .80    .80 .88    .85 1.00   .93 1.05
+    //   16,384 rows, up to 8 units              .65 .72    .69 .82    .75 .90    .78 .90    .84 .98    .88 1.06   .98 1.12
+    //                9 to 16, up to 64          .65 .75    .70 .78    .73 .85    .80 .95    .90 1.03
+    //                9 to 16, > 64              .61 .66    .62 .69    .65 .76    .61 .75    .70 .83    .82 .98    .87 1.02
+    //                more, or > 128 outputs     .92 1.05   .96 1.09  1.01 1.18
+    //   24,576 rows, up to 64                   .69 .81    .77 .90    .86 1.01   .92 1.02   .97 1.09
+    //                > 64                       .86 .92    .86 .95    .88 1.01
+    //   32,768 rows, up to 64                   .75 .89    .86 .98    .95 1.09  1.00 1.10
+    //                > 64                       .98 1.06   .93 1.08
     const int64_t F = X->cols, N = vp->W->cols, n = g->n;
-    if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || (N + 31) / 32 * ((F + 31) / 32 * 2) > kSmallUnits) return false;
+    const int64_t units = (N + 31) / 32 * ((F + 31) / 32 * 2);
+    if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || units > kSmallUnits || n > 32768) return false;
+    const int64_t average = g->nnz / n;
+    const int64_t steps = (n <= 8192 ? g->max_degree + average : g->max_degree / 2 + 2 * average) * (F > 64 ? 2 : 1) / (F <= 16 ? 4 : F <= 32 ? 2 : 1);
+    int64_t limit;
+    if (n <= 8192)
+        limit = units <= 16 ? 200 : F > 64 ? 180 : 110;
+    else if (units > 16 || N > 128)
+        limit = -1;
+    else if (n <= 16384)
+        limit = units <= 8 ? 180 : F > 64 ? 250 : 120;
+    else
+        limit = n > 24576 && F > 64 ? -1 : 60;
+    if (steps > limit || (n > 16384 && n * F * N > 1LL << 25)) return false;
     // Sums of rows of eight fragments over 32,768 columns of at most 16 edges: k_gather_light adds a column in one chain there (see
     // takes_light and launch_light), this kernel in eight sums.
     if (ga.agg == SAGA_AGG_SUM && (F + 3) / 4 == 8 && ga.n_light >= 32768) return false;
-    if (n > 32768 || n * F * N > (n <= 16384 ? 1LL << 27 : 1LL << 25)) return false;
     // Separate launches read everything before they write results, and all of A before any of Y; one must not write what its other
     // workgroups read, nor one result over the other.
     auto apart = [](const void* p, int64_t bytes, const void* q, int64_t more) {

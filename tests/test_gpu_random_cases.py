@@ -105,6 +105,7 @@ def test_random_forward_case(seed):
             opts["fused"] = 0
         if rng.random() < 0.4:
             opts["transform_first"] = 1
+    opts["small_layer"] = int(np.random.default_rng(9000 + seed).integers(2))   # small fp32 layers in one launch or in several
     want_accum = not (opts.get("transform_first") and rng.random() < 0.7)   # asking for the Gather output keeps the paper's order
     pads = [int(x) for x in rng.choice([0, 0, 0, 1, 3, 4, 8, 20], 3)]          # row strides beyond the row width
     with new_context(**opts) as c:
@@ -568,7 +569,7 @@ def test_random_session_on_one_context(seed):
     rng = np.random.default_rng(7000 + seed)
     t = lambda *shape, s=1.0: torch.as_tensor((rng.standard_normal(shape) * s).astype(np.float32))
     nan = lambda *s: torch.full(s, float("nan"), device="cuda")
-    with new_context() as c:
+    with new_context(small_layer=seed % 2) as c:
         graphs = []
         for k in range(3):
             _, g, *_ = _case(7100 + 10 * seed + k)

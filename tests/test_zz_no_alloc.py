@@ -20,11 +20,13 @@ def _graph(rng, n, m, hub):
 @pytest.mark.parametrize("op,agg,dtype", [("mul_weight", "sum", torch.float32), ("copy", "max", torch.float32),
                                           ("mul_weight", "sum", torch.bfloat16), ("gated", "sum", torch.float32),
                                           ("pool", "max", torch.float32)])
-def test_no_alloc_matches_the_ordinary_call(op, agg, dtype):
+@pytest.mark.parametrize("small_layer", [0, 1])   # 0: the second call, too, is several launches with rows and weights in the scratch
+def test_no_alloc_matches_the_ordinary_call(op, agg, dtype, small_layer):
     import paper_1810_08403_amd as saga
     rng = np.random.default_rng(21)
     t = lambda *shape, s=1.0: torch.as_tensor((rng.standard_normal(shape) * s).astype(np.float32)).cuda()
     ctx = saga.Context(0)
+    ctx.set_option("small_layer", small_layer)
     for n, m, hub, F, Fo in ((6000, 90000, True, 128, 64), (700, 5000, False, 64, 16)):   # the second call is the smaller one
         g = _graph(rng, n, m, hub)
         h = ctx.graph_create_csc(n, g.col_ptr.cuda(), g.row_idx.cuda())
