@@ -549,7 +549,7 @@ struct GemmArgs {
     int64_t M;
     int32_t N, K;
     int32_t dtype;      // of A and the weights
-    int32_t out_dtype;  // of C
+    int32_t out_dtype;  // of C: the same
     int32_t act;
     // optional: the product over a list of M rows. Row i of the product reads row row_ids[i] of A and writes row
     // row_ids[i] of C. Only where gemm_takes_row_list says so (fp32, one operand).

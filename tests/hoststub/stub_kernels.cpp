@@ -467,7 +467,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.row_ids && !gemm_takes_row_list(a)) return hipErrorInvalidValue;
     if (a.row_ids) ++g_row_list_launches;
     if (a.K <= 0 || (a.A2 && a.K2 <= 0)) return hipErrorInvalidValue;
-    if (a.dtype == SAGA_F32 && a.out_dtype != SAGA_F32) return hipErrorInvalidValue;
+    if (a.out_dtype != a.dtype) return hipErrorInvalidValue;
     const GemmArgs copy = a;
     stub_enqueue(s, [copy] { gemm_cpu(copy); });
     return hipSuccess;
