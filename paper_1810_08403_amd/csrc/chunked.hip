@@ -366,7 +366,10 @@ saga_status streamed_forward(saga_ctx* ctx, saga_graph* g, const saga_tensor* X,
     auto tile_rows_for = [&](int q) {
         // About 64 MiB a tile, but a sixteenth of a smaller budget, down to 8 MiB: two tiles stand beside the accumulator, and the
         // fewer destination intervals that leaves, the less often all vertex data cross the link (256 MiB, 262,144 vertices of 256
-        // features in and out: 64 MiB three intervals and 23.9 ms, 16 MiB two and 16.7, 8 MiB two and 17.0).
+        // features in and out: 64 MiB three intervals and 23.9 ms, 16 MiB two and 16.7, 8 MiB two and 17.0). Layers, ms, with tiles of
+        // 64 MiB and these: budget of 64 MiB, 262,144 vertices, 128 -> 128 37.2 21.4; 96, 131,072, 128 -> 16 3.4 3.4; 128, 262,144,
+        // 256 -> 256 47.7 25.8, 64 -> 64 6.0 4.6; 128, 524,288, 32 -> 128 23.6 11.9; 160, 131,072, 300 -> 300 16.3 10.7; 256, 262,144,
+        // 512 -> 64 36.2 36.1, 64 -> 300 8.4 8.3; 256, 524,288, 128 -> 128 25.9 17.6; 512 and 768, 262,144, 256 -> 256 10.4 and 10.6 both.
         const int64_t Dq = (n + q - 1) / q, mib = 1 << 20;
         const int64_t tile = ctx->budget > 0 ? std::min(64 * mib, std::max<int64_t>(8 * mib, (int64_t)(ctx->budget / 16))) : 64 * mib;
         return std::min<int64_t>(Dq, std::max<int64_t>(4096, tile / (F_out * 4)));
