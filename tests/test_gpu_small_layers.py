@@ -134,3 +134,33 @@ def test_not_finite_values_reach_their_own_columns_only():
     hit[dst[(row_idx == 5) | (row_idx == 77)]] = True
     assert bool(hit.any()) and not bool(hit.all())
     assert bool((torch.isfinite(Y).all(1) == ~hit).all()) and bool((torch.isfinite(A).all(1) == ~hit).all())
+
+
+@pytest.mark.parametrize("agg", ["sum", "max"])
+@pytest.mark.parametrize("act", ["sigmoid", "none"])
+@pytest.mark.parametrize("F", [13, 30, 48, 100])
+def test_edge_values_as_in_separate_launches(F, act, agg):
+    """Infinities, NaN, zeros and the largest and smallest values among features and edge weights, and what the activation makes of
+    them: the values that the general kernels give. (A maximum leaves an edge out past its column's end by a weight of infinity.)"""
+    n, N = 640, 33
+    col_ptr, row_idx, g = _graph(n, 3 + F)
+    m = row_idx.numel()
+    w = torch.randn(m, generator=g, device=DEV)
+    X, W = torch.randn(n, F, generator=g, device=DEV), torch.randn(F, N, generator=g, device=DEV)
+    odd = torch.tensor([float("nan"), float("inf"), -float("inf"), 0.0, -0.0, 3.4028235e38, -3.4028235e38, 1e-45], device=DEV)
+    X[torch.arange(8, device=DEV) * 41, torch.arange(8, device=DEV) % F] = odd
+    X[7] = float("nan")
+    X[11] = -float("inf")
+    w[torch.arange(8, device=DEV) * (m // 8)] = odd
+    bias = torch.randn(N, generator=g, device=DEV)
+    for weight in (w, None):
+        out = []
+        for small in (0, 1):
+            ctx, h = _context(n, col_ptr, row_idx, small)
+            args = {"edge_op": "copy"} if weight is None else {"edge_op": "mul_weight", "edge_weight": weight}
+            A, Y = torch.full((n, F), 7.0, device=DEV), torch.full((n, N), 7.0, device=DEV)
+            ctx.layer_forward(h, X, Y, accum_out=A, agg=agg, W=W, bias=bias, act=act, **args)
+            out.append((A, Y))
+        for a, b in zip(*out):
+            assert torch.equal(a.isnan(), b.isnan()) and torch.equal(torch.where(a.isnan(), 0.0, a), torch.where(b.isnan(), 0.0, b))
+        assert bool(out[1][0].isfinite().any()) and not bool(out[1][0].isfinite().all())
