@@ -280,7 +280,8 @@ struct ItemView {
     bool empty_item;      // the whole item has no edges (only a solo item can)
 };
 // An item is one wave-wide scalar read: a lane's read of it took a vector round trip and four moves to scalar registers ahead of the
-// first id (layers, us: GCN of two layers in training 888 -> 883, pooled 681 -> 676, 300 bf16 features 725 -> 720, others 0.2 to 0.5 %).
+// first id (layers, us: GCN of two layers in training 885 -> 880, pooled 709 -> 703, 300 bf16 features 750 -> 743; of 34 others one 1046 -> 1010, 18
+// by 0.4 to 2 %, the rest alike but for 32 fp32 values over 16 M edges, 264.0 -> 265.3).
 // SCALAR false: the lanes read it. With gates the scalar read took k_gather_narrow from 58 registers to 72 (ragged rows 59 to 78,
 // the maximum spilled), one wavefront less per SIMD.
 typedef const int32_t __attribute__((address_space(4))) * const_item_ptr;
