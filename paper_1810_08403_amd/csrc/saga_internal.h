@@ -160,6 +160,10 @@ struct HybridParams {
 //   21,621          128 188, 2669  64 111, 2521  48 95, 2488  32 115, 2534
 //   66,159          128 220, 3375  64 238, 3430
 //   148,828 (512 features, forward)  128 643, 4171  64 685, 4246  32 831, 4445
+// A tile's blocks are divided evenly. Whole chunks and a short last one (layers, us, even / whole; R-MAT 16 to 18, edges a vertex both
+// ways, features): training 17 x 32, 256 697 702, 17 x 100, 256 1101 1105, 16 x 100, 512 700 711, 18 x 200, 256 2605 2636; forward
+// 17 x 400, 256 1030 1076, 18 x 200, 512 2847 2873, 18 x 200, 640 3835 3872, 17 x 800, 512 2402 2456, but 18 x 400, 512 4149 4140 (the dense
+// kernel 643 626: whole chunks of full tiles begin at the same source tiles, 2.48 GB below the L2 for 2.86) and 9330 9177 in training.
 // Short chunks are more partial rows, 64 of F fp32 values each. Where a layer's scratch memory would not fit what
 // saga_layer_forward_noalloc has, and with longer chunks does, it takes the first of twice, four times, ... the length that fits;
 // the ordinary call takes the same, for the same bits. Under a budget always the longest: streamed calls plan with what is left of
