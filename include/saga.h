@@ -214,7 +214,8 @@ saga_status saga_layer_forward(saga_ctx* ctx, const saga_graph* g, const saga_te
 /*
  * The resident forward layer for callers that must not allocate: code under HIP graph
  * capture, tight serving loops, harnesses that forbid it. Same arguments, same kernels
- * and same results as saga_layer_forward, but everything the layer needs beyond its inputs
+ * and same results as saga_layer_forward (bf16 sums with dense blocks in other groups of
+ * fp32 partial sums where the usual ones do not fit, see "dense_chunk"), but everything the layer needs beyond its inputs
  * and outputs (the Gather output, the partial rows of cut columns, the packed weights, the
  * per-vertex products of gated and pooled layers) lives in one static device array of
  * 64 MiB (67,108,864 bytes) that the library holds on every GPU it runs on until the
@@ -415,9 +416,9 @@ saga_status saga_get_timings(saga_ctx* ctx, saga_timings* out); /* synchronises 
  *   "dense_min_edges"  edges from which a block goes to the matrix cores (0 = default 200; at most 2048)
  *   "dense_tile_gain"  edges beyond dense_min_edges, summed over the blocks of a destination tile, from which the tile
  *                uses the dense path at all (it costs a partial row per destination; -1 = default 512)
- *   "dense_chunk"  blocks of one destination tile worked by one workgroup (0, the default: 5 to 128, by their number; twice,
- *                four times, ... as many, up to 128, where the partial rows of the shorter chunks would not fit the scratch
- *                memory of saga_layer_forward_noalloc and those of the longer ones do; 128 in a context with a budget)
+ *   "dense_chunk"  blocks of one destination tile worked by one workgroup (0, the default: 5 to 128, by their number; in
+ *                saga_layer_forward_noalloc twice, four times, ... as many, up to 128, where the partial rows of the shorter
+ *                chunks would not fit its scratch memory and those of the longer ones do; 128 in a context with a budget)
  *   "dense_overlap"  0/1 (default 0): 1 runs the dense kernel on a second stream beside the sparse kernel (measured:
  *                no gain, the two fill the chip one after the other)
  *   "bwd_tile_rows"  streamed backward calls: rows per tile of the backward-ApplyVertex pass (default 0 = as

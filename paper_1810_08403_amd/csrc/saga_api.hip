@@ -738,14 +738,19 @@ static HybridParams hybrid_params(const saga_ctx* ctx)
 
 static size_t whole256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-// Which of the plan's chunk lengths a layer takes (see kDenseChunkMin)
-static int64_t chunk_length_for(const saga_ctx* ctx, const std::vector<HybridDevice::Length>& lengths, int32_t width, int64_t beside)
+// Would the partial rows fit the scratch memory of a call that must not allocate, beside what else the layer puts there?
+static bool fits_scratch(int64_t n_slots, int32_t width, int64_t beside)
 {
-    if (ctx->budget > 0) return lengths.back().length;
-    if (beside >= 0)
-        for (const HybridDevice::Length& l : lengths)
-            if ((size_t)beside + whole256(sizeof(float) * (size_t)l.n_slots * width) <= kScratchBytes) return l.length;
-    return lengths.front().length;
+    return (size_t)beside + whole256(sizeof(float) * (size_t)n_slots * width) <= kScratchBytes;
+}
+
+// Is the context's stream being captured into a graph (or can't that be asked just now)?
+static bool capturing(const saga_ctx* ctx)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 // The dense-block form of a resident graph for rows of `row_bytes` (the remainder's work list depends on the row width
@@ -773,15 +778,31 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     auto same = same_params;
     const bool there = h.built && same(p, h.list_params) && hp.min_block_edges == h.hp.min_block_edges &&
                        hp.min_tile_gain == h.hp.min_tile_gain && hp.max_chunk_blocks == h.hp.max_chunk_blocks;
+    // The lengths to be there after an ordinary call (see kDenseChunkMin): its own, and where that does not fit the scratch memory the
+    // first that does, for the call that must not allocate. The latter takes the shortest that is there and fits (one that another layer
+    // of this width made, whose vertex stage had other widths, will do).
+    auto find = [&](auto takes) {
+        const HybridCut* best = nullptr;
+        for (const HybridCut& c : h.cuts)
+            if (takes(c) && (!best || c.length < best->length)) best = &c;
+        return best;
+    };
+    auto own_length = [&] { return ctx->budget > 0 ? h.lengths.back().length : h.lengths.front().length; };
+    auto scratch_length = [&]() -> int64_t {  // 0: none that fits, or none needed
+        if (beside < 0 || ctx->budget > 0 || find([&](const HybridCut& c) { return fits_scratch(c.n_slots, width, beside); })) return 0;
+        for (const HybridDevice::Length& l : h.lengths)
+            if (fits_scratch(l.n_slots, width, beside)) return l.length;
+        return 0;
+    };
     if (there) {
         if (!h.usable) return SAGA_OK;
-        const int64_t length = chunk_length_for(ctx, h.lengths, width, beside);
-        for (const HybridCut& c : h.cuts)
-            if (c.length == length) *cut = &c;
-        if (*cut) return SAGA_OK;
-        if (ctx->arena_active)  // one that another layer made (its vertex stage had other widths) will do
-            for (const HybridCut& c : h.cuts)
-                if ((size_t)beside + whole256(sizeof(float) * (size_t)c.n_slots * width) <= kScratchBytes && (!*cut || c.length < (*cut)->length)) *cut = &c;
+        const HybridCut* own = find([&](const HybridCut& c) { return c.length == own_length(); });
+        if (ctx->arena_active) {
+            *cut = find([&](const HybridCut& c) { return fits_scratch(c.n_slots, width, beside); });
+            if (!*cut) *cut = own;  // (refused where its partial rows are carved)
+        } else if (own && (scratch_length() == 0 || capturing(ctx))) {
+            *cut = own;
+        }
         if (*cut) return SAGA_OK;
     }
     if (ctx->arena_active)
@@ -800,63 +821,70 @@ saga_status ensure_hybrid(saga_ctx* ctx, saga_graph* g, int64_t row_bytes, int32
     build_hybrid_plan(g->h_col_ptr.data(), h_row.data(), g->n, hp, &plan);
     if (plan.chunks.empty()) return SAGA_OK;  // nothing dense enough: the sparse kernel takes the whole graph
     WorkList wl;
-    build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
+    int64_t wl_length = 0;  // that wl was made for
     if (!there) {
+        build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
         // what longer chunks would take: the same pieces of the remainder, fewer rows of chunks
         const int64_t first = hp.max_chunk_blocks > 0 ? hp.max_chunk_blocks : dense_chunk_length((int64_t)plan.blk_src_tile.size());
         int64_t rows = 0;
         for (int32_t k : plan.extra_slots) rows += k;
         h.lengths.push_back({first, wl.n_slots});
+        wl_length = first;
         for (int64_t l = first; hp.max_chunk_blocks == 0 && l < kDenseChunkMax;) {
             l = std::min<int64_t>(2 * l, kDenseChunkMax);
             h.lengths.push_back({l, wl.n_slots - rows + divide_dense_blocks(&plan, g->n, l)});
         }
     }
-    HybridCut c;
-    c.length = chunk_length_for(ctx, h.lengths, width, beside);
-    divide_dense_blocks(&plan, g->n, c.length);
-    if (c.length != h.lengths.front().length) {
-        wl = WorkList{};
-        build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
-    }
-    // first partial row of every destination that has dense blocks, by destination rank
-    std::vector<int32_t> slot0_of((size_t)g->n, -1);
-    for (const HeavyVertex& hv : wl.heavy) slot0_of[(size_t)hv.v] = hv.slot0;
-    std::vector<int32_t> tile_row_slot0(plan.dst_order.size(), -1);
-    for (size_t i = 0; i < plan.dst_order.size(); ++i) {
-        const int32_t v = plan.dst_order[i];
-        if (v >= 0 && plan.extra_slots[(size_t)v] > 0) tile_row_slot0[i] = slot0_of[(size_t)v];
-    }
-    const int64_t n_items = (int64_t)wl.items.size();
-    wl.items.insert(wl.items.end(), wl.light.begin(), wl.light.end());  // one buffer for both
     auto up = [&](DevBuf* b, const void* src, size_t bytes) -> saga_status {
         if (saga_status st = ctx->dev_alloc(b, std::max<size_t>(bytes, 16))) return st;
         if (bytes) HIP_TRY(ctx, hipMemcpyAsync(b->p, src, bytes, hipMemcpyHostToDevice, ctx->stream));
         return SAGA_OK;
     };
-    saga_status st;
-    if ((st = up(&c.chunks, plan.chunks.data(), sizeof(DenseChunk) * plan.chunks.size())) ||
-        (st = up(&c.tile_row_slot0, tile_row_slot0.data(), 4 * tile_row_slot0.size())) ||
-        (st = up(&c.items, wl.items.data(), sizeof(WorkItem) * wl.items.size())) ||
-        (st = up(&c.heavy, wl.heavy.data(), sizeof(HeavyVertex) * wl.heavy.size()))) {
-        (void)hipStreamSynchronize(ctx->stream);
-        for (DevBuf* b : {&c.chunks, &c.tile_row_slot0, &c.items, &c.heavy}) ctx->dev_free(b);
+    auto add_cut = [&](const int64_t length) -> saga_status {
+        HybridCut c;
+        c.length = length;
+        divide_dense_blocks(&plan, g->n, length);
+        if (wl_length != length) build_work_list(plan.rem_col_ptr.data(), plan.rem_row_idx.data(), g->n, p, &wl, plan.extra_slots.data());
+        wl_length = 0;
+        // first partial row of every destination that has dense blocks, by destination rank
+        std::vector<int32_t> slot0_of((size_t)g->n, -1);
+        for (const HeavyVertex& hv : wl.heavy) slot0_of[(size_t)hv.v] = hv.slot0;
+        std::vector<int32_t> tile_row_slot0(plan.dst_order.size(), -1);
+        for (size_t i = 0; i < plan.dst_order.size(); ++i) {
+            const int32_t v = plan.dst_order[i];
+            if (v >= 0 && plan.extra_slots[(size_t)v] > 0) tile_row_slot0[i] = slot0_of[(size_t)v];
+        }
+        c.n_chunks = (int64_t)plan.chunks.size();
+        c.n_items = (int64_t)wl.items.size();
+        c.n_team = wl.n_team;
+        c.n_light = (int64_t)wl.light.size();
+        c.light_edges = wl.light_edges;
+        c.n_heavy = (int64_t)wl.heavy.size();
+        c.n_slots = wl.n_slots;
+        wl.items.insert(wl.items.end(), wl.light.begin(), wl.light.end());  // one buffer for both
+        h.cuts.reserve(h.cuts.size() + 1);
+        saga_status st;
+        if ((st = up(&c.chunks, plan.chunks.data(), sizeof(DenseChunk) * plan.chunks.size())) ||
+            (st = up(&c.tile_row_slot0, tile_row_slot0.data(), 4 * tile_row_slot0.size())) ||
+            (st = up(&c.items, wl.items.data(), sizeof(WorkItem) * wl.items.size())) ||
+            (st = up(&c.heavy, wl.heavy.data(), sizeof(HeavyVertex) * wl.heavy.size()))) {
+            (void)hipStreamSynchronize(ctx->stream);
+            for (DevBuf* b : {&c.chunks, &c.tile_row_slot0, &c.items, &c.heavy}) ctx->dev_free(b);
+            return st;
+        }
+        h.cuts.push_back(c);
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host vectors go out of scope
+        return SAGA_OK;
+    };
+    saga_status st = SAGA_OK;
+    if (!find([&](const HybridCut& c) { return c.length == own_length(); })) st = add_cut(own_length());
+    if (const int64_t length = st ? 0 : scratch_length()) st = add_cut(length);
+    if (st) {
         if (!there) hybrid_free(ctx, &h);
         return st;
     }
-    c.n_chunks = (int64_t)plan.chunks.size();
-    c.n_items = n_items;
-    c.n_team = wl.n_team;
-    c.n_light = (int64_t)wl.light.size();
-    c.light_edges = wl.light_edges;
-    c.n_heavy = (int64_t)wl.heavy.size();
-    c.n_slots = wl.n_slots;
-    h.cuts.push_back(c);
-    *cut = &h.cuts.back();
-    if (there) {
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host vectors go out of scope below
-        return SAGA_OK;
-    }
+    *cut = find([&](const HybridCut& c) { return c.length == own_length(); });
+    if (there) return SAGA_OK;
     if ((st = up(&h.blk_src_tile, plan.blk_src_tile.data(), 4 * plan.blk_src_tile.size())) ||
         (st = up(&h.blk_e0, plan.blk_e0.data(), 4 * plan.blk_e0.size())) ||
         (st = up(&h.blk_tile, plan.blk_tile.data(), 4 * plan.blk_tile.size())) ||

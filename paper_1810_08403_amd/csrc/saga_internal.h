@@ -165,9 +165,11 @@ struct HybridParams {
 // 17 x 400, 256 1030 1076, 18 x 200, 512 2847 2873, 18 x 200, 640 3835 3872, 17 x 800, 512 2402 2456, but 18 x 400, 512 4149 4140 (the dense
 // kernel 643 626: whole chunks of full tiles begin at the same source tiles, 2.48 GB below the L2 for 2.86) and 9330 9177 in training.
 // Short chunks are more partial rows, 64 of F fp32 values each. Where a layer's scratch memory would not fit what
-// saga_layer_forward_noalloc has, and with longer chunks does, it takes the first of twice, four times, ... the length that fits;
-// the ordinary call takes the same, for the same bits. Under a budget always the longest: streamed calls plan with what is left of
-// it. (65,536 vertices, R-MAT of 32 edges both ways, 256 bf16 features: 55 to 62 MiB with chunks of 128, 67 or more with 9.)
+// saga_layer_forward_noalloc has, and with twice, four times, ... the length it does, the first of those that fits is made beside it, for
+// that call alone (65,536 vertices, R-MAT of 32 edges both ways, 256 bf16 features: 55 to 62 MiB with chunks of 128, 67 or more with 9).
+// With one division for both calls, their bits the same, the ordinary one was slower: forward, us, short / first that fits, 16,384
+// vertices of 200 edges both ways, 512 features 139 272, of 100, 640 157 210, 32,768 of 200, 256 149 165. Under a budget always
+// the longest: streamed calls plan with what is left of it.
 constexpr int kDenseChunkMin = 5, kDenseChunkMax = 128, kDenseResident = 2 * 256;
 // A block's weights reach the kernel in one of two forms: as a list of (cell, weight) pairs that the workgroup scatters
 // into a cleared LDS operand (blocks of up to kDenseListMax edges: one pair per thread), or, for fuller blocks, as the

@@ -20,8 +20,8 @@ from stub_binding import StubContext, dev
 
 def dense_blocks_near_the_limit(lib, rng):
     """bf16 sums whose dense blocks, in chunks of the length that is taken by their number, write more partial rows than the
-    scratch array holds, and in longer chunks do not: accepted, with the ordinary call's bits; and in a context with a budget, no more
-    partial rows than the longest chunks write."""
+    scratch array holds, and in longer chunks do not: accepted, in those chunks, while the ordinary call keeps the short ones; and in a
+    context with a budget, no more partial rows than the longest chunks write."""
     src, dst = si.rmat_edges(9, 40 << 9, 909)
     g = si.build_csc(1 << 9, src, dst, symmetrise=True, self_loops=True)
 
@@ -58,24 +58,46 @@ def dense_blocks_near_the_limit(lib, rng):
     assert mib(rows[128], wide) < mib(rows[10], wide) + beside < 64 < mib(rows[5], wide) + beside and mib(rows[5], wide) < 64, rows
     assert mib(rows[5], 16384) > 64 > mib(rows[10], 16384)
     checked = 0
-    for F, Fo, budget, length in ((wide, 3, 0, 10), (16384, 0, 0, 10), (narrow, 3, 0, 5), (narrow, 3, 1 << 30, 128)):
+    # the ordinary call's chunks, those of the call that must not allocate
+    for F, Fo, budget, length, fits in ((wide, 3, 0, 5, 10), (16384, 0, 0, 5, 10), (narrow, 3, 0, 5, 5), (narrow, 3, 1 << 30, 128, 128)):
         ctx, h = context(budget)
         call = layer(F, Fo)
         Y0, _, n0 = call(ctx, h)
         Y1, _, n1 = call(ctx, h, no_alloc=True)
-        assert n0 == n1 == rows[length], (F, Fo, budget, n0, n1, rows)
-        assert torch.equal(Y0, Y1)
+        Y2, calls, n2 = call(ctx, h)
+        assert n0 == n2 == rows[length] and n1 == rows[fits] and calls == 0, (F, Fo, budget, n0, n1, n2, rows)
+        assert torch.equal(Y0, Y2)
+        if length == fits:
+            assert torch.equal(Y0, Y1)
+        else:   # other groups of the same fp32 sums, rounded to bf16 before the product and behind it
+            assert float((Y0.double() - Y1.double()).norm() / Y0.double().norm()) < 2.0 ** -8
         h.destroy()
         ctx.destroy()
         checked += 1
-    # two layers of one width, of which one fits with the shortest chunks and the other does not: a call that finds only the other's
-    # chunks takes those, and each keeps its own
+    # two layers of one width, of which one fits with the shortest chunks and the other does not: made at the ordinary call that needs
+    # them, but not while its stream is captured; a call that must not allocate takes the shortest that are there and fit
     ctx, h = context()
     with_w, without = layer(wide, 3), layer(wide, 0)
-    assert with_w(ctx, h)[2] == without(ctx, h, no_alloc=True)[2] == rows[10]
-    Y = without(ctx, h)[0]
-    assert torch.equal(without(ctx, h, no_alloc=True)[0], Y)
+    first = without(ctx, h)[0]
+    assert torch.equal(without(ctx, h, no_alloc=True)[0], first)
+    try:
+        with_w(ctx, h, no_alloc=True)
+        raise AssertionError("chunks that nothing has made yet were taken")
+    except B.SagaError as e:
+        assert e.status == 4, e
+    large = layer(wide, 3)
+    large(ctx, h)                                  # (grows the workspaces, and makes the longer chunks)
+    h.destroy()
+    h = ctx.graph_create_csc(g.n, dev(g.col_ptr), dev(g.row_idx))
+    without(ctx, h)
+    ctx.lib.stub_set_capturing(1)
+    _, calls, n = with_w(ctx, h)
+    assert calls == 0 and n == rows[5], "a plan was built while a stream was captured"
+    ctx.lib.stub_set_capturing(0)
+    _, calls, n = with_w(ctx, h)
+    assert calls > 0 and n == rows[5]
     assert with_w(ctx, h, no_alloc=True)[2] == rows[10]
+    assert without(ctx, h, no_alloc=True)[2] == rows[5]
     assert with_w(ctx, h)[1] == without(ctx, h)[1] == 0, "a plan that was there is built again"
     h.destroy()
     ctx.destroy()

@@ -332,6 +332,14 @@ hipError_t hipStreamSynchronize(hipStream_t s)
     run_until(s, s->enq);
     return hipSuccess;
 }
+static bool g_capturing = false;
+extern "C" void stub_set_capturing(int on) { g_capturing = on != 0; }  // what every stream answers; nothing is recorded
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status)
+{
+    (void)at(s);
+    *status = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
 {
     s = at(s);
