@@ -1728,38 +1728,45 @@ static bool small_layer(const saga_ctx* ctx, const saga_graph* g, const saga_ten
     if ((ep->op != SAGA_EDGE_COPY && ep->op != SAGA_EDGE_MUL_WEIGHT) || X->dtype != SAGA_F32) return false;
     if (g->nnz == 0 || g->nnz >= (1LL << 30) - 64 || X->cols < kSmallMinF || X->cols > kSmallMaxF) return false;
     if (((g->n - 1) * X->ld + X->cols) * 4 >= 0xffff0000LL) return false;
-    // Whole columns, weights that fit its LDS as split units, and what its time goes by: the steps a wavefront takes one after the
-    // other, four, two or one edges each (rows of up to 16, 32 and 64 values) or one edge in two passes. All 8,192 rows that 256
-    // workgroups hold run at once, and the longest column decides with the average one; of more rows, some wait for others.
-    // Times of a call, one launch over several, median and 95th of 100, of 25,000 layers of 256 to 32,768 vertices, 13 to 128
-    // features, 3 to 256 outputs, columns all alike, random and skewed, by the steps (several launches are 15 us or more):
-    //                                          < 30       60         90         120        180        250        400
-    //    8,192 rows, up to 16 units of W        .65 .68    .66 .70    .67 .74    .75 .85    .78 .89    .89 1.02   .98 1.12
-    //                more, > 64 features        .67 .76    .70 .79    .77 .84    .82 .89    .84 .95    .91 1.10  1.10 1.22
-    //                more, up to 64             .67 .73    .71 .80    .80 .88    .85 1.00   .93 1.05
-    //   16,384 rows, up to 8 units              .65 .72    .69 .82    .75 .90    .78 .90    .84 .98    .88 1.06   .98 1.12
-    //                9 to 16, up to 64          .65 .75    .70 .78    .73 .85    .80 .95    .90 1.03
-    //                9 to 16, > 64              .61 .66    .62 .69    .65 .76    .61 .75    .70 .83    .82 .98    .87 1.02
-    //                more, or > 128 outputs     .92 1.05   .96 1.09  1.01 1.18
-    //   24,576 rows, up to 64                   .69 .81    .77 .90    .86 1.01   .92 1.02   .97 1.09
-    //                > 64                       .86 .92    .86 .95    .88 1.01
-    //   32,768 rows, up to 64                   .75 .89    .86 .98    .95 1.09  1.00 1.10
-    //                > 64                       .98 1.06   .93 1.08
+    // Whole columns, weights that fit its LDS as split units, and what its time goes by: how many workgroups of 32 columns a compute
+    // unit has to hold (more than fit it are a second round: 0.95 to 1.5 times the time of several launches), and the steps a
+    // wavefront takes one after the other, four, two or one edges each (rows of up to 16, 32 and 64 values) or one edge in two
+    // passes, of the longest column and the average one. Times of a call, one launch over several, median and 95th of 100, of 59,000
+    // layers of 256 to 32,768 vertices, 13 to 128 features, 3 to 256 outputs, columns all alike, random and skewed, by workgroups
+    // a compute unit, tiles of 32 outputs, and steps (several launches are 15 us or more; these launches up to 40):
+    //      steps of                         < 30       60         110        150        200        260        400
+    //   1, n <= 2048  1 to 2 tiles        .64 .67    .64 .68    .67 .74    .75 .84    .83 .91    .91 .99   1.00 1.11
+    //                 3 to 4              .65 .72    .66 .77    .75 .84    .85 .92    .92 1.00   .99 1.08  1.09 1.18
+    //                 5 to 8              .65 .71    .68 .79    .79 .89    .89 .98    .98 1.06
+    //   1, more                           .64 .67    .64 .70    .65 .77    .70 .81    .74 .86    .78 .91    .82 .97
+    //   2             1, n <= 12,288      .65 .74    .71 .79    .80 .89    .88 .96    .94 1.03   .99 1.08  1.03 1.10
+    //                 1, more             .65 .77    .71 .81    .78 .86    .85 .91    .89 .94    .91 .95    .92 .96
+    //                 2                   .61 .72    .65 .77    .72 .81    .77 .86    .81 .90    .88 .94    .89 .95
+    //                 3 to 4              .69 .80    .76 .87    .82 .93    .89 1.00
+    //                 5 to 8              .94 1.04   .98 1.11  1.04 1.15
+    //   3             1                   .72 .93    .84 .93    .91 1.02   .96 1.07  1.00 1.10
+    //                 2                   .72 .90    .79 .89    .85 .94    .94 1.02   .98 1.07
+    //                 3 to 4              .78 .91    .82 .98    .90 1.01
+    //                 5 to 8             1.08 1.21  1.16 1.24
+    //   4, F <= 64    1 to 2              .79 1.00   .88 .98    .98 1.06  1.02 1.10
+    //                 3 to 4              .86 .98    .97 1.06
+    //   4, F > 64                        1.03 1.13   .95 1.09   .97 1.05  1.01 1.07
     const int64_t F = X->cols, N = vp->W->cols, n = g->n;
-    const int64_t units = (N + 31) / 32 * ((F + 31) / 32 * 2);
+    const int64_t tiles = (N + 31) / 32, units = tiles * ((F + 31) / 32 * 2);
     if (n_slots > 0 || g->max_degree > 96 || N > kSmallMaxN || units > kSmallUnits || n > 32768) return false;
-    const int64_t average = g->nnz / n;
-    const int64_t steps = (n <= 8192 ? g->max_degree + average : g->max_degree / 2 + 2 * average) * (F > 64 ? 2 : 1) / (F <= 16 ? 4 : F <= 32 ? 2 : 1);
-    int64_t limit;
-    if (n <= 8192)
-        limit = units <= 16 ? 200 : F > 64 ? 180 : 110;
-    else if (units > 16 || N > 128)
-        limit = -1;
-    else if (n <= 16384)
-        limit = units <= 8 ? 180 : F > 64 ? 250 : 120;
-    else
-        limit = n > 24576 && F > 64 ? -1 : 60;
-    if (steps > limit || (n > 16384 && n * F * N > 1LL << 25)) return false;
+    const int64_t held = ((n + kSmallRows - 1) / kSmallRows + 255) / 256, lds = small_layer_lds(F, N) + 4 * kSmallRows;
+    if (held > 4 || held * lds > 160 * 1024) return false;
+    const int64_t steps = (g->max_degree + g->nnz / n) * (F > 64 ? 2 : 1) / (F <= 16 ? 4 : F <= 32 ? 2 : 1), any = 400;
+    int64_t limit = -1;
+    if (held == 1)
+        limit = n > 2048 ? any : tiles <= 2 ? 260 : tiles <= 4 ? 200 : 150;
+    else if (held == 2 && tiles <= 4)
+        limit = tiles == 2 || (tiles == 1 && n > 12288) ? any : 150;
+    else if (held == 3 && tiles <= 4)
+        limit = tiles == 2 ? 110 : 80;
+    else if (held == 4 && tiles <= 4 && F <= 64)
+        limit = tiles <= 2 ? 60 : 30;
+    if (steps > limit) return false;
     // Sums of rows of eight fragments over 32,768 columns of at most 16 edges: k_gather_light adds a column in one chain there (see
     // takes_light and launch_light), this kernel in eight sums.
     if (ga.agg == SAGA_AGG_SUM && (F + 3) / 4 == 8 && ga.n_light >= 32768) return false;

@@ -475,6 +475,11 @@ struct SmallLayerArgs {
 constexpr int kSmallMinF = 13, kSmallMaxF = 128;  // rows of 4 to 32 fragments
 constexpr int kSmallMaxN = 256;                    // 32 columns a wavefront
 constexpr int kSmallUnits = 32;                    // 32 columns x 16 k of the weights, 3 KiB of LDS each
+constexpr int kSmallRows = 32;                     // columns of the graph (rows of the product) per workgroup
+inline int64_t small_layer_lds(int64_t F, int64_t N)  // dynamic LDS of a workgroup: units of the weights, and rows
+{
+    return (F + 31) / 32 * 2 * ((N + 31) / 32) * 3072 + kSmallRows * ((F + 31) / 32 * 32 + 4) * 4;
+}
 hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s);
 
 struct CombineArgs {

@@ -13,7 +13,6 @@ typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kSmallRows = 32;  // columns of the graph (rows of the product) per workgroup
 constexpr uint32_t kPastTheEnd = 0xffff0000u;  // an offset past every table this kernel takes, whatever is added for the lane
 
 template <int AGG>
@@ -260,7 +259,7 @@ hipError_t launch_layer_small(const SmallLayerArgs& a, hipStream_t s)
     while ((1 << p2_log2) < nvec) ++p2_log2;
     const dim3 grid((unsigned)((a.n_items + kSmallRows - 1) / kSmallRows));
     const uint32_t xb = (uint32_t)x_bytes, ib = (uint32_t)(a.n_edges * 4);
-    const size_t lds = (size_t)n_units * 3 * 1024 + kSmallRows * ((a.F + 31) / 32 * 32 + 4) * 4;
+    const size_t lds = (size_t)small_layer_lds(a.F, a.N);
     auto go = [&](auto agg_c, auto lpr_c) -> hipError_t {
         constexpr int AGG = decltype(agg_c)::value, LPR = decltype(lpr_c)::value;
         static PerDevice lds_raised;

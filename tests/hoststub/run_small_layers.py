@@ -104,21 +104,24 @@ def main():
     light = graph(32768, 2)
     for F, agg, one in ((28, "sum", True), (29, "sum", False), (32, "sum", False), (32, "max", True), (33, "sum", True)):
         layer(light, F, 8, one, agg=agg, place="no A")
-    # as many steps in a row as are faster than several launches: two passes of rows of more than 64 values, longest and average column
-    # alike (99 edges: 198 of at most 200), or four edges a step
-    edge, past = graph(300, 49), graph(300, 50)
-    layer(edge, 128, 16, True)                    # 2 x (50 + 49)
-    layer(past, 128, 16, False)                   # 2 x (51 + 50)
-    layer(past, 65, 65, False)                    # 18 units of weights: 180
-    layer(past, 64, 160, True)                    # 101 of 110
-    layer(past, 64, 16, True)
-    # more rows than run at once: longest / 2 + 2 x average
-    many, full = graph(8193, 45), graph(16385, 24)
-    for F, N, one in ((64, 32, True), (64, 128, True), (16, 128, True), (16, 129, False), (64, 129, False), (128, 16, False), (65, 33, True)):
-        layer(many, F, N, one, place="no A")      # 113, twice that past 64 values
-    for F, N, one in ((33, 16, True), (64, 16, True), (65, 16, False)):
-        layer(full, F, N, one, place="no A")      # 60, 120
-    for x in (edge, past, many, full):
+    # as many steps in a row as are faster than several launches, of the longest column and the average one: two passes of rows of more
+    # than 64 values, up to 260, 200 and 150 with one or two, up to four and more tiles of 32 outputs
+    for deg, F, N, one in ((64, 128, 16, True), (65, 128, 16, False), (65, 64, 16, True), (49, 65, 65, True), (50, 65, 65, False),
+                           (74, 64, 160, True), (75, 64, 160, False)):
+        x = graph(300, deg)
+        layer(x, F, N, one)
+        x[3].destroy()
+    # no limit where the rows are a workgroup per compute unit; two to a unit, three and four, and not more than LDS holds
+    for n, deg, cases in ((2049, 94, ((128, 128, True), (64, 256, True))),
+                          (8193, 45, ((64, 32, True), (64, 128, True), (16, 128, True), (16, 129, False), (64, 129, False), (128, 16, False), (65, 33, True),
+                                      (97, 65, False))),
+                          (12289, 45, ((128, 16, True),)),
+                          (16385, 24, ((33, 16, True), (64, 16, True), (65, 16, False), (65, 64, True), (33, 96, False))),
+                          (24577, 14, ((64, 64, True), (65, 16, False), (32, 96, True), (33, 96, False), (32, 160, False))),
+                          (24577, 30, ((64, 64, False), (32, 64, True), (32, 96, False)))):
+        x = graph(n, deg)
+        for F, N, one in cases:
+            layer(x, F, N, one, place="no A")
         x[3].destroy()
     for x in (g, long, longer, light):
         x[3].destroy()
