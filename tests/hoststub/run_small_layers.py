@@ -116,9 +116,9 @@ def main():
                           (8193, 45, ((64, 32, True), (64, 128, True), (16, 128, True), (16, 129, False), (64, 129, False), (128, 16, False), (65, 33, True),
                                       (97, 65, False))),
                           (12289, 45, ((128, 16, True),)),
-                          (16385, 24, ((33, 16, True), (64, 16, True), (65, 16, False), (65, 64, True), (33, 96, False))),
+                          (16385, 24, ((33, 16, True), (64, 16, True), (65, 16, False), (65, 64, True), (33, 96, True), (33, 97, False))),
                           (24577, 14, ((64, 64, True), (65, 16, False), (32, 96, True), (33, 96, False), (32, 160, False))),
-                          (24577, 30, ((64, 64, False), (32, 64, True), (32, 96, False)))):
+                          (24577, 31, ((64, 64, False), (32, 64, True), (32, 96, False)))):
         x = graph(n, deg)
         for F, N, one in cases:
             layer(x, F, N, one, place="no A")
